@@ -317,18 +317,6 @@ __global__ void k_bits_select(const uint8_t *bits, int64_t n_qubits, int64_t row
 // Block b covers samples [b c, min(n, (b+1) c)), c = ceil(n / P).
 constexpr int SN = 256;
 constexpr int SW = 1024;  // weights staged in LDS per chunk (z_is pass)
-__device__ double block_sum(double v, double *red) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int h = SN / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    const double r = red[0];
-    __syncthreads();
-    return r;
-}
-
 __device__ inline void stats_range(int64_t n, int P, int64_t &beg, int64_t &end) {
     const int64_t c = (n + P - 1) / P;
     beg = (int64_t)blockIdx.x * c;
@@ -351,69 +339,105 @@ __global__ void __launch_bounds__(SN) k_stats_max(const double *lq, const double
     if (threadIdx.x == 0) pmax[blockIdx.x] = red[0];
 }
 
-__global__ void __launch_bounds__(SN) k_stats_sums(const double *lq, const double *lp, int64_t n, double logZ,
-                                                   const uint8_t *bits, int64_t nq, int P, const double *pmax,
-                                                   double *psum, double *pz) {
-    __shared__ double red[SN];
+// The largest partial maximum, by the first wave; the block receives it.
+__device__ double stats_top(const double *pmax, int P) {
+    static_assert(STATS_BLOCKS_MAX <= 64, "one lane per block's maximum");
+    __shared__ double top;
+    if (threadIdx.x < 64) {
+        double m = (int)threadIdx.x < P ? pmax[threadIdx.x] : -INFINITY;
+        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+        if (threadIdx.x == 0) top = m;
+    }
+    __syncthreads();
+    return top;
+}
+
+// Workgroup (b, 0) forms the scalar sums of sample block b, workgroup (b, y > 0)
+// the weighted bit sums of SQ qubits over the same samples: SZ lanes per qubit,
+// each with every SZ-th sample of the block, added in a fixed tree.  Bound by
+// the latency of its loads: a lane per qubit alone walked the block's 1024
+// samples in one chain (the whole call took 141 us at 4096 samples of 144
+// qubits, 38 us with this split).  It is a split within the block, so the
+// partials stay P x nq.
+constexpr int SQ = 16, SZ = 64;
+__global__ void __launch_bounds__(SQ * SZ) k_stats_sums(const double *lq, const double *lp, int64_t n, double logZ,
+                                                        const uint8_t *bits, int64_t nq, int P, const double *pmax,
+                                                        double *psum, double *pz) {
     __shared__ double wl[SW];
-    double top = -INFINITY;
-    for (int b = 0; b < P; ++b) top = fmax(top, pmax[b]);
+    __shared__ double red[SZ][SQ + 1];
+    const double top = stats_top(pmax, P);
     int64_t beg, end;
     stats_range(n, P, beg, end);
-    double s1 = 0.0, s2 = 0.0, kl = 0.0;
-    for (int64_t i = beg + threadIdx.x; i < end; i += SN) {
-        const double w = exp(lp[i] - lq[i] - top);
-        s1 += w;
-        s2 += w * w;
-        kl += lq[i] - lp[i] + logZ;
-    }
-    s1 = block_sum(s1, red);
-    s2 = block_sum(s2, red);
-    kl = block_sum(kl, red);
-    if (threadIdx.x == 0) {
-        psum[3 * blockIdx.x] = s1;
-        psum[3 * blockIdx.x + 1] = s2;
-        psum[3 * blockIdx.x + 2] = kl;
-    }
-    if (!pz) return;
-    double *zb = pz + (int64_t)blockIdx.x * nq;
-    for (int64_t q = threadIdx.x; q < nq; q += SN) zb[q] = 0.0;  // each (block, q) is owned by one thread
-    for (int64_t c0 = beg; c0 < end; c0 += SW) {
-        const int len = (int)(end - c0 < SW ? end - c0 : SW);
-        __syncthreads();
-        for (int i = threadIdx.x; i < len; i += SN) wl[i] = exp(lp[c0 + i] - lq[c0 + i] - top);
-        __syncthreads();
-        for (int64_t q = threadIdx.x; q < nq; q += SN) {
-            double acc = 0.0;
-            for (int i = 0; i < len; ++i) acc += bits[(c0 + i) * nq + q] ? -wl[i] : wl[i];
-            zb[q] += acc;
+    const int t = threadIdx.x;
+    if (blockIdx.y == 0) {
+        double s[3] = {0.0, 0.0, 0.0};
+        for (int64_t i = beg + t; i < end; i += SQ * SZ) {
+            const double w = exp(lp[i] - lq[i] - top);
+            s[0] += w;
+            s[1] += w * w;
+            s[2] += lq[i] - lp[i] + logZ;
         }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            s[k] = wsum(s[k]);
+            if ((t & 63) == 0) red[t >> 6][k] = s[k];
+        }
+        __syncthreads();
+        if (t < 3) {
+            double v = 0.0;
+            for (int i = 0; i < SQ * SZ / 64; ++i) v += red[i][t];
+            psum[3 * blockIdx.x + t] = v;
+        }
+        return;
+    }
+    const int ql = t % SQ, sl = t / SQ;
+    for (int64_t q0 = (int64_t)(blockIdx.y - 1) * SQ; q0 < nq; q0 += (int64_t)(gridDim.y - 1) * SQ) {
+        const int64_t q = q0 + ql;
+        double acc = 0.0;
+        for (int64_t c0 = beg; c0 < end; c0 += SW) {
+            const int len = (int)(end - c0 < SW ? end - c0 : SW);
+            __syncthreads();
+            for (int i = t; i < len; i += SQ * SZ) wl[i] = exp(lp[c0 + i] - lq[c0 + i] - top);
+            __syncthreads();
+            if (q < nq) {
+#pragma unroll 4
+                for (int i = sl; i < len; i += SZ) acc += bits[(c0 + i) * nq + q] ? -wl[i] : wl[i];
+            }
+        }
+        red[sl][ql] = acc;
+        __syncthreads();
+        for (int h = SZ / 2; h > 0; h >>= 1) {
+            if (sl < h) red[sl][ql] += red[sl + h][ql];
+            __syncthreads();
+        }
+        if (sl == 0 && q < nq) pz[(int64_t)blockIdx.x * nq + q] = red[0][ql];
     }
 }
 
 __global__ void __launch_bounds__(SN) k_stats_final(const double *psum, const double *pz, int P, int64_t n,
                                                     int64_t nq, const double *pmax, double *out, double *z_is) {
-    __shared__ double s1s;
-    if (threadIdx.x == 0) {
-        double top = -INFINITY, s1 = 0.0, s2 = 0.0, kl = 0.0;
-        for (int b = 0; b < P; ++b) {
-            top = fmax(top, pmax[b]);
-            s1 += psum[3 * b];
-            s2 += psum[3 * b + 1];
-            kl += psum[3 * b + 2];
-        }
+    __shared__ double part[3 * STATS_BLOCKS_MAX];
+    const double top = stats_top(pmax, P);
+    for (int i = threadIdx.x; i < 3 * P; i += SN) part[i] = psum[i];
+    __syncthreads();
+    double s1 = 0.0, s2 = 0.0, kl = 0.0;
+    for (int b = 0; b < P; ++b) {
+        s1 += part[3 * b];
+        s2 += part[3 * b + 1];
+        kl += part[3 * b + 2];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         out[0] = top + log(s1 / (double)n);
         out[1] = kl / (double)n;
         out[2] = s1 * s1 / s2;
-        s1s = s1;
     }
-    __syncthreads();
     if (!z_is) return;
-    for (int64_t q = threadIdx.x; q < nq; q += SN) {
-        double acc = 0.0;
-        for (int b = 0; b < P; ++b) acc += pz[(int64_t)b * nq + q];
-        z_is[q] = acc / s1s;
-    }
+    const int64_t q = (int64_t)blockIdx.x * SN + threadIdx.x;
+    if (q >= nq) return;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < P; ++b) acc += pz[(int64_t)b * nq + q];
+    z_is[q] = acc / s1;
 }
 
 // Fingerprint of raw tensor bytes: acc += sum_i mix(word_i, salt + i), with
@@ -584,9 +608,13 @@ hipError_t launch_sample_stats(const double *log_q, const double *log_p, int64_t
     double *psum = pmax + P;
     double *pz = z_is ? psum + 3 * P : nullptr;
     hipLaunchKernelGGL(k_stats_max, dim3(P), dim3(SN), 0, s, log_q, log_p, n, P, pmax);
-    hipLaunchKernelGGL(k_stats_sums, dim3(P), dim3(SN), 0, s, log_q, log_p, n, log_Z, z_is ? bits : nullptr,
+    // grid.y: the scalar sums and one workgroup per SQ qubits (they loop past 65534)
+    int64_t zc = z_is ? (n_qubits + SQ - 1) / SQ : 0;
+    if (zc > 65534) zc = 65534;
+    hipLaunchKernelGGL(k_stats_sums, dim3(P, (unsigned)(1 + zc)), dim3(SQ * SZ), 0, s, log_q, log_p, n, log_Z, bits,
                        n_qubits, P, pmax, psum, pz);
-    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(SN), 0, s, psum, pz, P, n, n_qubits, pmax, out, z_is);
+    const int64_t fb = z_is ? (n_qubits + SN - 1) / SN : 1;
+    hipLaunchKernelGGL(k_stats_final, dim3((unsigned)fb), dim3(SN), 0, s, psum, pz, P, n, n_qubits, pmax, out, z_is);
     return hipGetLastError();
 }
 
