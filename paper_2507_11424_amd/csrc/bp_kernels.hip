@@ -21,10 +21,6 @@ __device__ inline double2 cscale(double2 a, double s) { return make_double2(a.x 
 __device__ inline double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 __device__ inline double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
 __device__ inline double cabsv(double2 a) { return hypot(a.x, a.y); }
-__device__ inline double2 cdiv(double2 a, double2 b) {
-    const double d = cabs2(b);
-    return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
-}
 __device__ inline double2 csqrt(double2 z) {
     const double r = cabsv(z);
     if (r == 0.0) return make_double2(0.0, 0.0);
@@ -165,77 +161,133 @@ __global__ void __launch_bounds__(NT) k_gather_mats(const double2 *pairs, const 
     }
 }
 
-// Eigenvalues of one general complex n x n matrix per lane (the matrix is
+// Eigenvalues of one general complex n x n matrix per workgroup (the matrix is
 // overwritten): Householder reduction to upper Hessenberg form, then the
 // shifted QR algorithm with Givens rotations on the active window, Wilkinson
 // shifts (an exceptional shift every 11th iteration without deflation) and
 // deflation when |h[k][k-1]| <= eps (|h[k][k]| + |h[k-1][k-1]|) (Golub and Van
 // Loan, Matrix Computations, 7.4-7.5).  eps[q] = 1 - max|lambda| / sum|lambda|;
 // info[q] = 0, or 1 if the iteration limit (30 n per eigenvalue) was hit.
-__global__ void k_eig(double2 *mats, int n, int batch, double2 *lam, double *eps, int *info) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= batch) return;
-    double2 *H = mats + (int64_t)q * n * n;
-    double2 *L = lam + (int64_t)q * n;
-#define AT(i, j) H[(int64_t)(i) * n + (j)]
+//
+// Bound by the chain of rotations, one square root and one division each: NT
+// lanes share every other part.  A lane owns one column in the products from
+// the left (it carries the column's entry of the current row in registers, so
+// a rotation reads one new row) and one row in those from the right; the
+// rotation is formed by every lane from its owner's two entries.  Up to 64
+// columns one wave does it, without barriers, the entries handed round by
+// lane reads; above, four waves through LDS.  The matrix sits in LDS up to
+// EIG_LDS_N columns (row length n + 1: a lane per row reads without bank
+// conflicts), else in place.  tn_bp on a 12 x 12 brick at D = 8 (its 55 loop
+// matrices have n = 64) went from 195 ms, one lane per matrix, to 36 ms.
+// The matrix is first scaled by a power of two to entries of at most 1, so the
+// squares of entries underflow only below 1e-154 of the largest.
+constexpr int EIG_LDS_N = 96;
+__device__ inline double2 lane_read(double2 v, int lane) {
+    const int2 a = __builtin_bit_cast(int2, v.x), b = __builtin_bit_cast(int2, v.y);
+    const int2 c = make_int2(__builtin_amdgcn_readlane(a.x, lane), __builtin_amdgcn_readlane(a.y, lane));
+    const int2 d = make_int2(__builtin_amdgcn_readlane(b.x, lane), __builtin_amdgcn_readlane(b.y, lane));
+    return make_double2(__builtin_bit_cast(double, c), __builtin_bit_cast(double, d));
+}
+
+template <int NTH, bool IN_LDS>
+__global__ void __launch_bounds__(NTH) k_eig(double2 *mats, int n, double2 *lam, double *eps, int *info) {
+    extern __shared__ double2 hl[];
+    constexpr int NW = NTH / 64;
+    __shared__ double2 va[NTH], vb[NTH];   // reflector; rotations x / r, y / r
+    __shared__ double2 ls[NTH];            // eigenvalues of the scaled matrix
+    __shared__ double2 hand[2][2];         // the current rotation's entries (NW > 1)
+    __shared__ double red[NW];
+    __shared__ int redi[NW];
+    const int q = blockIdx.x, t = threadIdx.x;
+    double2 *G = mats + (int64_t)q * n * n;
+    double2 *H = IN_LDS ? hl : G;
+    const int ld = IN_LDS ? n + 1 : n;
+#define AT(i, j) H[(int64_t)(i) * ld + (j)]
+    auto reduce = [&](double v, bool mx) {  // sum or maximum over the block, to every thread
+        for (int o = 32; o > 0; o >>= 1) {
+            const double u = __shfl_xor(v, o);
+            v = mx ? fmax(v, u) : v + u;
+        }
+        if constexpr (NW > 1) {
+            __syncthreads();
+            if ((t & 63) == 0) red[t >> 6] = v;
+            __syncthreads();
+            v = red[0];
+            for (int i = 1; i < NW; ++i) v = mx ? fmax(v, red[i]) : v + red[i];
+        }
+        return v;
+    };
+    double big = 0.0;
+    for (int e = t; e < n * n; e += NTH) big = fmax(big, fmax(fabs(G[e].x), fabs(G[e].y)));
+    big = reduce(big, true);
+    int ex = 0;
+    if (big > 0.0 && isfinite(big)) ex = ilogb(big);
+    for (int e = t; e < n * n; e += NTH) {
+        const double2 g = G[e];
+        AT(e / n, e % n) = make_double2(ldexp(g.x, -ex), ldexp(g.y, -ex));
+    }
+    __syncthreads();
     // Householder to Hessenberg: zero H[k+2.., k]
     for (int k = 0; k + 2 < n; ++k) {
-        double xn2 = 0.0;
-        for (int i = k + 1; i < n; ++i) xn2 += cabs2(AT(i, k));
-        const double xn = sqrt(xn2);
+        const double2 x = t > k && t < n ? AT(t, k) : make_double2(0.0, 0.0);
+        const double tail2 = reduce(t > k + 1 ? cabs2(x) : 0.0, false);
+        if (tail2 <= 1e-300) continue;  // uniform
         const double2 x0 = AT(k + 1, k);
-        const double a0 = cabsv(x0);
-        if (xn == 0.0 || xn2 - a0 * a0 <= 1e-300) continue;
+        const double a2 = cabs2(x0), a0 = sqrt(a2), xn = sqrt(a2 + tail2);
         const double2 ph = a0 > 0.0 ? cscale(x0, 1.0 / a0) : make_double2(1.0, 0.0);
         // v = x + ph |x| e1, H <- (I - 2 v v^H / v^H v) H (I - ...)
         const double2 v0 = cadd(x0, cscale(ph, xn));
-        double vn2 = cabs2(v0);
-        for (int i = k + 2; i < n; ++i) vn2 += cabs2(AT(i, k));
-        const double beta = 2.0 / vn2;
-        auto v = [&](int i) { return i == k + 1 ? v0 : AT(i, k); };
-        // left: rows k+1..n-1, columns k+1..n-1 (column k handled below)
-        for (int j = k + 1; j < n; ++j) {
+        const double beta = 2.0 / (cabs2(v0) + tail2);
+        va[t] = t == k + 1 ? v0 : x;
+        __syncthreads();
+        if (t > k && t < n) {  // left: column t, rows k+1..n-1
             double2 s = make_double2(0.0, 0.0);
-            for (int i = k + 1; i < n; ++i) s = cadd(s, cmul(cconj(v(i)), AT(i, j)));
+            for (int i = k + 1; i < n; ++i) s = cadd(s, cmul(cconj(va[i]), AT(i, t)));
             s = cscale(s, beta);
-            for (int i = k + 1; i < n; ++i) AT(i, j) = csub(AT(i, j), cmul(v(i), s));
+            for (int i = k + 1; i < n; ++i) AT(i, t) = csub(AT(i, t), cmul(va[i], s));
         }
-        // right: all rows, columns k+1..n-1
-        for (int i = 0; i < n; ++i) {
+        __syncthreads();
+        if (t < n) {           // right: row t, columns k+1..n-1
             double2 s = make_double2(0.0, 0.0);
-            for (int j = k + 1; j < n; ++j) s = cadd(s, cmul(AT(i, j), v(j)));
+            for (int j = k + 1; j < n; ++j) s = cadd(s, cmul(AT(t, j), va[j]));
             s = cscale(s, beta);
-            for (int j = k + 1; j < n; ++j) AT(i, j) = csub(AT(i, j), cmul(s, cconj(v(j))));
+            for (int j = k + 1; j < n; ++j) AT(t, j) = csub(AT(t, j), cmul(s, cconj(va[j])));
+            if (t > k) AT(t, k) = t == k + 1 ? cscale(ph, -xn) : make_double2(0.0, 0.0);
         }
-        // column k: x -> -ph |x| e1 (v's entries are stored there until now)
-        AT(k + 1, k) = cscale(ph, -xn);
-        for (int i = k + 2; i < n; ++i) AT(i, k) = make_double2(0.0, 0.0);
+        __syncthreads();
     }
     int hi = n - 1, iter = 0, bad = 0;
     const double ulp = 2.220446049250313e-16;
-    while (hi >= 0) {
+    while (hi >= 0) {  // hi, iter and l are the same in every thread
         if (hi == 0) {
-            L[0] = AT(0, 0);
+            if (t == 0) ls[0] = AT(0, 0);
             break;
         }
-        int l = hi;
-        while (l > 0) {
-            const double s = cabsv(AT(l, l)) + cabsv(AT(l - 1, l - 1));
-            if (cabsv(AT(l, l - 1)) <= ulp * (s > 0.0 ? s : 1.0)) {
-                AT(l, l - 1) = make_double2(0.0, 0.0);
-                break;
-            }
-            --l;
+        // the window l..hi: the lowest row reached from hi without a negligible subdiagonal
+        bool small = false;
+        if (t >= 1 && t <= hi) {
+            const double s = cabsv(AT(t, t)) + cabsv(AT(t - 1, t - 1));
+            small = cabsv(AT(t, t - 1)) <= ulp * (s > 0.0 ? s : 1.0);
+            if (small) AT(t, t - 1) = make_double2(0.0, 0.0);  // read by this thread alone
+        }
+        const unsigned long long bal = __ballot(small);
+        int l = bal ? (t & ~63) + 63 - __clzll((long long)bal) : 0;
+        if constexpr (NW > 1) {
+            if ((t & 63) == 0) redi[t >> 6] = l;
+            __syncthreads();
+            l = redi[0];
+            for (int i = 1; i < NW; ++i) l = max(l, redi[i]);
         }
         if (l == hi) {
-            L[hi] = AT(hi, hi);
+            if (t == 0) ls[hi] = AT(hi, hi);
             --hi;
             iter = 0;
+            __syncthreads();  // the next scan rewrites redi
             continue;
         }
         if (++iter > 30 * n) {
             bad = 1;
-            for (int i = 0; i <= hi; ++i) L[i] = AT(i, i);
+            if (t <= hi) ls[t] = AT(t, t);
             break;
         }
         // Wilkinson shift: eigenvalue of the trailing 2x2 closer to h[hi][hi]
@@ -250,62 +302,69 @@ __global__ void k_eig(double2 *mats, int n, int batch, double2 *lam, double *eps
             const double2 m1 = cadd(tr2, disc), m2 = csub(tr2, disc);
             mu = cabs2(csub(m1, d)) < cabs2(csub(m2, d)) ? m1 : m2;
         }
-        // one QR step on the window l..hi: H - mu I = Q R, H <- R Q + mu I, by
-        // Givens rotations G_k on rows (k, k+1), applied to columns as they go
-        for (int i = l; i <= hi; ++i) AT(i, i) = csub(AT(i, i), mu);
+        __syncthreads();
+        // one QR step on the window: H - mu I = Q R, H <- R Q + mu I.  Rotation k
+        // takes (x, y) = (h[k][k], h[k+1][k]) to (r, 0): rows k, k+1 become
+        // (conj(x) row_k + conj(y) row_k+1) / r and (x row_k+1 - y row_k) / r.
+        const bool col = t >= l && t <= hi;
+        double2 cur = col ? AT(l, t) : make_double2(0.0, 0.0);
+        if (t == l) cur = csub(cur, mu);
+        double2 nxt = col ? AT(l + 1, t) : make_double2(0.0, 0.0);
         for (int k = l; k < hi; ++k) {
-            const double2 x = AT(k, k), y = AT(k + 1, k);
-            const double r = sqrt(cabs2(x) + cabs2(y));
-            double c;
-            double2 s;
-            if (r == 0.0) {
-                c = 1.0;
-                s = make_double2(0.0, 0.0);
+            double2 row = nxt;
+            if (t == k + 1) row = csub(row, mu);
+            if (k + 2 <= hi && col) nxt = AT(k + 2, t);  // one row ahead
+            double2 x, y;
+            if constexpr (NW == 1) {
+                x = lane_read(cur, k);
+                y = lane_read(row, k);
             } else {
-                const double ax = cabsv(x);
-                if (ax == 0.0) {
-                    c = 0.0;
-                    s = cdiv(cconj(y), make_double2(cabsv(y), 0.0));  // phase of conj(y)
-                } else {
-                    c = ax / r;
-                    const double2 ph = cscale(x, 1.0 / ax);          // x / |x|
-                    s = cscale(cmul(ph, cconj(y)), 1.0 / r);          // (x/|x|) conj(y) / r
-                }
+                if (t == k) { hand[k & 1][0] = cur; hand[k & 1][1] = row; }
+                __syncthreads();
+                x = hand[k & 1][0];
+                y = hand[k & 1][1];
             }
-            // rows k, k+1 of columns k..hi: [c, s; -conj(s), c]
-            for (int j = k; j <= hi; ++j) {
-                const double2 hk = AT(k, j), hk1 = AT(k + 1, j);
-                AT(k, j) = cadd(cscale(hk, c), cmul(s, hk1));
-                AT(k + 1, j) = csub(cscale(hk1, c), cmul(cconj(s), hk));
+            const double r2 = cabs2(x) + cabs2(y);
+            if (r2 > 0.0) {
+                const double inv = 1.0 / sqrt(r2);
+                x = cscale(x, inv);
+                y = cscale(y, inv);
+            } else {
+                x = make_double2(1.0, 0.0);
+                y = make_double2(0.0, 0.0);
             }
-            // keep the rotation for the right multiplication: store c, s in the
-            // now-zero subdiagonal slot (real c) and in the lambda buffer (s)
-            AT(k + 1, k) = make_double2(c, 0.0);
-            L[k] = s;
+            if (t == 0) { va[k] = x; vb[k] = y; }
+            if (t >= k && t <= hi) AT(k, t) = cadd(cmul(cconj(x), cur), cmul(cconj(y), row));
+            cur = csub(cmul(x, row), cmul(y, cur));
         }
-        // H <- R G_l^H ... G_{hi-1}^H: columns k, k+1 of rows l..k+1 (R is upper
-        // triangular there; row k+2 still holds the stored cosine of G_{k+1})
-        for (int k = l; k < hi; ++k) {
-            const double c = AT(k + 1, k).x;
-            const double2 s = L[k];
-            AT(k + 1, k) = make_double2(0.0, 0.0);
-            for (int i = l; i <= k + 1; ++i) {
-                const double2 hk = AT(i, k), hk1 = AT(i, k + 1);
-                AT(i, k) = cadd(cscale(hk, c), cmul(hk1, cconj(s)));
-                AT(i, k + 1) = csub(cscale(hk1, c), cmul(hk, s));
+        if (t == hi) AT(hi, hi) = cur;
+        __syncthreads();
+        // columns k, k+1 of rows l..k+1, by rows: row t starts at column t - 1 (its
+        // subdiagonal entry was annihilated) or at the window's first column
+        if (col) {
+            const int k0 = t > l ? t - 1 : l;
+            double2 a = t > l ? make_double2(0.0, 0.0) : AT(l, l);
+            for (int k = k0; k < hi; ++k) {
+                const double2 b = AT(t, k + 1), x = va[k], y = vb[k];
+                double2 o = cadd(cmul(a, x), cmul(b, y));
+                if (t == k) o = cadd(o, mu);
+                AT(t, k) = o;
+                a = csub(cmul(b, cconj(x)), cmul(a, cconj(y)));
             }
+            if (t == hi) a = cadd(a, mu);
+            AT(t, hi) = a;
         }
-        for (int i = l; i <= hi; ++i) AT(i, i) = cadd(AT(i, i), mu);
+        __syncthreads();
     }
+    __syncthreads();
 #undef AT
-    double mx = 0.0, sm = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double a = cabsv(L[i]);
-        mx = fmax(mx, a);
-        sm += a;
+    const double a = t < n ? cabsv(ls[t]) : 0.0;
+    const double mx = reduce(a, true), sm = reduce(a, false);
+    if (t < n) lam[(int64_t)q * n + t] = make_double2(ldexp(ls[t].x, ex), ldexp(ls[t].y, ex));
+    if (t == 0) {
+        eps[q] = sm > 0.0 ? 1.0 - mx / sm : 0.0;
+        info[q] = bad;
     }
-    eps[q] = sm > 0.0 ? 1.0 - mx / sm : 0.0;
-    info[q] = bad;
 }
 
 }  // namespace
@@ -338,8 +397,23 @@ hipError_t launch_gather_mats(const void *pairs, const int64_t *off, const int *
 
 hipError_t launch_eig(void *mats, int n, int batch, void *lam, double *eps, int *info, hipStream_t s) {
     if (batch <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_eig, dim3((batch + 63) / 64), dim3(64), 0, s, static_cast<double2 *>(mats), n, batch,
-                       static_cast<double2 *>(lam), eps, info);
+    if (n < 1 || n > BP_EIG_NMAX) return hipErrorInvalidValue;
+    double2 *m = static_cast<double2 *>(mats), *l = static_cast<double2 *>(lam);
+    const size_t lds = (size_t)n * (n + 1) * sizeof(double2);
+    constexpr int most = EIG_LDS_N * (EIG_LDS_N + 1) * (int)sizeof(double2);
+    if (n <= 64) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eig<64, true>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_eig<64, true>), dim3(batch), dim3(64), lds, s, m, n, l, eps, info);
+    } else if (n <= EIG_LDS_N) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eig<256, true>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_eig<256, true>), dim3(batch), dim3(256), lds, s, m, n, l, eps, info);
+    } else {
+        hipLaunchKernelGGL((k_eig<256, false>), dim3(batch), dim3(256), 0, s, m, n, l, eps, info);
+    }
     return hipGetLastError();
 }
 

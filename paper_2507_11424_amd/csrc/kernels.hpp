@@ -284,7 +284,7 @@ hipError_t launch_bp_free_energy(const void *outr, const void *msg, const int *n
 hipError_t launch_gather_mats(const void *pairs, const int64_t *off, const int *trans, int count, int n, void *mats,
                               hipStream_t s);
 // Eigenvalues of `batch` general complex n x n matrices (overwritten), one
-// lane each: Householder Hessenberg reduction and shifted QR with deflation.
+// workgroup each: Householder Hessenberg reduction and shifted QR with deflation.
 // lam [batch][n] complex128; eps[q] = 1 - max|lambda| / sum|lambda|; info[q] = 1
 // if the iteration limit was reached.
 constexpr int BP_EIG_NMAX = 256;
