@@ -11,15 +11,18 @@
 // padded to the largest bond Dm:
 // msg[z][leg][k][k'] (into site z through leg, ket index k, bra index k'),
 // e0 e0^T on legs without a bond, so padded entries never contribute.  A
-// parallel sweep computes, for each of the four legs, the message every site
-// sends through it -- the pair (A, conj A) closed with the site's other three
-// incoming messages, three batched contractions over all sites and one with
-// conj(A) -- then k_bp_update takes each one's Hermitian part, normalises it to
-// unit Frobenius norm and stores it as the neighbour's incoming message.
+// parallel sweep computes, for each bond leg, the message every site sends
+// through it -- the pair (A, conj A) closed with the site's other incoming
+// messages -- then k_bp_update takes each one's Hermitian part, normalises it to
+// unit Frobenius norm and stores it as the neighbour's incoming message.  The
+// products are small and many (a shape class has up to 12 per sweep), so a sweep
+// is bound by launches and their latency: the independent ones of all classes
+// run together, four grouped launches per sweep.
 // FP64 throughout.
 #include <algorithm>
 #include <cmath>
 #include <map>
+#include <memory>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -67,86 +70,107 @@ Op class_op(const SiteClass &c, const std::string &idx, bool conj) {
     return o;
 }
 
+// Contractions that run together: group d holds those that need the results of
+// the groups before it, and every intermediate keeps a buffer of its own until
+// the end; a network of message products over all site classes is a handful of
+// groups, launched once per sweep.  Without `grouped` each contraction runs when
+// it is added and an intermediate goes when nothing refers to it any more: for
+// states whose intermediates would not all fit.
+struct Stages {
+    Engine &E;
+    const bool grouped;
+    std::vector<Engine::Group> g;
+    std::vector<std::shared_ptr<Ten>> bufs;
+    Stages(Engine &e, bool grouped_) : E(e), grouped(grouped_) {}
+    Stages(const Stages &) = delete;
+    ~Stages() {
+        for (auto &x : g) E.group_free(x);
+    }
+    void add(int d, const Op &A, const Op &B, const Op &C) {
+        if (!grouped) return E.contract(A, B, C);
+        if ((int)g.size() <= d) g.resize((size_t)d + 1);
+        E.group_add(g[(size_t)d], A, B, C);
+    }
+    std::shared_ptr<Ten> buffer(const std::vector<int> &dims) {
+        Engine *e = &E;
+        std::shared_ptr<Ten> t(new Ten(E.make(dims)), [e](Ten *x) {
+            e->drop(*x);
+            delete x;
+        });
+        if (grouped) bufs.push_back(t);
+        return t;
+    }
+    void run() {
+        for (auto &x : g) E.group_run(x);
+    }
+};
+
+// A class's site tensors with some messages contracted: t holds the letters
+// `idx` (null: the site tensors themselves) and is ready after `depth` groups.
+struct Partial {
+    std::shared_ptr<Ten> t;
+    std::string idx = "zsabcd";
+    int depth = 0;
+    Op op_of(const SiteClass &c) const { return t ? op(*t, idx) : class_op(c, idx, false); }
+};
+
+// Contracts the incoming messages of `legs` into x: each replaces a ket letter
+// by its bra letter.  The message 1 of a leg without a bond is multiplied in
+// like any other: the 3M product with 1 rounds, and the phases of the simple
+// update's singular vectors follow the last bit of the messages.
+Partial with_messages(Stages &S, const SiteClass &c, const Ten &msg, Partial x, const std::vector<int> &legs,
+                      int Dm) {
+    for (int leg : legs) {
+        Partial y;
+        y.idx.clear();
+        for (char ch : x.idx)
+            if (ch != KET[leg]) y.idx += ch;
+        y.idx += BRA[leg];
+        std::vector<int> dims;
+        const Op src = x.op_of(c);
+        for (char ch : y.idx)
+            dims.push_back(ch == BRA[leg] ? c.dims[leg + 1] : src.dims[src.idx.find(ch)]);
+        y.t = S.buffer(dims);
+        y.depth = x.depth + 1;
+        S.add(x.depth, src, msg_op(msg, c, leg, Dm), op(*y.t, y.idx));
+        x = y;
+    }
+    return x;
+}
+
+// Closes x with conj(A) over s and the bra letters it holds, into `out`.
+void close_pair(Stages &S, const SiteClass &c, const Partial &x, const Op &out) {
+    S.add(x.depth, x.op_of(c), class_op(c, "zsefgh", true), out);
+}
+
 // The pair (A, conj A) of every site of the class with the incoming messages
 // on all legs not in `keep` contracted; result [z] + (ket, bra) letters of the
 // kept legs in order, written through `out` (the caller's view of the class's
 // blocks; every dimension is the site's own, nothing is padded).
-void pair_closed(Engine &E, const SiteClass &c, const Ten &msg, const std::vector<int> &keep, const Op &out,
+void pair_closed(Stages &S, const SiteClass &c, const Ten &msg, const std::vector<int> &keep, const Op &out,
                  int Dm) {
-    std::string cur = "zsabcd";
-    Ten t;  // current intermediate (empty: A itself)
-    for (int leg = 0; leg < NLEG; ++leg) {
-        if (std::find(keep.begin(), keep.end(), leg) != keep.end()) continue;
-        std::string nxt;
-        for (char ch : cur)
-            if (ch != KET[leg]) nxt += ch;
-        nxt += BRA[leg];
-        Ten r = E.contract_new(t.p ? op(t, cur) : class_op(c, cur, false), msg_op(msg, c, leg, Dm), nxt);
-        if (t.p) E.drop(t);
-        t = r;
-        cur = nxt;
-    }
-    // close with conj(A) over s and the bra legs of the contracted legs
-    E.contract(op(t, cur), class_op(c, "zsefgh", true), out);
-    E.drop(t);
+    std::vector<int> legs;
+    for (int leg = 0; leg < NLEG; ++leg)
+        if (std::find(keep.begin(), keep.end(), leg) == keep.end()) legs.push_back(leg);
+    close_pair(S, c, with_messages(S, c, msg, Partial{}, legs, Dm), out);
 }
 
-// Contracts the incoming messages of `legs` into the intermediate `t`
-// (letters `cur`; t empty = the class's site tensors A themselves): each
-// message replaces a ket letter by its bra letter.
-Ten with_messages(Engine &E, const SiteClass &c, const Ten &msg, const Ten &t, std::string &cur,
-                  const std::vector<int> &legs, int Dm) {
-    Ten r = t;
-    bool own = false;
-    try {
-        for (int leg : legs) {
-            std::string nxt;
-            for (char ch : cur)
-                if (ch != KET[leg]) nxt += ch;
-            nxt += BRA[leg];
-            Ten x = E.contract_new(r.p ? op(r, cur) : class_op(c, cur, false), msg_op(msg, c, leg, Dm), nxt);
-            if (own) E.drop(r);
-            r = x;
-            own = true;
-            cur = nxt;
-        }
-    } catch (...) {
-        if (own) E.drop(r);
-        throw;
-    }
-    return r;
-}
-
-// The four outgoing messages of every site of the class into out_op(leg):
-// the same values as pair_closed with keep = {leg} for each leg, from shared
-// partial products (A with the messages of legs 2 and 3 serves the outputs
-// of legs 0 and 1, A with those of legs 0 and 1 the outputs of legs 2 and 3):
-// 12 contractions instead of 16.
+// The outgoing messages of every site of the class through its bonds into
+// out_op(leg), from shared partial products: A with the messages of legs 2 and
+// 3 serves the outputs of legs 0 and 1, A with those of legs 0 and 1 the outputs
+// of legs 2 and 3.
 template <typename OutOp>
-void all_outgoing(Engine &E, const SiteClass &c, const Ten &msg, int Dm, OutOp out_op) {
+void all_outgoing(Stages &S, const SiteClass &c, const Ten &msg, int Dm, OutOp out_op) {
     const int pairs[2][2] = {{2, 3}, {0, 1}};  // legs contracted first; the outputs are the other two
     for (const auto &pr : pairs) {
-        std::string base = "zsabcd";
-        Ten X = with_messages(E, c, msg, Ten{}, base, {pr[0], pr[1]}, Dm);
         const int o0 = pr[0] == 2 ? 0 : 2;
-        try {
-            for (int q = 0; q < 2; ++q) {
-                const int keep = o0 + q, other = o0 + 1 - q;
-                std::string cur = base;
-                Ten Y = with_messages(E, c, msg, X, cur, {other}, Dm);
-                try {
-                    E.contract(op(Y, cur), class_op(c, "zsefgh", true), out_op(keep, c));
-                } catch (...) {
-                    E.drop(Y);
-                    throw;
-                }
-                E.drop(Y);
-            }
-        } catch (...) {
-            E.drop(X);
-            throw;
+        if (c.dims[o0 + 1] == 1 && c.dims[o0 + 2] == 1) continue;
+        const Partial X = with_messages(S, c, msg, Partial{}, {pr[0], pr[1]}, Dm);
+        for (int q = 0; q < 2; ++q) {
+            const int keep = o0 + q, other = o0 + 1 - q;
+            if (c.dims[keep + 1] == 1) continue;
+            close_pair(S, c, with_messages(S, c, msg, X, {other}, Dm), out_op(keep, c));
         }
-        E.drop(X);
     }
 }
 
@@ -262,15 +286,25 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
     }
     const int N = (int)act.size();
     if (N == 0) throw TnError(ST_INVALID, "belief propagation: the state has no site with a bond or a qubit");
+    std::vector<tnk::CopyBlock> tab;  // gathers the classes' site tensors (and the initial messages)
+    double class_bytes = 0;
     for (auto &c : cls) {
         c.A = E.make({c.count, c.dims[0], c.dims[1], c.dims[2], c.dims[3], c.dims[4]});
-        const size_t bytes = (size_t)c.dims[0] * c.dims[1] * c.dims[2] * c.dims[3] * c.dims[4] * 16;
+        const int64_t per = c.A.numel() / c.count;
+        class_bytes += (double)c.A.bytes();
         for (int i = 0; i < c.count; ++i) {
             const Ten &t = P.site[(size_t)act[(size_t)c.start + i]];
             if (t.esz != 16) throw TnError(ST_INVALID, "belief propagation runs on complex128 site tensors");
-            TN_HIP(hipMemcpyAsync(static_cast<char *>(c.A.p) + (size_t)i * bytes, t.p, bytes,
-                                  hipMemcpyDeviceToDevice, E.s));
+            tab.push_back({t.p, static_cast<char *>(c.A.p) + (size_t)i * per * 16, 1, per, 0});
         }
+    }
+    // a sweep's intermediates: at most eight of the state's size, held together
+    // unless they would take more than a quarter of the memory (asked from 1 GiB on)
+    bool grouped = true;
+    if (8 * class_bytes > (double)((size_t)1 << 30)) {
+        size_t freeb = 0, total = 0;
+        TN_HIP(hipMemGetInfo(&freeb, &total));
+        grouped = 8 * class_bytes <= 0.25 * ((double)freeb + (double)E.held());
     }
     // neighbour table and initial messages: identity / sqrt(D) on bonds, e0 e0^T elsewhere
     std::vector<int> hn((size_t)N * NLEG, -1);
@@ -297,7 +331,15 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
     Ten out = E.make({NLEG, N, Dm, Dm});
     double *dmax = static_cast<double *>(E.raw((size_t)N * NLEG * 8));
     double *dscal = static_cast<double *>(E.raw(64));
-    const size_t site_msgs = (size_t)NLEG * n2 * 16;  // bytes of one site's four messages
+    const int64_t site_msgs = (int64_t)NLEG * n2;  // elements of one site's four messages
+    void *dtab = nullptr;
+    auto copy_table = [&]() {  // the caller synchronises before `tab` changes
+        int64_t mx = 0;
+        for (const auto &b : tab) mx = std::max<int64_t>(mx, b.rows * b.cols);
+        if (!dtab) dtab = E.raw(2 * (size_t)std::max(N, 1) * sizeof(tnk::CopyBlock));
+        TN_HIP(hipMemcpyAsync(dtab, tab.data(), tab.size() * sizeof(tnk::CopyBlock), hipMemcpyHostToDevice, E.s));
+        TN_HIP(tnk::launch_copy_blocks(static_cast<const tnk::CopyBlock *>(dtab), (int)tab.size(), mx, E.s));
+    };
     auto cleanup = [&]() {
         for (auto &c : cls)
             if (c.A.p) E.drop(c.A);
@@ -306,16 +348,17 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
         E.unraw(nbr);
         E.unraw(dmax);
         E.unraw(dscal);
+        if (dtab) E.unraw(dtab);
     };
     try {
         if (o.init_messages) {  // grid layout [NG][4][Dm][Dm]: the active sites' blocks
             for (int i = 0; i < N; ++i)
-                TN_HIP(hipMemcpyAsync(static_cast<char *>(msg.p) + (size_t)i * site_msgs,
-                                      static_cast<const char *>(o.init_messages) + (size_t)act[i] * site_msgs,
-                                      site_msgs, hipMemcpyDeviceToDevice, E.s));
+                tab.push_back({static_cast<const char *>(o.init_messages) + (size_t)act[i] * site_msgs * 16,
+                               static_cast<char *>(msg.p) + (size_t)i * site_msgs * 16, 1, site_msgs, 0});
         } else {
             TN_HIP(hipMemcpyAsync(msg.p, hm.data(), hm.size() * 8, hipMemcpyHostToDevice, E.s));
         }
+        copy_table();
         TN_HIP(hipMemcpyAsync(nbr, hn.data(), hn.size() * sizeof(int), hipMemcpyHostToDevice, E.s));
         // the sweeps write each site's own D x D block of its outgoing messages
         TN_HIP(tnk::launch_fill(out.p, out.esz, out.numel(), 0.0, 0.0, E.s));
@@ -331,11 +374,15 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
         };
         double delta = INFINITY;
         int sweep = 0;
+        Stages round(E, grouped);
         while (sweep < o.max_sweeps) {
-            for (const auto &c : cls) all_outgoing(E, c, msg, Dm, out_op);
-            TN_HIP(tnk::launch_bp_update(out.p, msg.p, nbr, N, Dm, dmax, dscal, E.s));
+            if (sweep == 0 || !grouped)
+                for (const auto &c : cls) all_outgoing(round, c, msg, Dm, out_op);
+            round.run();
             ++sweep;
-            if (sweep % 4 == 0 || sweep == o.max_sweeps) {
+            const bool check = sweep % 4 == 0 || sweep == o.max_sweeps;
+            TN_HIP(tnk::launch_bp_update(out.p, msg.p, nbr, N, Dm, dmax, check ? dscal : nullptr, E.s));
+            if (check) {
                 TN_HIP(hipMemcpyAsync(&delta, dscal, 8, hipMemcpyDeviceToHost, E.s));
                 E.sync();
                 if (!(delta < INFINITY)) throw TnError(ST_NUMERIC, "BP message vanished or overflowed");
@@ -345,27 +392,32 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
         res.sweeps = sweep;
         res.delta = delta;
         // Z_BP from the final messages
-        for (const auto &c : cls) pair_closed(E, c, msg, {3}, out_op(3, c), Dm);
-        double *zv = static_cast<double *>(E.raw((size_t)N * 16));
-        double *ze = static_cast<double *>(E.raw((size_t)N * 32));
-        TN_HIP(tnk::launch_bp_free_energy(static_cast<char *>(out.p) + (size_t)3 * N * n2 * 16, msg.p, nbr, N, Dm,
-                                          zv, ze, dscal, E.s));
-        double h2[2];
-        TN_HIP(hipMemcpyAsync(h2, dscal, 16, hipMemcpyDeviceToHost, E.s));
-        E.sync();
-        E.unraw(zv);
-        E.unraw(ze);
-        res.log_abs = h2[0];
-        res.arg = h2[1];
+        if (o.free_energy) {
+            Stages fin(E, grouped);
+            for (const auto &c : cls) pair_closed(fin, c, msg, {3}, out_op(3, c), Dm);
+            fin.run();
+            double *zv = static_cast<double *>(E.raw((size_t)N * 16));
+            double *ze = static_cast<double *>(E.raw((size_t)N * 32));
+            TN_HIP(tnk::launch_bp_free_energy(static_cast<char *>(out.p) + (size_t)3 * N * n2 * 16, msg.p, nbr, N, Dm,
+                                              zv, ze, dscal, E.s));
+            double h2[2];
+            TN_HIP(hipMemcpyAsync(h2, dscal, 16, hipMemcpyDeviceToHost, E.s));
+            E.sync();
+            E.unraw(zv);
+            E.unraw(ze);
+            res.log_abs = h2[0];
+            res.arg = h2[1];
+        }
         if (o.messages) {
             // grid layout [NG][4][Dm][Dm]: dummies hold e0 e0^T on every leg
             std::vector<double> dm((size_t)NG * NLEG * n2 * 2, 0.0);
             for (size_t q = 0; q < (size_t)NG * NLEG; ++q) dm[q * n2 * 2] = 1.0;
             TN_HIP(hipMemcpyAsync(o.messages, dm.data(), dm.size() * 8, hipMemcpyHostToDevice, E.s));
+            tab.clear();
             for (int i = 0; i < N; ++i)
-                TN_HIP(hipMemcpyAsync(static_cast<char *>(o.messages) + (size_t)act[i] * site_msgs,
-                                      static_cast<const char *>(msg.p) + (size_t)i * site_msgs, site_msgs,
-                                      hipMemcpyDeviceToDevice, E.s));
+                tab.push_back({static_cast<const char *>(msg.p) + (size_t)i * site_msgs * 16,
+                               static_cast<char *>(o.messages) + (size_t)act[i] * site_msgs * 16, 1, site_msgs, 0});
+            copy_table();
             E.sync();  // dm is released on return
         }
         // loop BP error
@@ -394,6 +446,7 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
                 Ten pt = E.make({(int)pairs.size(), N, Dm, Dm, Dm, Dm});
                 TN_HIP(tnk::launch_fill(pt.p, pt.esz, pt.numel(), 0.0, 0.0, E.s));
                 const size_t pstride = (size_t)N * n2 * n2;
+                Stages prs(E, grouped);
                 for (size_t k = 0; k < pairs.size(); ++k)
                     for (const auto &c : cls) {
                         const int a = pairs[k].first, b = pairs[k].second;
@@ -403,8 +456,9 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
                         q.idx = std::string("z") + KET[a] + BRA[a] + KET[b] + BRA[b];
                         q.dims = {c.count, c.dims[a + 1], c.dims[a + 1], c.dims[b + 1], c.dims[b + 1]};
                         q.str = {(int64_t)n2 * n2, (int64_t)Dm * n2, n2, Dm, 1};
-                        pair_closed(E, c, msg, {a, b}, q, Dm);
+                        pair_closed(prs, c, msg, {a, b}, q, Dm);
                     }
+                prs.run();
                 // loops grouped by length: gather [loop][k] matrices, multiply along the walk
                 std::map<int, std::vector<int>> bylen;
                 for (int i = 0; i < (int)loops.size(); ++i) bylen[(int)loops[i].size()].push_back(i);

@@ -130,11 +130,11 @@ __global__ void __launch_bounds__(NT) k_bp_values(const double2 *outr, const dou
 }
 
 // out[0] = sum log|zv| - sum log|ze|, out[1] = the same sum of phases, in a
-// fixed order (one thread).
-__global__ void k_bp_logsum(const double2 *zv, const double2 *ze, int N, double *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// fixed order (one wave: a lane per site, then a tree over the lanes; one lane
+// alone took 235 us for 144 sites).
+__global__ void __launch_bounds__(64) k_bp_logsum(const double2 *zv, const double2 *ze, int N, double *out) {
     double lz = 0.0, ph = 0.0;
-    for (int z = 0; z < N; ++z) {
+    for (int z = threadIdx.x; z < N; z += 64) {
         lz += log(cabsv(zv[z]));
         ph += atan2(zv[z].y, zv[z].x);
         for (int k = 0; k < 2; ++k) {
@@ -143,8 +143,14 @@ __global__ void k_bp_logsum(const double2 *zv, const double2 *ze, int N, double 
             ph -= atan2(e.y, e.x);
         }
     }
-    out[0] = lz;
-    out[1] = remainder(ph, 2.0 * M_PI);
+    for (int o = 32; o > 0; o >>= 1) {
+        lz += __shfl_xor(lz, o);
+        ph += __shfl_xor(ph, o);
+    }
+    if (threadIdx.x == 0) {
+        out[0] = lz;
+        out[1] = remainder(ph, 2.0 * M_PI);
+    }
 }
 
 // mats[q] (n x n, n = Dm^2) <- the pair tensor tab[q] = (buffer offset, flag):
@@ -373,7 +379,7 @@ hipError_t launch_bp_update(const void *out, void *msg, const int *nbr, int N, i
                             hipStream_t s) {
     hipLaunchKernelGGL(k_bp_update, dim3(N * 4), dim3(NT), 0, s, static_cast<const double2 *>(out),
                        static_cast<double2 *>(msg), nbr, N, Dm, dmax);
-    hipLaunchKernelGGL(k_max, dim3(1), dim3(NT), 0, s, dmax, N * 4, delta);
+    if (delta) hipLaunchKernelGGL(k_max, dim3(1), dim3(NT), 0, s, dmax, N * 4, delta);
     return hipGetLastError();
 }
 

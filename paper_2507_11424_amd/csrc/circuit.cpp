@@ -214,6 +214,7 @@ void simple_update(Engine &E, PepsDev &P, const std::vector<SuGate> &gates, cons
             bo.max_sweeps = o.bp_max_sweeps;
             bo.tol = o.bp_tol;
             bo.loops = false;
+            bo.free_energy = false;
             bo.messages = msg.p;
             bo.init_messages = first ? nullptr : msg.p;  // warm start from the previous group's messages
             BpResult br;

@@ -847,13 +847,7 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         return;
     }
     Plan *P = plan(A, B, C);
-    tnk::GettArgs g = P->base;
-    g.A = P->swapped ? B.p : A.p;
-    g.B = P->swapped ? A.p : B.p;
-    g.C = const_cast<void *>(C.p);
-    g.conjA = (P->swapped ? B.conj : A.conj) ? 1 : 0;
-    g.conjB = (P->swapped ? A.conj : B.conj) ? 1 : 0;
-    g.accumulate = accumulate ? 1 : 0;
+    tnk::GettArgs g = args_of(*P, A, B, C, accumulate);
     int cfg = P->cfg;
     if (force_cfg == tnk::CFG_128x128W && !P->pack)
         throw TnError(ST_UNSUPPORTED, "the 128x128 tile serves packed split-BF16 operands only");
@@ -919,6 +913,94 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
     ctr.gemm_launches += 1;
     ctr.gemm_bytes += (double)P->Z * ((double)P->kM * P->K + (double)P->K * P->kN +
                                       (double)P->kM * P->kN * (accumulate ? 2.0 : 1.0)) * esz;
+}
+
+tnk::GettArgs Engine::args_of(const Plan &P, const Op &A, const Op &B, const Op &C, bool accumulate) {
+    tnk::GettArgs g = P.base;
+    g.A = P.swapped ? B.p : A.p;
+    g.B = P.swapped ? A.p : B.p;
+    g.C = const_cast<void *>(C.p);
+    g.conjA = (P.swapped ? B.conj : A.conj) ? 1 : 0;
+    g.conjB = (P.swapped ? A.conj : B.conj) ? 1 : 0;
+    g.accumulate = accumulate ? 1 : 0;
+    return g;
+}
+
+// A grouped contraction keeps the K slices that the planner gives the same
+// contraction on its own, so it is the same sum in the same order; the tile is
+// the narrow one for at most 16 columns (the planner's line).
+void Engine::group_add(Group &gr, const Op &A, const Op &B, const Op &C) {
+    if (prec != tnk::P_FP64 || A.esz != 16 || B.esz != 16 || C.esz != 16)
+        throw TnError(ST_INVALID, "grouped contractions are FP64");
+    Plan *P = nullptr;
+    if (op_window(A, B, C) <= (int64_t)tnk::GETT_MAX_WINDOW && op_window(B, A, C) <= (int64_t)tnk::GETT_MAX_WINDOW &&
+        op_window(C, A, B) / C.esz <= (int64_t)INT32_MAX)
+        P = plan(A, B, C);
+    if (!P || P->cfg == tnk::CFG_128x64) {  // cut into slices, or the 4M tile: run by itself
+        gr.direct.push_back({A, B, C});
+        return;
+    }
+    tnk::GettArgs g = args_of(*P, A, B, C, false);
+    const int c = P->K == 1 ? 2 : P->kN <= 16 ? 1 : 0;
+    const int bm = 64, bn = c == 1 ? 16 : 64;
+    if (g.ksplit > 1) {
+        g.part = pool_.get((size_t)g.ksplit * g.batch * (size_t)g.M * g.N * 16);
+        gr.mem.push_back(g.part);
+    }
+    const int id = (int)gr.args.size();
+    const int tiles = c == 2 ? (int)(((int64_t)g.M * g.N + 255) / 256) : ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+    for (int z = 0; z < g.ksplit; ++z)
+        for (int b = 0; b < g.batch; ++b)
+            for (int t = 0; t < tiles; ++t) gr.blk[c].push_back({id, t, b, z});
+    if (g.ksplit > 1)
+        for (int64_t e = 0; e < (int64_t)g.M * g.N * g.batch; e += 256) gr.red.push_back({id, (int)(e / 256), 0, 0});
+    if (c < 2) gr.ktab[c] = std::max(gr.ktab[c], (g.a_kaff ? 0 : g.kchunk) + (g.b_kaff ? 0 : g.kchunk));
+    gr.flops += P->flops;
+    gr.bytes += 16.0 * P->Z * ((double)P->kM * P->K + (double)P->K * P->kN + (double)P->kM * P->kN);
+    gr.args.push_back(g);
+}
+
+void Engine::group_run(Group &gr) {
+    static const int cfg[3] = {tnk::CFG_64x64, tnk::CFG_64x16, tnk::CFG_K1};
+    if (!gr.tab && !gr.args.empty()) {
+        size_t off[5], end = 0;
+        auto place = [&](int i, const void *src, size_t bytes) {
+            off[i] = end;
+            end += (bytes + 15) & ~size_t(15);
+            gr.host.resize(end);
+            if (bytes) std::memcpy(gr.host.data() + off[i], src, bytes);
+        };
+        for (int i = 0; i < 4; ++i) {
+            const std::vector<tnk::GroupBlock> &b = i < 3 ? gr.blk[i] : gr.red;
+            place(i, b.data(), b.size() * sizeof(tnk::GroupBlock));
+        }
+        place(4, gr.args.data(), gr.args.size() * sizeof(tnk::GettArgs));
+        char *d = static_cast<char *>(pool_.get(end));
+        gr.mem.push_back(d);
+        // gr.host lives until group_free, which synchronises
+        TN_HIP(hipMemcpyAsync(d, gr.host.data(), end, hipMemcpyHostToDevice, s));
+        for (int i = 0; i < 4; ++i) gr.dblk[i] = reinterpret_cast<const tnk::GroupBlock *>(d + off[i]);
+        gr.tab = reinterpret_cast<const tnk::GettArgs *>(d + off[4]);
+    }
+    for (const auto &d : gr.direct) contract(d.A, d.B, d.C);
+    if (gr.args.empty()) return;
+    EvPair *ev = timing ? next_pair(0) : nullptr;
+    if (ev) TN_HIP(hipEventRecord(ev->a, s));
+    for (int i = 0; i < 3; ++i) {
+        if (gr.blk[i].empty()) continue;
+        TN_HIP(tnk::launch_gett_group(gr.tab, gr.dblk[i], (int)gr.blk[i].size(), cfg[i], gr.ktab[i], s));
+        ctr.gemm_launches += 1;
+    }
+    if (!gr.red.empty()) TN_HIP(tnk::launch_reduce_group(gr.tab, gr.dblk[3], (int)gr.red.size(), s));
+    if (ev) TN_HIP(hipEventRecord(ev->b, s));
+    ctr.gemm_flops += gr.flops;
+    ctr.gemm_bytes += gr.bytes;
+}
+
+void Engine::group_free(Group &gr) {
+    (void)hipStreamSynchronize(s);  // the uploads read the group's host tables
+    for (void *p : gr.mem) pool_.put(p);
+    gr = Group();
 }
 
 Ten Engine::contract_new(const Op &A, const Op &B, const std::string &ic) {

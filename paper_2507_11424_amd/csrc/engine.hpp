@@ -169,6 +169,26 @@ class Engine {
     // Allocates C with the letters of ic (dims taken from A and B).
     Ten contract_new(const Op &A, const Op &B, const std::string &ic);
 
+    // Independent FP64 contractions (C = A * B) run together: one kernel launch
+    // per tile configuration instead of one or two per contraction.  Add them
+    // all, then run the group any number of times (the operands' addresses are
+    // fixed when they are added), then free it.
+    struct Group {
+        std::vector<tnk::GettArgs> args;
+        std::vector<tnk::GroupBlock> blk[3], red;   // 64x64 tiles, 64x16 tiles, K = 1; split-K sums
+        int ktab[3] = {0, 0, 0};                    // k table entries a workgroup stages
+        struct Direct { Op A, B, C; };
+        std::vector<Direct> direct;                 // operands above the kernel's windows: run one by one
+        std::vector<void *> mem;                    // device tables, split-K partials
+        std::vector<char> host;                     // the tables as uploaded
+        const tnk::GettArgs *tab = nullptr;
+        const tnk::GroupBlock *dblk[4] = {nullptr, nullptr, nullptr, nullptr};
+        double flops = 0, bytes = 0;
+    };
+    void group_add(Group &g, const Op &A, const Op &B, const Op &C);
+    void group_run(Group &g);
+    void group_free(Group &g);
+
     // Reduced QR (FP64) of `batch` matrices; see tnk::QrArgs.
     void qr(const tnk::QrArgs &a);
     // Orthonormal Q for m >= n (else Householder): shifted CholeskyQR3 in
@@ -250,6 +270,7 @@ class Engine {
     std::map<std::string, TuneChoice> tune_cache_;  // key -> tile configuration, K slices, packing
     std::map<std::string, int64_t> qr_shapes_;               // factorisation calls by shape
     void set_split(Plan *P, int cfg, int ksplit_hint);
+    static tnk::GettArgs args_of(const Plan &P, const Op &A, const Op &B, const Op &C, bool accumulate);
     void pack_bf16(tnk::GettArgs &g, void **pa, void **pb);
     void tune(Plan *P, tnk::GettArgs g);
     EvPair *next_pair(int kind);

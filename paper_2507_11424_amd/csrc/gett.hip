@@ -121,9 +121,16 @@ __device__ inline void stage_ktab(int *dst, const int32_t *tab, int kbeg, int kl
 // rounding error of 4M relative to sum |a||b|.
 // Two LDS stages: the tile for step k+1 is loaded from HBM into registers while
 // step k computes, then stored to the other stage; one barrier per step.
+template <typename T, int BM, int BN, int BK> struct GettTiles {
+    T a[2][2][BK][BM + 2];  // [stage][re/im][k][m]
+    T b[2][2][BK][BN + 2];
+};
+
+// One BM x BN tile of problem p over its K slice kz, for the batch items b0,
+// b0 + bstep, ...
 template <typename T, int BM, int BN, int BK, int WGM, int WGN, bool G3>
-__global__ void __launch_bounds__(64 * WGM * WGN, 2)
-gett_mfma(GettArgs p) {
+__device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, int bstep, int kz,
+                                           GettTiles<T, BM, BN, BK> &sm, int *ktab) {
     using C2 = typename Tr<T>::C2;
     using Acc = typename Tr<T>::Acc;
     constexpr int NT = 64 * WGM * WGN;
@@ -131,23 +138,16 @@ gett_mfma(GettArgs p) {
     constexpr int FM = WTM / 16, FN = WTN / 16;
     constexpr int LA = (BM * BK) / NT;
     constexpr int LB = (BK * BN) / NT;
-    constexpr int PA = BM + 2, PB = BN + 2;
     constexpr int ESZ = (int)sizeof(C2);
     static_assert(LA >= 1 && LB >= 1 && NT % BK == 0 && NT >= BM && NT >= BN, "tile");
-    __shared__ T sA[2][2][BK][PA];  // [stage][re/im][k][m]
-    __shared__ T sB[2][2][BK][PB];
-    extern __shared__ int ktab[];   // non-affine k tables of the block's K slice
+    auto &sA = sm.a;
+    auto &sB = sm.b;
 
     const int tid = threadIdx.x;
     const int tiles_n = (p.N + BN - 1) / BN;
-    const int tiles_m = (p.M + BM - 1) / BM;
-    // a masked launch keeps the dispatch order, which deals consecutive tiles
-    // round-robin over the XCDs: with contiguous per-XCD ranges the tiles of
-    // one sample would sit on one or two XCDs and the others would idle
-    const int tile = p.mask ? (int)blockIdx.x : xcd_remap(blockIdx.x, tiles_m * tiles_n);
     const int m0 = (tile / tiles_n) * BM;
     const int n0 = (tile % tiles_n) * BN;
-    const int kbeg = blockIdx.z * p.kchunk;
+    const int kbeg = kz * p.kchunk;
     const int kend = min(p.K, kbeg + p.kchunk);
 
     int am[LA], bn[LB];
@@ -180,7 +180,7 @@ gett_mfma(GettArgs p) {
     const T sgnA = p.conjA ? T(-1) : T(1);
     const T sgnB = p.conjB ? T(-1) : T(1);
 
-    for (int b = blockIdx.y; b < p.batch; b += gridDim.y) {
+    for (int b = b0; b < p.batch; b += bstep) {
         if (gett_skip(p, b, m0, n0)) continue;
         const __amdgpu_buffer_rsrc_t rA = make_rsrc(reinterpret_cast<const C2 *>(p.A) + p.a_boff[b], p.a_bytes);
         const __amdgpu_buffer_rsrc_t rB = make_rsrc(reinterpret_cast<const C2 *>(p.B) + p.b_boff[b], p.b_bytes);
@@ -294,7 +294,7 @@ gett_mfma(GettArgs p) {
         }
         // epilogue: see Tr<T>::row for the accumulator layout
         C2 *Pb = p.ksplit > 1
-                     ? reinterpret_cast<C2 *>(p.part) + ((int64_t)blockIdx.z * p.batch + b) * (int64_t)p.M * p.N
+                     ? reinterpret_cast<C2 *>(p.part) + ((int64_t)kz * p.batch + b) * (int64_t)p.M * p.N
                      : nullptr;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
@@ -327,6 +327,36 @@ gett_mfma(GettArgs p) {
     }
 }
 
+template <typename T, int BM, int BN, int BK, int WGM, int WGN, bool G3>
+__global__ void __launch_bounds__(64 * WGM * WGN, 2)
+gett_mfma(GettArgs p) {
+    __shared__ GettTiles<T, BM, BN, BK> sm;
+    extern __shared__ int ktab[];   // non-affine k tables of the block's K slice
+    // a masked launch keeps the dispatch order, which deals consecutive tiles
+    // round-robin over the XCDs: with contiguous per-XCD ranges the tiles of
+    // one sample would sit on one or two XCDs and the others would idle
+    const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
+    const int tile = p.mask ? (int)blockIdx.x : xcd_remap(blockIdx.x, tiles);
+    gett_block<T, BM, BN, BK, WGM, WGN, G3>(p, tile, blockIdx.y, gridDim.y, blockIdx.z, sm, ktab);
+}
+
+// Many independent problems in one launch: workgroup i computes the tile,
+// batch item and K slice named by blk[i] of the problem tab[blk[i].prob].
+// Each output is the same sum, in the same order, as from gett_mfma (3M).  Bound
+// by latency: a problem alone is a few tiles of one to a few dozen k-steps, 5 to
+// 8 us whatever its size, and a BP sweep has about a hundred.  Together they are
+// four to eight launches: tn_bp on the 12 x 12 brick at D = 8 went from 36 to 6.8
+// ms, a Trotter layer of the 129-qubit heavy-hex at D = 16 from 257 to 53 ms.
+template <typename T, int BM, int BN, int BK, int WGM, int WGN>
+__global__ void __launch_bounds__(64 * WGM * WGN, 2)
+gett_group(const GettArgs *tab, const GroupBlock *blk) {
+    __shared__ GettTiles<T, BM, BN, BK> sm;
+    extern __shared__ int ktab[];
+    const GroupBlock g = blk[blockIdx.x];
+    const GettArgs p = tab[g.prob];
+    gett_block<T, BM, BN, BK, WGM, WGN, GAUSS3M>(p, g.tile, g.b, p.batch, g.kz, sm, ktab);
+}
+
 template <typename C2>
 __global__ void __launch_bounds__(256) splitk_reduce(GettArgs p) {
     const int64_t per = (int64_t)p.M * p.N;
@@ -350,6 +380,48 @@ __global__ void __launch_bounds__(256) splitk_reduce(GettArgs p) {
         o.y = si;
         *dst = o;
     }
+}
+
+// Grouped problems with K = 1 (a message of one entry): workgroup i computes the
+// 256 outputs from blk[i].tile * 256 on of batch item blk[i].b, with the roundings
+// of the 3M tile (its products start from +0).  A tile per 64 rows spent 51 us on
+// 129 tensors of 8192 entries, this 8 us.
+__global__ void __launch_bounds__(256) gett_group_k1(const GettArgs *tab, const GroupBlock *blk) {
+#pragma clang fp contract(off)
+    const GroupBlock g = blk[blockIdx.x];
+    const GettArgs p = tab[g.prob];
+    const int64_t e = (int64_t)g.tile * 256 + threadIdx.x;
+    if (e >= (int64_t)p.M * p.N) return;
+    const int m = (int)(e / p.N), n = (int)(e - (int64_t)m * p.N);
+    double2 a = reinterpret_cast<const double2 *>(p.A)[p.a_boff[g.b] + p.a_moff[m] + p.a_koff[0]];
+    double2 b = reinterpret_cast<const double2 *>(p.B)[p.b_boff[g.b] + p.b_noff[n] + p.b_koff[0]];
+    if (p.conjA) a.y = -a.y;
+    if (p.conjB) b.y = -b.y;
+    const double p1 = a.x * b.x + 0.0, p2 = a.y * b.y + 0.0, p3 = (a.x + a.y) * (b.x + b.y) + 0.0;
+    reinterpret_cast<double2 *>(p.C)[p.c_boff[g.b] + p.c_moff[m] + p.c_noff[n]] = make_double2(p1 - p2, p3 - p1 - p2);
+}
+
+// The split-K sums of grouped problems: workgroup i reduces the 256 outputs
+// from blk[i].tile * 256 on of problem tab[blk[i].prob] (all batch items).
+template <typename C2>
+__global__ void __launch_bounds__(256) splitk_reduce_group(const GettArgs *tab, const GroupBlock *blk) {
+    const GroupBlock g = blk[blockIdx.x];
+    const GettArgs p = tab[g.prob];
+    const int64_t per = (int64_t)p.M * p.N, total = per * p.batch;
+    const int64_t e = (int64_t)g.tile * 256 + threadIdx.x;
+    if (e >= total) return;
+    const int b = (int)(e / per);
+    const int64_t mn = e - (int64_t)b * per;
+    const int m = (int)(mn / p.N), n = (int)(mn - (int64_t)m * p.N);
+    const C2 *P = reinterpret_cast<const C2 *>(p.part);
+    C2 o;
+    o.x = o.y = 0;
+    for (int z = 0; z < p.ksplit; ++z) {
+        const C2 v = P[(int64_t)z * total + e];
+        o.x += v.x;
+        o.y += v.y;
+    }
+    reinterpret_cast<C2 *>(p.C)[p.c_boff[b] + p.c_moff[m] + p.c_noff[n]] = o;
 }
 
 // --------------------------------------------------------------------------
@@ -872,6 +944,32 @@ void gett_tile(int cfg, int prec, int *bm, int *bn) {
         default: *bm = 64; *bn = 64; break;
     }
     (void)prec;
+}
+
+hipError_t launch_gett_group(const GettArgs *tab, const GroupBlock *blk, int nblk, int cfg, int ktab_ints,
+                             hipStream_t s) {
+    if (nblk <= 0) return hipSuccess;
+    if (ktab_ints > 2 * GETT_KTAB) return hipErrorInvalidValue;
+    auto go = [&](auto kernel) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)(2 * GETT_KTAB * sizeof(int)));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(nblk), dim3(256), (size_t)ktab_ints * sizeof(int), s, tab, blk);
+        return hipGetLastError();
+    };
+    switch (cfg) {
+        case CFG_64x64: return go(gett_group<double, 64, 64, 16, 2, 2>);
+        case CFG_64x16: return go(gett_group<double, 64, 16, 16, 4, 1>);
+        case CFG_K1: return go(gett_group_k1);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_reduce_group(const GettArgs *tab, const GroupBlock *blk, int nblk, hipStream_t s) {
+    if (nblk <= 0) return hipSuccess;
+    hipLaunchKernelGGL(splitk_reduce_group<double2>, dim3(nblk), dim3(256), 0, s, tab, blk);
+    return hipGetLastError();
 }
 
 static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t s);

@@ -60,8 +60,20 @@ enum GettCfg : int {
     CFG_64x16 = 2,    // skinny N
     CFG_128x64W = 3,  // 8 waves, 32x32 per wave
     CFG_128x128W = 4, // 8 waves, 64x32 per wave (packed split-BF16 only)
-    CFG_COUNT = 5
+    CFG_COUNT = 5,
+    CFG_K1 = 5        // an output per thread (grouped problems with K = 1 only)
 };
+
+// Grouped launches (FP64): independent problems of any shapes in one kernel.
+// tab and blk are device tables; a workgroup takes one blk entry.  With CFG_K1
+// and in launch_reduce_group tile counts blocks of 256 outputs (of one batch item;
+// of all of a split-K problem).
+struct GroupBlock {
+    int prob, tile, b, kz;
+};
+hipError_t launch_gett_group(const GettArgs *tab, const GroupBlock *blk, int nblk, int cfg, int ktab_ints,
+                             hipStream_t s);
+hipError_t launch_reduce_group(const GettArgs *tab, const GroupBlock *blk, int nblk, hipStream_t s);
 
 hipError_t launch_gett(const GettArgs &a, int prec, int cfg, hipStream_t s);
 // Split-BF16 operand packing: element (row, k) of batch item b at
@@ -271,8 +283,8 @@ hipError_t launch_logp(const double *amp, const double *mlog, int batch, double 
 // 1 left, 2 down, 3 right); msg [N][4][Dm][Dm]: incoming messages; nbr [N][4]:
 // the neighbour receiving through each leg, -1 without a bond.  Stores the
 // Hermitian part of every sent message, normalised to unit Frobenius norm, as
-// the neighbour's incoming message; dmax [N * 4] scratch; *delta = largest
-// element change (infinity if a message vanished or overflowed).
+// the neighbour's incoming message; dmax [N * 4] scratch; *delta (optional) =
+// largest element change (infinity if a message vanished or overflowed).
 hipError_t launch_bp_update(const void *out, void *msg, const int *nbr, int N, int Dm, double *dmax, double *delta,
                             hipStream_t s);
 // outr [N][Dm][Dm]: the message each site would send to the right (pair closed

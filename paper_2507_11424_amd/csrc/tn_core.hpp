@@ -112,6 +112,7 @@ struct BpOpts {
     int max_sweeps = 1000;
     double tol = 1e-13;
     bool loops = true;          // also the loop BP error of every primitive loop
+    bool free_energy = true;    // also Z_BP (log_abs, arg)
     void *messages = nullptr;   // optional device copy of the final messages [N][4][Dm][Dm]
     // optional device messages to start from (same layout, those of an earlier
     // state of the same lattice); identity / sqrt(D) on every bond otherwise
