@@ -168,6 +168,11 @@ void simple_update(Engine &E, PepsDev &P, const std::vector<SuGate> &gates, cons
             }
         }
     }
+    struct KeepSums {
+        Engine &E;
+        explicit KeepSums(Engine &e) : E(e) { E.keep_sums = true; }
+        ~KeepSums() { E.keep_sums = false; }
+    } keep_sums(E);
     const int nmat = gstride ? ng : 1;
     Ten Gd = E.make({nmat, 4, 4});
     Ten msg = E.make({N, 4, Dm, Dm});

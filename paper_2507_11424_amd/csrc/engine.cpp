@@ -1017,14 +1017,16 @@ Ten Engine::contract_new(const Op &A, const Op &B, const std::string &ic) {
     return C;
 }
 
-void Engine::qr(const tnk::QrArgs &a) {
+void Engine::qr(const tnk::QrArgs &a0) {
+    tnk::QrArgs a = a0;
+    a.keep_sums = keep_sums ? 1 : 0;
     if (a.n > 64 && a.m >= a.n && (int64_t)a.m * a.n > 8192) {
         // one workgroup per matrix would factor it alone: blocks of 64 columns,
         // block Gram-Schmidt between them and Householder TSQR within
         ortho_impl(a, true);
         return;
     }
-    const size_t ws = tnk::qr_workspace_bytes(a.m, a.n, a.batch);
+    const size_t ws = tnk::qr_workspace_bytes(a.m, a.n, a.batch, a.keep_sums);
     void *w = pool_.get(ws);
     {
         std::ostringstream k;

@@ -147,6 +147,13 @@ class Engine {
     // sampler truncates its amplitude boundaries, whose zero-padded bonds make
     // the fit's matrices rank-deficient (CholeskyQR needs full column rank)
     bool householder_only = false;
+    // Set by the simple update: Householder QR keeps the order of its sums (the
+    // LDS kernels).  Its pair SVD is a one-sided Jacobi, which multiplies columns
+    // by the phases of products that are rounding residue where columns are
+    // already orthogonal, so the phases of the singular vectors, and with them
+    // the updated site tensors, depend on the last bit of its input: another
+    // order of summation gives the same state in another gauge.
+    bool keep_sums = false;
     // Contractions issued while a mask is set skip the tiles of the items z of
     // letter `letter` with mask[z] == skip (device int array over that letter's
     // extent) when the letter is the slowest of the batch, M or N index space;

@@ -89,14 +89,16 @@ void gett_tile(int cfg, int prec, int *bm, int *bn);
 // Element (i, j) of matrix b of A: A + b*a_bs + i*a_rs + j*a_cs (complex
 // elements of size esz: 16 = complex128, 8 = complex64), conjugated if a_conj.
 // Outputs Q (m x k, k = min(m, n)) with the same addressing scheme, and R (k x n)
-// if R != nullptr.  Workspace: see qr_workspace_bytes.
+// if R != nullptr.  Workspace: see qr_workspace_bytes.  keep_sums: every sum in
+// the order of the LDS kernels (see Engine::keep_sums).
 struct QrArgs {
     int m, n, batch;
     const void *A; int a_esz; int64_t a_bs, a_rs, a_cs; int a_conj;
     void *Q; int q_esz; int64_t q_bs, q_rs, q_cs; int q_conj;
     void *R; int r_esz; int64_t r_bs, r_rs, r_cs; int r_conj;
+    int keep_sums;
 };
-size_t qr_workspace_bytes(int m, int n, int batch);
+size_t qr_workspace_bytes(int m, int n, int batch, int keep_sums);
 hipError_t launch_qr(const QrArgs &a, void *workspace, hipStream_t s);
 // Householder QR (one workgroup per matrix, global memory) of the batch items
 // whose flags[b] has bit 4 set (a clamped Cholesky pivot), overwriting their Q

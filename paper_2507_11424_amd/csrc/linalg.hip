@@ -2,13 +2,15 @@
 // (chi * phys) x chi site matrices (the gauge moves of the one-site fit), norms,
 // renormalisation, Philox initial guesses.
 //
-// QR is a tall-skinny (TSQR) tree: the rows are split into balanced blocks of at
-// most QR_LDS / n rows, each block is factored by one workgroup entirely in LDS
-// (Householder, wavefront reductions), the stacked n x n R factors are factored
-// the same way level by level, and the explicit thin Q is formed top-down by
-// applying each block's reflectors to its chunk of the parent Q.  Matrices with
-// more than 64 columns that do not fit one block fall back to a one-workgroup
-// factorisation in global memory.
+// QR is a tall-skinny (TSQR) tree: the rows are split into balanced blocks, each
+// block is factored by one workgroup (Householder), the stacked n x n R factors
+// are factored the same way level by level, and the explicit thin Q is formed
+// top-down by applying each block's reflectors to its chunk of the parent Q.
+// Up to 64 columns a block is at most QR_REG_ROWS rows in registers (k_qr_reg),
+// else, and where the order of the sums must stay (QrArgs::keep_sums), at most
+// QR_LDS / n rows in LDS (k_qr_leaf, k_qr_form).  Matrices with more than 64
+// columns that do not fit one block fall back to a one-workgroup factorisation
+// in global memory.
 #include "kernels.hpp"
 
 #include <algorithm>
@@ -286,7 +288,7 @@ __global__ void __launch_bounds__(QR_NT) k_qr_leaf(LeafArgs a) {
 struct FormArgs {
     int rows, n, nb, k, top, level0;
     char *ws; int64_t ws_bs;
-    size_t v_off, t_off, x_off, q_off;  // x_off: parent Q ((nb n) x k), q_off: this level's Q
+    size_t v_off, t_off, b_off, x_off, q_off;  // x_off: parent Q ((nb n) x k), q_off: this level's Q
     MatOut out;                          // level 0 destination
 };
 
@@ -326,6 +328,328 @@ __global__ void __launch_bounds__(QR_NT) k_qr_form(FormArgs a) {
         double2 *qb = reinterpret_cast<double2 *>(wb + a.q_off) + (int64_t)r0 * k;
         for (int e = threadIdx.x; e < len * k; e += QR_NT) qb[e] = Y[e];
     }
+}
+
+// The same level of the tree with the block in registers: a workgroup of NT
+// threads is G = NT / NC row groups of NC lanes (NC = 16, 32 or 64 >= n), a lane
+// holds one column of its group's rows, row i in register i / G of group i % G.
+// A step is bound by its serial chain (a reciprocal square root, a division, one
+// barrier), so everything else is kept off it: a group reads the pivot column's
+// entries of its own rows from the owning lane (no LDS), and one reduction over
+// the groups carries both the column's norm and its products with all other
+// columns.  The reflector stays unnormalised in its column, p = (ph d, x_j+1, ..),
+// d = |x_j| + sigma, with its factor f = ph / d in the column's lanes:
+// v = conj(f) p, v_j = 1.  At the top of the tree the reflectors, still in
+// registers, are applied to the identity in the same launch.  Measured against
+// the LDS kernels (five barriers a step), Q and R: 128 x 64 339 for 600 us, 4096 x
+// 64 2.08 for 3.69 ms, 128 x 32 141 for 346, 32 of 128 x 16 48 for 234, 64 x 16 46
+// for 109.  512 threads serve 64 columns as well as 256 (338 and 367 us; 1024: 474);
+// up to 32 columns 256 are no slower than 512 and leave room for more blocks.
+constexpr int QR_REG_ROWS = 128;
+constexpr int QR_REG_FEW = 32;  // blocks of at most so many rows hold a quarter of the registers
+
+__device__ inline double lane_get(double v, int lane) {
+    const int2 a = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(a.x, lane),
+                                                __builtin_amdgcn_readlane(a.y, lane)));
+}
+
+// Column j's value in every lane of its group (j the same in all lanes).
+template <int NC> __device__ __forceinline__ double2 column(double2 v, int j) {
+    if constexpr (NC == 64) return make_double2(lane_get(v.x, j), lane_get(v.y, j));
+    const int src = (threadIdx.x & 63 & ~(NC - 1)) | j;
+    return make_double2(__shfl(v.x, src, 64), __shfl(v.y, src, 64));
+}
+
+template <int NC, int NT> struct QrRegShared {
+    double2 part[2][NT / 64][NC];  // [parity of the reduction][wave][column]
+    double2 row[2][NC];      // the pivot row
+};
+constexpr int QR_CH = 8;     // registers handled under one test
+
+// Adds the row groups of a wave (its lanes of equal column).
+template <int NC> __device__ __forceinline__ double2 group_add(double2 v) {
+#pragma unroll
+    for (int o = NC; o < 64; o *= 2) {
+        v.x += __shfl_xor(v.x, o, 64);
+        v.y += __shfl_xor(v.y, o, 64);
+    }
+    return v;
+}
+
+// Visits the registers r of the rows i = g + G r >= lo with f(r, v), v the pivot
+// column's entry of V there; a register none of whose rows is live is skipped
+// eight at a time, and rows above lo get v = 0.
+template <int NC, int NT, int RT, typename F>
+__device__ __forceinline__ void reg_rows(const double2 (&V)[RT], int j, int lo, F f) {
+    constexpr int G = NT / NC, CH = RT < QR_CH ? RT : QR_CH;
+    const int g = threadIdx.x / NC;
+#pragma unroll
+    for (int c = 0; c < RT; c += CH) {
+        if (G * (c + CH) <= lo) continue;  // the same in every thread
+        if (G * c >= lo) {
+#pragma unroll
+            for (int r = c; r < c + CH; ++r) f(r, column<NC>(V[r], j));
+        } else {
+#pragma unroll
+            for (int r = c; r < c + CH; ++r) {
+                const double2 v = column<NC>(V[r], j);
+                const bool live = g + G * r >= lo;
+                f(r, make_double2(live ? v.x : 0.0, live ? v.y : 0.0));
+            }
+        }
+    }
+}
+
+// sum_i conj(p_i) y_i over the wave's rows i >= lo, p = column j of V.
+template <int NC, int NT, int RT>
+__device__ __forceinline__ double2 reg_dot(const double2 (&V)[RT], const double2 (&Y)[RT], int j, int lo) {
+    double2 s[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+    reg_rows<NC, NT, RT>(V, j, lo, [&](int r, double2 v) {
+        double2 &a = s[r & 1];
+        a.x = fma(v.x, Y[r].x, a.x);
+        a.y = fma(v.x, Y[r].y, a.y);
+        a.x = fma(v.y, Y[r].y, a.x);
+        a.y = fma(-v.y, Y[r].x, a.y);
+    });
+    return group_add<NC>(make_double2(s[0].x + s[1].x, s[0].y + s[1].y));
+}
+
+// y_i -= p_i u over the rows i >= lo.
+template <int NC, int NT, int RT>
+__device__ __forceinline__ void reg_take(const double2 (&V)[RT], double2 (&Y)[RT], int j, int lo, double2 u) {
+    reg_rows<NC, NT, RT>(V, j, lo, [&](int r, double2 v) {
+        Y[r].x = fma(-v.x, u.x, Y[r].x);
+        Y[r].y = fma(-v.x, u.y, Y[r].y);
+        Y[r].x = fma(v.y, u.y, Y[r].x);
+        Y[r].y = fma(-v.y, u.x, Y[r].y);
+    });
+}
+
+// Householder steps on X; the lanes of column j end with R[j][j] in beta, tau_j
+// and f_j.  A column whose squares fall below HH_SMALL2 is scaled up by 2^400 (its
+// reflector does not change with scale) and its step taken again, at most three
+// times: then it is zero, with tau = 0.
+template <int NC, int NT, int RT>
+__device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, double2 &beta, double &tau, double2 &fac,
+                                           QrRegShared<NC, NT> &sh) {
+    constexpr int G = NT / NC;
+    const int col = threadIdx.x % NC, g = threadIdx.x / NC, w = threadIdx.x >> 6;
+    beta = make_double2(0.0, 0.0);
+    fac = make_double2(0.0, 0.0);
+    tau = 0.0;
+    const int kmax = rows < n ? rows : n;
+    int pb = 0, ups = 0;
+    for (int j = 0; j < kmax;) {
+        pb ^= 1;
+        const double2 part = reg_dot<NC, NT, RT>(X, X, j, j + 1);
+        if ((threadIdx.x & 63) < NC) sh.part[pb][w][col] = part;
+        const int rj = j / G;  // the pivot row's register
+        double2 mine = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            if (r * G < NC) mine = make_double2(r == rj ? X[r].x : mine.x, r == rj ? X[r].y : mine.y);
+        if (g == j % G) sh.row[pb][col] = mine;
+        __syncthreads();
+        double2 dot = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < NT / 64; ++q) {
+            const double2 p = sh.part[pb][q][col];
+            dot.x += p.x;
+            dot.y += p.y;
+        }
+        const double2 xj = sh.row[pb][col], alpha = sh.row[pb][j];
+        const double a2 = alpha.x * alpha.x + alpha.y * alpha.y;
+        const double s = column<NC>(dot, j).x + a2;
+        // s is the same in every thread, and so is every branch on it
+        if (s < HH_SMALL2) {
+            if (ups < 3) {
+                ++ups;
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+                    if (col == j && g + G * r >= j) { X[r].x *= 0x1p400; X[r].y *= 0x1p400; }
+            } else {
+                ups = 0;
+                ++j;
+            }
+            continue;
+        }
+        const double is = rsqrt(s), sigma = s * is;
+        const double ia = a2 > 0.0 ? rsqrt(a2) : 0.0, d = a2 * ia + sigma, id = 1.0 / d;
+        // u = tau conj(f) v^H x_c with v^H x_c = x_jc + f sum_{i > j} conj(x_ij) x_ic:
+        // tau |f|^2 = 1 / (sigma d), tau conj(f) = conj(ph) / sigma
+        const double2 ph = make_double2(a2 > 0.0 ? alpha.x * ia : 1.0, alpha.y * ia);
+        const double isd = is * id;
+        const double2 px = cmulc(ph, xj);
+        const double2 u = make_double2(col > j ? fma(px.x, is, dot.x * isd) : 0.0,
+                                       col > j ? fma(px.y, is, dot.y * isd) : 0.0);
+        if (col == j) {
+            beta = make_double2(-ph.x * sigma, -ph.y * sigma);
+            for (int i = 0; i < ups; ++i) { beta.x *= 0x1p-400; beta.y *= 0x1p-400; }
+            tau = d * is;
+            fac = make_double2(ph.x * id, ph.y * id);
+        }
+        const bool own = col == j && g == j % G;  // the reflector's first entry
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            if (r * G < NC) {
+                const bool at = own && r == rj;
+                X[r].x = at ? ph.x * d : X[r].x;
+                X[r].y = at ? ph.y * d : X[r].y;
+            }
+        reg_take<NC, NT, RT>(X, X, j, j, u);
+        ups = 0;
+        ++j;
+    }
+}
+
+// Y <- H_0 ... H_{k-1} Y, the reflectors in V (lanes of column j, with tau and f).
+template <int NC, int NT, int RT>
+__device__ __forceinline__ void reg_apply(double2 (&Y)[RT], const double2 (&V)[RT], int k, double tau, double2 fac,
+                                          QrRegShared<NC, NT> &sh) {
+    const int col = threadIdx.x % NC, w = threadIdx.x >> 6;
+    const double t2 = tau * (fac.x * fac.x + fac.y * fac.y);  // tau conj(f) f
+    int pb = 0;
+    for (int j = k - 1; j >= 0; --j) {
+        const double tj = column<NC>(make_double2(t2, 0.0), j).x;
+        if (__builtin_amdgcn_readfirstlane(tj == 0.0)) continue;  // the same in every thread
+        pb ^= 1;
+        const double2 part = reg_dot<NC, NT, RT>(V, Y, j, j);
+        if ((threadIdx.x & 63) < NC) sh.part[pb][w][col] = part;
+        __syncthreads();
+        double2 ws = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < NT / 64; ++q) {
+            const double2 p = sh.part[pb][q][col];
+            ws.x += p.x;
+            ws.y += p.y;
+        }
+        reg_take<NC, NT, RT>(V, Y, j, j, make_double2(tj * ws.x, tj * ws.y));
+    }
+}
+
+template <int NC, int NT, int RT>
+__device__ __forceinline__ void reg_store_q(const FormArgs &f, const double2 (&Y)[RT], int r0, int len, char *wb) {
+    constexpr int G = NT / NC;
+    const int col = threadIdx.x % NC, g = threadIdx.x / NC;
+    char *ob = f.level0 ? reinterpret_cast<char *>(f.out.p) + (int64_t)blockIdx.y * f.out.bs * f.out.esz : nullptr;
+    double2 *qb = reinterpret_cast<double2 *>(wb + f.q_off);
+    if (col >= f.k) return;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int i = g + G * r;
+        if (i >= len) continue;
+        if (ob) st_c(ob, f.out.esz, (int64_t)(r0 + i) * f.out.rs + (int64_t)col * f.out.cs, Y[r], f.out.conj);
+        else qb[(int64_t)(r0 + i) * f.k + col] = Y[r];
+    }
+}
+
+// Factors one block of a level; at the top also forms its Q (f).
+template <int NC, int NT, int RT, bool TOP>
+__global__ void __launch_bounds__(NT, NT / 256) k_qr_reg(LeafArgs a, FormArgs f) {
+    __shared__ QrRegShared<NC, NT> sh;
+    constexpr int G = NT / NC;
+    const int blk = blockIdx.x, bt = blockIdx.y, n = a.n;
+    const int col = threadIdx.x % NC, g = threadIdx.x / NC;
+    const int r0 = (int)(((int64_t)blk * a.rows) / a.nb);
+    const int r1 = (int)(((int64_t)(blk + 1) * a.rows) / a.nb);
+    const int len = r1 - r0, k = len < n ? len : n;
+    char *wb = a.ws + (int64_t)bt * a.ws_bs;
+    const char *inb = reinterpret_cast<const char *>(a.in.p) + (int64_t)bt * a.in.bs * a.in.esz;
+    double2 X[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int i = g + G * r;
+        X[r] = i < len && col < n ? ld_c(inb, a.in.esz, (int64_t)(r0 + i) * a.in.rs + (int64_t)col * a.in.cs, a.in.conj)
+                                  : make_double2(0.0, 0.0);
+    }
+    double2 beta, fac;
+    double tau;
+    reg_factor<NC, NT, RT>(X, len, n, beta, tau, fac, sh);
+    // R: beta on the diagonal, the registers above it
+    if (col < n && (!TOP || a.want_r)) {
+        double2 *Rb = TOP ? nullptr : reinterpret_cast<double2 *>(wb + a.rs_off) + (int64_t)blk * n * n;
+        char *rb = TOP ? reinterpret_cast<char *>(a.R.p) + (int64_t)bt * a.R.bs * a.R.esz : nullptr;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const int i = g + G * r;
+            if (i >= (TOP ? k : n)) continue;
+            const bool diag = i < k && col == i, up = i < k && col > i;
+            const double2 v = make_double2(diag ? beta.x : up ? X[r].x : 0.0, diag ? beta.y : up ? X[r].y : 0.0);
+            if (TOP) st_c(rb, a.R.esz, (int64_t)i * a.R.rs + (int64_t)col * a.R.cs, v, a.R.conj);
+            else Rb[i * n + col] = v;
+        }
+    }
+    if constexpr (TOP) {
+        double2 Y[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r) Y[r] = make_double2(g + G * r == col && col < k ? 1.0 : 0.0, 0.0);
+        __syncthreads();  // the last step's reads of the partial sums
+        reg_apply<NC, NT, RT>(Y, X, k, tau, fac, sh);
+        reg_store_q<NC, NT, RT>(f, Y, r0, len, wb);
+    } else {
+        if (col >= n) return;
+        double2 *Vb = reinterpret_cast<double2 *>(wb + a.v_off) + (int64_t)r0 * n;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            if (g + G * r < len) Vb[(int64_t)(g + G * r) * n + col] = X[r];
+        if (g == 0) {
+            reinterpret_cast<double *>(wb + a.t_off)[(int64_t)blk * n + col] = tau;
+            reinterpret_cast<double2 *>(wb + a.b_off)[(int64_t)blk * n + col] = fac;
+        }
+    }
+}
+
+// Applies the reflectors of one block below the top to its chunk of the parent Q.
+template <int NC, int NT, int RT>
+__global__ void __launch_bounds__(NT, NT / 256) k_qr_reg_form(FormArgs f) {
+    __shared__ QrRegShared<NC, NT> sh;
+    constexpr int G = NT / NC;
+    const int blk = blockIdx.x, n = f.n, k = f.k;
+    const int col = threadIdx.x % NC, g = threadIdx.x / NC;
+    const int r0 = (int)(((int64_t)blk * f.rows) / f.nb);
+    const int r1 = (int)(((int64_t)(blk + 1) * f.rows) / f.nb);
+    const int len = r1 - r0, kb = len < n ? len : n;
+    char *wb = f.ws + (int64_t)blockIdx.y * f.ws_bs;
+    const double2 *Vb = reinterpret_cast<const double2 *>(wb + f.v_off) + (int64_t)r0 * n;
+    const double2 *P = reinterpret_cast<const double2 *>(wb + f.x_off);
+    double2 V[RT], Y[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int i = g + G * r;
+        V[r] = i < len && col < n ? Vb[(int64_t)i * n + col] : make_double2(0.0, 0.0);
+        Y[r] = i < kb && col < k ? P[((int64_t)blk * n + i) * k + col] : make_double2(0.0, 0.0);
+    }
+    const double tau = col < n ? reinterpret_cast<const double *>(wb + f.t_off)[(int64_t)blk * n + col] : 0.0;
+    const double2 fac = col < n ? reinterpret_cast<const double2 *>(wb + f.b_off)[(int64_t)blk * n + col]
+                                : make_double2(0.0, 0.0);
+    reg_apply<NC, NT, RT>(Y, V, kb, tau, fac, sh);
+    reg_store_q<NC, NT, RT>(f, Y, r0, len, wb);
+}
+
+// One level of the tree: columns rounded up to 16, 32 or 64 lanes, the registers
+// of 128 rows or of at most QR_REG_FEW.
+template <int NC, int NT> void launch_reg_level(const LeafArgs *a, const FormArgs &f, int rows_per_block, dim3 g,
+                                                hipStream_t s) {
+    constexpr int R = QR_REG_ROWS * NC / NT, F = QR_REG_FEW * NC / NT;
+    const dim3 b(NT);
+    const bool few = rows_per_block <= QR_REG_FEW;
+    if (!a) {
+        if (few) hipLaunchKernelGGL((k_qr_reg_form<NC, NT, F>), g, b, 0, s, f);
+        else hipLaunchKernelGGL((k_qr_reg_form<NC, NT, R>), g, b, 0, s, f);
+    } else if (a->top) {
+        if (few) hipLaunchKernelGGL((k_qr_reg<NC, NT, F, true>), g, b, 0, s, *a, f);
+        else hipLaunchKernelGGL((k_qr_reg<NC, NT, R, true>), g, b, 0, s, *a, f);
+    } else {
+        if (few) hipLaunchKernelGGL((k_qr_reg<NC, NT, F, false>), g, b, 0, s, *a, f);
+        else hipLaunchKernelGGL((k_qr_reg<NC, NT, R, false>), g, b, 0, s, *a, f);
+    }
+}
+
+void launch_reg(const LeafArgs *a, const FormArgs &f, int n, int rows_per_block, dim3 g, hipStream_t s) {
+    if (n <= 16) launch_reg_level<16, 256>(a, f, rows_per_block, g, s);
+    else if (n <= 32) launch_reg_level<32, 256>(a, f, rows_per_block, g, s);
+    else launch_reg_level<64, 512>(a, f, rows_per_block, g, s);
 }
 
 // Fallback: one workgroup per matrix, matrix in global workspace.
@@ -391,10 +715,13 @@ struct TsqrLevel {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
+// Blocks of the tree in registers: the block's columns are one per lane.
+bool use_reg(int n, int keep_sums) { return n <= 64 && !keep_sums; }
+
 // Plans the TSQR tree; returns per-batch workspace bytes.
-size_t plan_tsqr(int m, int n, std::vector<TsqrLevel> &lv) {
+size_t plan_tsqr(int m, int n, int keep_sums, std::vector<TsqrLevel> &lv) {
     lv.clear();
-    const int rb = QR_LDS / n;
+    const int rb = use_reg(n, keep_sums) ? QR_REG_ROWS : QR_LDS / n;
     int rows = m;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
@@ -832,11 +1159,11 @@ hipError_t launch_qr_fallback(const QrArgs &q, const int *flags, void *workspace
     return hipGetLastError();
 }
 
-size_t qr_workspace_bytes(int m, int n, int batch) {
+size_t qr_workspace_bytes(int m, int n, int batch, int keep_sums) {
     if (m <= 0 || n <= 0) return 0;
     std::vector<TsqrLevel> lv;
     size_t w, y, t, b;
-    const size_t per = use_tsqr(m, n) ? plan_tsqr(m, n, lv) : global_qr_bytes(m, n, &w, &y, &t, &b);
+    const size_t per = use_tsqr(m, n) ? plan_tsqr(m, n, keep_sums, lv) : global_qr_bytes(m, n, &w, &y, &t, &b);
     return per * (size_t)batch;
 }
 
@@ -859,7 +1186,7 @@ hipError_t launch_qr(const QrArgs &q, void *workspace, hipStream_t s) {
         return hipGetLastError();
     }
     std::vector<TsqrLevel> lv;
-    const size_t per = plan_tsqr(m, n, lv);
+    const size_t per = plan_tsqr(m, n, q.keep_sums, lv);
     const size_t lds_bytes = (size_t)QR_LDS * 16;
     static bool attr_set = false;
     if (!attr_set) {
@@ -869,6 +1196,17 @@ hipError_t launch_qr(const QrArgs &q, void *workspace, hipStream_t s) {
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         attr_set = true;
     }
+    auto form_of = [&](int L) {
+        FormArgs f;
+        f.rows = lv[L].rows; f.n = n; f.nb = lv[L].nb; f.k = k;
+        f.top = (L + 1 == (int)lv.size()); f.level0 = (L == 0);
+        f.ws = ws; f.ws_bs = (int64_t)per;
+        f.v_off = lv[L].v_off; f.t_off = lv[L].t_off; f.b_off = lv[L].b_off;
+        f.x_off = f.top ? 0 : lv[L + 1].q_off;
+        f.q_off = lv[L].q_off;
+        f.out = qo;
+        return f;
+    };
     for (size_t L = 0; L < lv.size(); ++L) {
         LeafArgs a;
         if (L == 0) a.in = in;
@@ -877,20 +1215,21 @@ hipError_t launch_qr(const QrArgs &q, void *workspace, hipStream_t s) {
         a.ws = ws; a.ws_bs = (int64_t)per;
         a.v_off = lv[L].v_off; a.t_off = lv[L].t_off; a.b_off = lv[L].b_off; a.rs_off = lv[L].rs_off;
         a.R = ro; a.want_r = (q.R != nullptr);
-        hipLaunchKernelGGL(k_qr_leaf, dim3(lv[L].nb, q.batch), dim3(QR_NT), lds_bytes, s, a);
+        if (use_reg(n, q.keep_sums)) {
+            launch_reg(&a, form_of((int)L), n, (lv[L].rows + lv[L].nb - 1) / lv[L].nb, dim3(lv[L].nb, q.batch), s);
+        } else {
+            hipLaunchKernelGGL(k_qr_leaf, dim3(lv[L].nb, q.batch), dim3(QR_NT), lds_bytes, s, a);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     for (int L = (int)lv.size() - 1; L >= 0; --L) {
-        FormArgs f;
-        f.rows = lv[L].rows; f.n = n; f.nb = lv[L].nb; f.k = k;
-        f.top = (L + 1 == (int)lv.size()); f.level0 = (L == 0);
-        f.ws = ws; f.ws_bs = (int64_t)per;
-        f.v_off = lv[L].v_off; f.t_off = lv[L].t_off;
-        f.x_off = f.top ? 0 : lv[L + 1].q_off;
-        f.q_off = lv[L].q_off;
-        f.out = qo;
-        hipLaunchKernelGGL(k_qr_form, dim3(lv[L].nb, q.batch), dim3(QR_NT), lds_bytes, s, f);
+        const FormArgs f = form_of(L);
+        if (!use_reg(n, q.keep_sums)) {
+            hipLaunchKernelGGL(k_qr_form, dim3(lv[L].nb, q.batch), dim3(QR_NT), lds_bytes, s, f);
+        } else if (!f.top) {
+            launch_reg(nullptr, f, n, (lv[L].rows + lv[L].nb - 1) / lv[L].nb, dim3(lv[L].nb, q.batch), s);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
