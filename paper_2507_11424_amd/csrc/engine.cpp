@@ -1088,7 +1088,23 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
     };
     try {
         if (ev) TN_HIP(hipEventRecord(ev->a, s));
-        if (n <= 64) {
+        const double u = 1.1102230246251565e-16;
+        // shift relative to tr(G)/n; tr(G) bounds ||A||_2^2
+        const double shift0 = 11.0 * ((double)m * n + (double)n * (n + 1)) * u * n;
+        // Numerically rank-deficient items (a pivot clamped: the passes cannot
+        // complete a basis from dependent columns) are refactored by Householder,
+        // which returns orthonormal columns for any rank; the others skip it.
+        auto fallback = [&](int *flags) {
+            void *ws = raw(tnk::qr_fallback_workspace_bytes(m, n, Z));
+            TN_HIP(tnk::launch_qr_fallback(a, flags, ws, s));
+            unraw(ws);
+            unraw(flags);
+        };
+        if (!a.R && tnk::cqr_one_fits(m, n)) {
+            int *flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
+            TN_HIP(tnk::launch_cqr_one(a, shift0, flags, s));
+            fallback(flags);
+        } else if (n <= 64) {
             // Three CholeskyQR passes (the first shifted), each one launch over
             // row blocks (rows times the previous inverse factor, their partial
             // Gram matrices), one ordered sum of the partials and one
@@ -1105,10 +1121,8 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
             const size_t r0 = tmp.size();
             if (a.R)
                 for (int i = 0; i < 3; ++i) tmp.push_back(make({Z, n, n}, 16));
-            const double u = 1.1102230246251565e-16;
             // a clamped pivot in any pass flags the item for the Householder fallback
             int *flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
-            TN_HIP(tnk::launch_fill_i32(flags, Z, 0, s));
             for (int pass = 0; pass <= 3; ++pass) {
                 tnk::CqrPass c{};
                 c.m = m; c.n = n; c.batch = Z; c.rb = rb;
@@ -1130,15 +1144,14 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
                 }
                 TN_HIP(tnk::launch_cqr_pass(c, s));
                 if (pass == 3) break;
-                // shift relative to tr(G)/n; tr(G) bounds ||A||_2^2
-                const double shift = pass == 0 ? 11.0 * ((double)m * n + (double)n * (n + 1)) * u * n : 0.0;
+                const double shift = pass == 0 ? shift0 : 0.0;
                 const double clamp = pass == 0 ? 1e-300 : 1e-14;
                 TN_HIP(tnk::launch_sum_parts(reinterpret_cast<const double *>(Pg.p), nblk, n, Z,
                                              reinterpret_cast<double *>(G.p), s));
                 TN_HIP(tnk::launch_chol_inv(reinterpret_cast<const double *>(G.p), n, Z, shift, clamp,
                                             reinterpret_cast<double *>(Ri.p),
                                             a.R ? reinterpret_cast<double *>(tmp[r0 + pass].p) : nullptr, flags,
-                                            s));
+                                            pass == 0, s));
             }
             if (a.R) {
                 contract(op(tmp[r0 + 2], "bij"), op(tmp[r0 + 1], "bjk"), op(G, "bik"));
@@ -1146,13 +1159,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
                 TN_HIP(tnk::launch_strided_copy(Ri.p, 16, (int64_t)n * n, n, 1, a.R, a.r_esz, a.r_bs, a.r_rs, a.r_cs, n,
                                                 n, Z, a.r_conj, s));
             }
-            // Numerically rank-deficient items (a pivot clamped: the passes cannot
-            // complete a basis from dependent columns) are refactored by Householder,
-            // which returns orthonormal columns for any rank; the others skip it.
-            void *ws = raw(tnk::qr_fallback_workspace_bytes(m, n, Z));
-            TN_HIP(tnk::launch_qr_fallback(a, flags, ws, s));
-            unraw(ws);
-            unraw(flags);
+            fallback(flags);
         } else {
             // Wider than one Cholesky block: columns in blocks of 64; each block is
             // made orthogonal to the finished ones by three passes of block

@@ -111,10 +111,14 @@ hipError_t launch_qr_fallback(const QrArgs &a, const int *flags, void *workspace
 // Cholesky of Hermitian G (batch x n x n, complex128, only the upper triangle is
 // read) as G + shift * tr(G)/n * I = R^H R, Rinv = R^{-1} (upper triangular,
 // complex128, batch x n x n) and, if Rf is not null, R itself.  A pivot below
-// clamp * tr(G)/n is raised to it (flags[b] |= 4 when that happens).  One
-// workgroup per matrix; n <= 64.
+// clamp * tr(G)/n is raised to it (flags[b] |= 4 when that happens; `first` clears
+// flags[b] before).  One workgroup per matrix; n <= 64.
 hipError_t launch_chol_inv(const double *G, int n, int batch, double shift, double clamp, double *Rinv, double *Rf,
-                           int *flags, hipStream_t s);
+                           int *flags, int first, hipStream_t s);
+// The three passes of shifted CholeskyQR (Q only) of every matrix in one launch, a
+// workgroup each; flags[b] = 4 where a pivot was raised, else 0.
+bool cqr_one_fits(int m, int n);
+hipError_t launch_cqr_one(const QrArgs &a, double shift, int *flags, hipStream_t s);
 // One CholeskyQR pass over row blocks of p.rb rows (see k_cqr_rows): rows of
 // the batch x m x n (n <= 64) source, times the previous pass's inverse factor
 // Ri when given, written to X (contiguous complex128) and/or dst (strided), and

@@ -22,7 +22,6 @@ namespace {
 
 constexpr int QR_NT = 256;
 constexpr int CQR_ROWS = 32;  // rows of a CholeskyQR pass staged in LDS at a time
-constexpr int CQR_LD = 65;    // padded LDS row of those passes (complex doubles)
 constexpr int SUM_E = 8;      // entries per workgroup of the partial-sum reduction
 constexpr int QR_LDS = 8192;  // complex doubles held by one workgroup (128 KiB)
 constexpr int QR_G = QR_NT / 64;
@@ -754,269 +753,440 @@ size_t global_qr_bytes(int m, int n, size_t *w, size_t *y, size_t *t, size_t *b)
     return off;
 }
 
-// ---------------------------------------------------------------- Cholesky + inverse
-// One workgroup of 1024 threads per matrix, n <= 64.  Right-looking elimination on
-// the augmented pair [W | E] = [G + sI | I]: at pivot k every lower row i takes
-//   row_i -= conj(W[k][i]) / W[k][k] * row_k
-// on both halves, and row k is scaled by 1 / sqrt(W[k][k]).  With G + sI =
-// L D L^H this leaves W = D^{1/2} L^H = R (upper) and E = D^{-1/2} L^{-1} =
-// R^{-H} (lower), so R^{-1} = E^H comes out of the same sweep, with no
-// back substitution.  Thread (row i, lane q of CL per row) keeps its part of the
-// row in registers: W[i][j] for j = i + q + CL m >= i and E[i][j] for
-// j = q + CL m <= i (m < NMAX / CL); the owners of row k + 1 publish it to LDS
-// (two buffers) for the next pivot: one barrier per pivot.  Sixteen lanes per
-// row (1024 threads, four waves per SIMD) hide the latency of the short
-// dependent chains.  Rf (optional) receives R.
-__device__ inline void csub_conj_mul(double2 &w, double ax, double ay, double2 c) {
-    // w -= (ax - i ay) * c, i.e. w -= conj(a) c / d with (ax, ay) = a / d
-    w.x = fma(-ax, c.x, w.x);
-    w.x = fma(-ay, c.y, w.x);
-    w.y = fma(-ax, c.y, w.y);
-    w.y = fma(ay, c.x, w.y);
+// ---------------------------------------------------------------- CholeskyQR
+// Matrices of up to 64 columns, padded to P = 1..4 blocks of 16: the Gram
+// matrices, the triangular products and the block steps of the Cholesky
+// factorisation run on v_mfma_f64_16x16x4 (four real products per complex one),
+// with the operands in LDS as planar (re, im) arrays.  A lane l of a fragment
+// holds (row or column l % 16, k = l / 16); a result register r holds (row 4 r +
+// l / 16, column l % 16).
+typedef double v4d __attribute__((ext_vector_type(4)));
+constexpr int CB = 16;         // block edge
+template <int LD> struct CMat { double (*re)[LD]; double (*im)[LD]; };
+template <int P> constexpr int CLD = CB * P + 2;  // padded LDS row of P blocks
+struct CAcc { v4d re, im; };
+
+__device__ __forceinline__ void acc_zero(CAcc &c) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c.re[r] = c.im[r] = 0.0;
+}
+__device__ __forceinline__ void acc_mma(CAcc &c, double ar, double ai, double br, double bi) {
+    c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, c.re, 0, 0, 0);
+    c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, c.im, 0, 0, 0);
+    c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, c.re, 0, 0, 0);
+    c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, c.im, 0, 0, 0);
+}
+// c += op(A) B over 16 k indices: op(A)(m, k) = A[ar + m][ac + k], or with HERM
+// conj(A[ar + k][ac + m]); B(k, n) = B[br + k][bc + n].
+template <bool HERM, int LA, int LB>
+__device__ __forceinline__ void acc_block(CAcc &c, CMat<LA> A, int ar, int ac, CMat<LB> B, int br, int bc, int lane) {
+    const int x = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int k = 0; k < CB; k += 4) {
+        const int i = HERM ? ar + k + q : ar + x, j = HERM ? ac + x : ac + k + q;
+        const double pr = A.re[i][j], pi = A.im[i][j];
+        acc_mma(c, pr, HERM ? -pi : pi, B.re[br + k + q][bc + x], B.im[br + k + q][bc + x]);
+    }
+}
+// M[r0.., c0..] (a 16 x 16 block) = s * c, or += with ADD.
+template <bool ADD, int LD>
+__device__ __forceinline__ void acc_store(const CAcc &c, CMat<LD> M, int r0, int c0, double s, int lane) {
+    const int x = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        double &re = M.re[r0 + 4 * r + q][c0 + x], &im = M.im[r0 + 4 * r + q][c0 + x];
+        re = (ADD ? re : 0.0) + s * c.re[r];
+        im = (ADD ? im : 0.0) + s * c.im[r];
+    }
 }
 
-// NMAX rows of CL lanes each (64 x 16 = 1024 threads).  G holds nparts
-// matrices per batch item ([batch][nparts][n][n]) whose sum is factored.
-template <int NMAX, int CL>
-__global__ void __launch_bounds__(NMAX * CL) k_chol_inv(const double2 *G, int nparts, int n, double shift,
-                                                       double clamp, double2 *Rinv, double2 *Rf, int *flags) {
-    constexpr int CT = NMAX * CL;   // threads per matrix
-    constexpr int CM = NMAX / CL;   // row elements per lane
-    __shared__ double2 PW[2][NMAX];
-    __shared__ double2 PE[2][NMAX];
-    __shared__ double PD[2][2];  // pivot (raised to the clamp if below it) and its reciprocal
-    __shared__ double red[CT / 64];
-    const int b = blockIdx.x, t = threadIdx.x;
-    const double2 *Gb = G + (int64_t)b * nparts * n * n;
-    const int ti = t / CL, tq = t % CL;
-    const bool row = ti < n;
-    double2 w[CM], e[CM];
-#pragma unroll
-    for (int m = 0; m < CM; ++m) {
-        const int j = ti + tq + CL * m;
-        w[m] = make_double2(0.0, 0.0);
-        if (row && j < n)
-            for (int q = 0; q < nparts; ++q) {  // fixed order: the sum is reproducible
-                const double2 g = Gb[((int64_t)q * n + ti) * n + j];
-                w[m].x += g.x;
-                w[m].y += g.y;
-            }
-        const int je = tq + CL * m;
-        e[m] = make_double2(row && je == ti ? 1.0 : 0.0, 0.0);
+// 1 / d for d > 0 in the normal range: the hardware estimate and two Newton steps.
+__device__ __forceinline__ double recip(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
+}
+// Lane K of each row of 16 lanes, to the whole row.
+template <int K> __device__ __forceinline__ double row_lane(double v) {
+    const int2 a = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, a.x, 0x150 + K, 0xf, 0xf, false),
+                                                __builtin_amdgcn_update_dpp(0, a.y, 0x150 + K, 0xf, 0xf, false)));
+}
+
+// One wave: the 16 x 16 Hermitian diagonal block at `o` of W becomes R (upper,
+// zero below) and that block of E its inverse.  Elimination on the pair [W | I]:
+// at pivot k every later row i takes row_i -= W[i][k] / W[k][k] row_k on both
+// halves, which leaves D^{1/2} R above the diagonal and D^{-1/2} R^{-H} on the
+// other side.  Lane l holds rows 4 r + l / 16 of column l % 16.  A pivot below
+// cl is raised to it (returns true).  Bound by the chain pivot -> reciprocal ->
+// next pivot.
+struct DiagState { double2 w[4], e[4]; double d[4]; };
+template <int K>
+__device__ __forceinline__ void diag_pivot(DiagState &s, double cl, bool &bad, int lane) {
+    constexpr int rk = K >> 2, qk = K & 3;
+    const int x = lane & 15, q = lane >> 4;
+    double d = lane_get(s.w[rk].x, qk * 16 + K);
+    if (!(d >= cl)) {  // the same in every lane
+        bad = true;
+        d = cl > 0.0 ? cl : 1e-300;
     }
-    // tr(G) / n
-    {
-        double v = (row && tq == 0) ? w[0].x : 0.0;
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if ((t & 63) == 0) red[t >> 6] = v;
-    }
-    __syncthreads();
-    double tr = 0.0;
+    const double inv = recip(d);
+    s.d[rk] = q == qk ? d : s.d[rk];
+    const int src = qk * 16 + x;
+    const double2 pw = make_double2(__shfl(s.w[rk].x, src, 64), __shfl(s.w[rk].y, src, 64));
+    const double2 pe = make_double2(__shfl(s.e[rk].x, src, 64), __shfl(s.e[rk].y, src, 64));
 #pragma unroll
-    for (int i = 0; i < CT / 64; ++i) tr += red[i];
-    const double scale = tr / n;
-    const double sh = shift * scale, cl = clamp * scale;
-    if (row && tq == 0) w[0].x += sh;
-    // the owner of a pivot row publishes the row, the pivot and its reciprocal
-    auto publish_pivot = [&](int slot) {
-        double d = w[0].x;
-        if (!(d >= cl)) {
-            if (flags) flags[b] |= 4;
-            d = cl > 0.0 ? cl : 1e-300;
+    for (int r = rk; r < 4; ++r) {
+        const double t = 4 * r + q > K ? inv : 0.0;
+        const double ax = row_lane<K>(s.w[r].x) * t, ay = row_lane<K>(s.w[r].y) * t;
+        s.w[r].x = fma(-ax, pw.x, fma(ay, pw.y, s.w[r].x));
+        s.w[r].y = fma(-ax, pw.y, fma(-ay, pw.x, s.w[r].y));
+        s.e[r].x = fma(-ax, pe.x, fma(ay, pe.y, s.e[r].x));
+        s.e[r].y = fma(-ax, pe.y, fma(-ay, pe.x, s.e[r].y));
+    }
+}
+template <int K>
+__device__ __forceinline__ void diag_pivots(DiagState &s, double cl, bool &bad, int lane) {
+    diag_pivot<K>(s, cl, bad, lane);
+    if constexpr (K < 15) diag_pivots<K + 1>(s, cl, bad, lane);
+}
+template <int LD>
+__device__ __forceinline__ bool diag_factor(CMat<LD> W, CMat<LD> E, int o, double cl, int lane) {
+    const int x = lane & 15, q = lane >> 4;
+    DiagState s;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 4 * r + q;
+        s.w[r] = make_double2(W.re[o + i][o + x], W.im[o + i][o + x]);
+        s.e[r] = make_double2(i == x ? 1.0 : 0.0, 0.0);
+        s.d[r] = 1.0;
+    }
+    bool bad = false;
+    diag_pivots<0>(s, cl, bad, lane);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 4 * r + q;
+        const double rs = 1.0 / sqrt(s.d[r]);
+        W.re[o + i][o + x] = x > i ? s.w[r].x * rs : x == i ? s.d[r] * rs : 0.0;
+        W.im[o + i][o + x] = x > i ? s.w[r].y * rs : 0.0;
+        E.re[o + x][o + i] = x <= i ? s.e[r].x * rs : 0.0;
+        E.im[o + x][o + i] = x <= i ? -s.e[r].y * rs : 0.0;
+    }
+    return bad;
+}
+
+// W (P x P blocks, the diagonal blocks Hermitian in full, the blocks above them
+// filled) = R^H R: R replaces W's upper part and E receives R^{-1} (upper blocks).
+// NW waves; returns whether a pivot was raised (wave 0).  Right-looking over
+// panels of 16: one wave factors the diagonal block, the others' work (the
+// panel's row of R, the trailing update, the inverse's off-diagonal blocks) is
+// matrix products spread over the waves.  E and W may be the same array for P <= 2.
+template <int P, int NW, int LD>
+__device__ __forceinline__ bool chol_blocks(CMat<LD> W, CMat<LD> E, double cl, int wave, int lane) {
+    bool bad = false;
+#pragma unroll 1
+    for (int p = 0; p < P; ++p) {
+        if (wave == 0) bad |= diag_factor(W, E, CB * p, cl, lane);
+        __syncthreads();
+        for (int j = p + 1 + wave; j < P; j += NW) {  // R_pj = R_pp^{-H} W_pj
+            CAcc c;
+            acc_zero(c);
+            acc_block<true>(c, E, CB * p, CB * p, W, CB * p, CB * j, lane);
+            acc_store<false>(c, W, CB * p, CB * j, 1.0, lane);
         }
-        PD[slot][0] = d;
-        PD[slot][1] = 1.0 / d;
-    };
-    if (ti == 0) {
-#pragma unroll
-        for (int m = 0; m < CM; ++m) {
-            const int j = tq + CL * m;
-            if (j < n) { PW[0][j] = w[m]; PE[0][j] = e[m]; }
-        }
-        if (tq == 0) publish_pivot(0);
+        __syncthreads();
+        int t = 0;
+        for (int i = p + 1; i < P; ++i)
+            for (int j = i; j < P; ++j, ++t) {
+                if (t % NW != wave) continue;
+                CAcc c;
+                acc_zero(c);
+                acc_block<true>(c, W, CB * p, CB * i, W, CB * p, CB * j, lane);
+                acc_store<true>(c, W, CB * i, CB * j, -1.0, lane);
+            }
+        __syncthreads();
     }
-    __syncthreads();
-    double myrk = 1.0;  // 1 / sqrt of this row's pivot
-    for (int k = 0; k < n; ++k) {
-        const int pb = k & 1;
-        const double d = PD[pb][0];
-        if (ti == k) {
-            myrk = 1.0 / sqrt(d);
-            if (tq == 0) w[0] = make_double2(d, 0.0);  // a raised pivot stays consistent
-        } else if (row && ti > k) {
-            const double inv = PD[pb][1];
-            const double2 a = PW[pb][ti];
-            const double ax = a.x * inv, ay = a.y * inv;
-            double2 cw[CM], ce[CM];
-#pragma unroll
-            for (int m = 0; m < CM; ++m) {
-                const int j = ti + tq + CL * m;
-                cw[m] = PW[pb][j < NMAX ? j : NMAX - 1];  // unconditional loads, then select
-                ce[m] = PE[pb][tq + CL * m];
-            }
-#pragma unroll
-            for (int m = 0; m < CM; ++m) {
-                if (ti + tq + CL * m < n) csub_conj_mul(w[m], ax, ay, cw[m]);
-                if (tq + CL * m <= k) csub_conj_mul(e[m], ax, ay, ce[m]);
-            }
-            if (ti == k + 1) {
-#pragma unroll
-                for (int m = 0; m < CM; ++m) {
-                    const int j = tq + CL * m;
-                    if (ti + j < n) PW[pb ^ 1][ti + j] = w[m];  // column ti + tq + CL m
-                    if (j < n) PE[pb ^ 1][j] = e[m];
-                }
-                if (tq == 0) publish_pivot(pb ^ 1);  // w[0]: the diagonal, final after pivot k
-            }
+#pragma unroll 1
+    for (int d = 1; d < P; ++d) {
+        for (int i = wave; i + d < P; i += NW) {  // E_ij = -E_ii sum_k R_ik E_kj
+            const int j = i + d;
+            CAcc c;
+            acc_zero(c);
+            for (int k = i + 1; k <= j; ++k) acc_block<false>(c, W, CB * i, CB * k, E, CB * k, CB * j, lane);
+            acc_store<false>(c, E, CB * i, CB * j, 1.0, lane);
+            CAcc f;
+            acc_zero(f);
+            acc_block<false>(f, E, CB * i, CB * i, E, CB * i, CB * j, lane);
+            acc_store<false>(f, E, CB * i, CB * j, -1.0, lane);
         }
         __syncthreads();
     }
-    if (!row) return;
-    // R[i][j] = W[i][j] / sqrt(d_i) (j >= i), R^{-1}[j][i] = conj(E[i][j]) / sqrt(d_i) (j <= i)
-    double2 *Ob = Rinv + (int64_t)b * n * n;
-#pragma unroll
-    for (int m = 0; m < CM; ++m) {
-        const int j = tq + CL * m;
-        if (j < n) Ob[j * n + ti] = j <= ti ? make_double2(e[m].x * myrk, -e[m].y * myrk) : make_double2(0.0, 0.0);
+    return bad;
+}
+
+// Mean diagonal of the n x n matrix in W (every thread gets it), then the shift
+// and a diagonal of that mean on the padding.  Ends with a barrier.
+template <int LD>
+__device__ __forceinline__ double chol_scale(CMat<LD> W, int n, int np, double shift, double *red) {
+    const int t = threadIdx.x;
+    if (t < 64) {
+        double v = t < n ? W.re[t][t] : 0.0;
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        const double scale = v / n;
+        if (t < n) W.re[t][t] += shift * scale;
+        else if (t < np) W.re[t][t] = scale > 0.0 ? scale : 1.0;
+        if (t == 0) *red = scale;
     }
-    if (Rf) {
-        double2 *Fb = Rf + (int64_t)b * n * n;
+    __syncthreads();
+    return *red;
+}
+
+// Cholesky factor and inverse, one workgroup per matrix (see launch_chol_inv).
+// A 64 x 64 call takes 33 us, half of it in the four diagonal blocks; an
+// elimination of single rows by 1024 threads, bound by its LDS reads, took 44.
+template <int P>
+__global__ void __launch_bounds__(256) k_chol_inv(const double2 *G, int n, double shift, double clamp, double2 *Rinv,
+                                                 double2 *Rf, int *flags, int first) {
+    __shared__ double sm[4][CB * P][CLD<P>];
+    __shared__ double red;
+    const CMat<CLD<P>> W{sm[0], sm[1]}, E{sm[2], sm[3]};
+    const int b = blockIdx.x, t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const double2 *Gb = G + (int64_t)b * n * n;
+    constexpr int NP = CB * P;
 #pragma unroll
-        for (int m = 0; m < CM; ++m) {
-            const int j = ti + tq + CL * m;
-            if (j < n) Fb[ti * n + j] = j == ti ? make_double2(w[m].x * myrk, 0.0)
-                                                : make_double2(w[m].x * myrk, w[m].y * myrk);
-            const int jl = tq + CL * m;
-            if (jl < ti) Fb[ti * n + jl] = make_double2(0.0, 0.0);
-        }
+    for (int u = 0; u < NP * NP / 256; ++u) {
+        const int e = t + 256 * u, i = e / NP, j = e % NP;
+        const bool in = i < n && j < n, up = j >= i;
+        double2 g = make_double2(0.0, 0.0);
+        if (in) g = up ? Gb[i * n + j] : Gb[j * n + i];  // only the upper triangle is given
+        W.re[i][j] = g.x;
+        W.im[i][j] = i == j ? 0.0 : up ? g.y : -g.y;
+    }
+    __syncthreads();
+    const double scale = chol_scale(W, n, NP, shift, &red);
+    const bool bad = chol_blocks<P, 4>(W, E, clamp * scale, wave, lane);
+    if (t == 0 && flags) flags[b] = (first ? 0 : flags[b]) | (bad ? 4 : 0);
+    double2 *Ob = Rinv + (int64_t)b * n * n;
+    double2 *Fb = Rf ? Rf + (int64_t)b * n * n : nullptr;
+    for (int e = t; e < n * n; e += 256) {
+        const int i = e / n, j = e % n;
+        const bool up = j >= i;
+        Ob[e] = up ? make_double2(E.re[i][j], E.im[i][j]) : make_double2(0.0, 0.0);
+        if (Fb) Fb[e] = up ? make_double2(W.re[i][j], W.im[i][j]) : make_double2(0.0, 0.0);
     }
 }
 
-// One pass of CholeskyQR over a block of p.rb rows of a (batch x m x n,
-// n <= 64) complex matrix, 256 threads, CQR_ROWS rows staged in LDS at a time:
-// the rows are read through p.src's strides (complex64 or complex128,
-// conjugated if asked), multiplied by the inverse factor p.Ri of the previous
-// pass when given (Y = X Ri, Ri upper triangular), written to the contiguous
-// complex128 rows p.X and/or through p.dst's strides, and their Gram matrix
-// Y^H Y (upper triangle) is written to p.part[b][block] when p.part is given.
-// Each thread of the Gram owns a 4 x 4 block of it; each thread of the product
-// owns one row and 8 columns of Y.
+// One pass of CholeskyQR over a block of p.rb rows of a (batch x m x n, n <= 16 P)
+// complex matrix, CQR_ROWS rows staged in LDS at a time: the rows are read through
+// p.src's strides (complex64 or complex128, conjugated if asked), multiplied by
+// the inverse factor p.Ri of the previous pass when given (Y = X Ri, Ri upper
+// triangular: the zero blocks are skipped), written to the contiguous complex128
+// rows p.X and/or through p.dst's strides, and their Gram matrix Y^H Y (upper
+// triangle) is written to p.part[b][block] when p.part is given.  Two row tiles
+// by P column tiles of the product and P (P + 1) / 2 tiles of the Gram matrix
+// are dealt to the four waves so that each has the same number of k steps (at P =
+// 4) and keeps its Gram tiles in registers over the staged chunks.  With the
+// products on the vector unit a pass was bound by its LDS reads: 28 us on 4096 x
+// 64, now 14 (the whole orthonormalisation 164 for 285 us; 512 x 32 70 for 146).
+template <int P>
 __global__ void __launch_bounds__(256) k_cqr_rows(CqrPass p) {
-    __shared__ double2 sRi[64][CQR_LD];
-    __shared__ double2 sA[CQR_ROWS][CQR_LD];
-    __shared__ double2 sY[CQR_ROWS][CQR_LD];
-    const int t = threadIdx.x, b = blockIdx.y, n = p.n;
+    constexpr int NP = CB * P;
+    constexpr int TG = P * (P + 1) / 2;          // Gram tiles
+    constexpr int GW = (TG + 3) / 4;             // of one wave
+    __shared__ double sX[2][CQR_ROWS][CLD<P>];
+    __shared__ double sY[2][CQR_ROWS][CLD<P>];
+    __shared__ double sR[2][NP][CLD<P>];
+    const CMat<CLD<P>> X{sX[0], sX[1]}, Yr{sY[0], sY[1]}, Ri{sR[0], sR[1]};
+    const int t = threadIdx.x, b = blockIdx.y, n = p.n, wave = t >> 6, lane = t & 63;
     const int r_beg = blockIdx.x * p.rb, r_end = min(p.m, r_beg + p.rb);
     const bool apply = p.Ri != nullptr;
-    if (apply) {  // all loads issued before the LDS stores (n * n <= 16 * 256)
-        const double2 *Rb = reinterpret_cast<const double2 *>(p.Ri) + (int64_t)b * n * n;
-        double2 rv[16];
+    const bool by_col = p.s_cs != 1;             // source contiguous along rows
+    constexpr int LX = CQR_ROWS * NP / 256;
+    double2 xv[LX];
+    auto load = [&](int r0) {                    // one chunk, all loads issued together
+        const int nr = min(CQR_ROWS, r_end - r0);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < LX; ++i) {
             const int e = t + 256 * i;
-            rv[i] = e < n * n ? Rb[e] : make_double2(0.0, 0.0);
+            const int r = by_col ? e % CQR_ROWS : e / NP, c = by_col ? e / CQR_ROWS : e % NP;
+            xv[i] = (r < nr && c < n) ? ld_c(p.src, p.s_esz, (int64_t)b * p.s_bs + (int64_t)(r0 + r) * p.s_rs +
+                                                                 (int64_t)c * p.s_cs, p.s_conj)
+                                      : make_double2(0.0, 0.0);
+        }
+    };
+    load(r_beg);
+    if (apply) {
+        const double2 *Rb = reinterpret_cast<const double2 *>(p.Ri) + (int64_t)b * n * n;
+        double2 rv[NP * NP / 256];
+#pragma unroll
+        for (int i = 0; i < NP * NP / 256; ++i) {
+            const int e = t + 256 * i, r = e / NP, c = e % NP;
+            rv[i] = r < n && c < n ? Rb[r * n + c] : make_double2(0.0, 0.0);
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int e = t + 256 * i;
-            if (e < n * n) sRi[e / n][e % n] = rv[i];
+        for (int i = 0; i < NP * NP / 256; ++i) {
+            const int e = t + 256 * i, r = e / NP, c = e % NP;
+            Ri.re[r][c] = rv[i].x;
+            Ri.im[r][c] = rv[i].y;
         }
     }
-    const int gi = (t >> 4) * 4, gj = (t & 15) * 4;        // Gram block
-    const bool gown = p.part && gi < n && gj < n && gi <= gj + 3;
-    double2 g[4][4];
+    CAcc g[GW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) g[i][j] = make_double2(0.0, 0.0);
-    const int yr = t >> 3, yc = t & 7;                      // product: row yr, columns yc + 8 q
-    const bool by_col = p.s_cs != 1;                        // source contiguous along rows
+    for (int i = 0; i < GW; ++i) acc_zero(g[i]);
     for (int r0 = r_beg; r0 < r_end; r0 += CQR_ROWS) {
         const int nr = min(CQR_ROWS, r_end - r0);
-        {   // CQR_ROWS * n <= 8 * 256 elements: all loads issued before the LDS stores
-            double2 av[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int e = t + 256 * i;
-                const int r = by_col ? e % CQR_ROWS : e / n, c = by_col ? e / CQR_ROWS : e % n;
-                av[i] = (e < CQR_ROWS * n && r < nr)
-                            ? ld_c(p.src, p.s_esz, (int64_t)b * p.s_bs + (int64_t)(r0 + r) * p.s_rs +
-                                                       (int64_t)c * p.s_cs, p.s_conj)
-                            : make_double2(0.0, 0.0);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int e = t + 256 * i;
-                const int r = by_col ? e % CQR_ROWS : e / n, c = by_col ? e / CQR_ROWS : e % n;
-                if (e < CQR_ROWS * n) sA[r][c] = av[i];
-            }
+        for (int i = 0; i < LX; ++i) {
+            const int e = t + 256 * i;
+            const int r = by_col ? e % CQR_ROWS : e / NP, c = by_col ? e / CQR_ROWS : e % NP;
+            X.re[r][c] = xv[i].x;
+            X.im[r][c] = xv[i].y;
         }
         __syncthreads();
-        double2 (*Y)[CQR_LD] = sA;
+        if (r0 + CQR_ROWS < r_end) load(r0 + CQR_ROWS);
+        CMat<CLD<P>> Y = X;
         if (apply) {
-            double2 y[8];
+            // row tile wave % 2; waves 0, 1 take the outer columns, 2, 3 the inner ones
 #pragma unroll
-            for (int q = 0; q < 8; ++q) y[q] = make_double2(0.0, 0.0);
-#pragma unroll 8
-            for (int k = 0; k < n; ++k) {
-                const double2 a = sA[yr][k];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int j = yc + 8 * q;
-                    if (j < n && k <= j) {
-                        const double2 r = sRi[k][j];
-                        y[q].x = fma(a.x, r.x, fma(-a.y, r.y, y[q].x));
-                        y[q].y = fma(a.x, r.y, fma(a.y, r.x, y[q].y));
-                    }
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int j = yc + 8 * q;
-                if (j < n) sY[yr][j] = y[q];
+            for (int c = 0; c < P; ++c) {
+                const bool outer = c == 0 || c == P - 1;
+                if ((P <= 2 ? c % 2 == 0 : outer) != (wave < 2)) continue;
+                CAcc a;
+                acc_zero(a);
+                for (int k = 0; k <= c; ++k) acc_block<false>(a, X, CB * (wave & 1), CB * k, Ri, CB * k, CB * c, lane);
+                acc_store<false>(a, Yr, CB * (wave & 1), CB * c, 1.0, lane);
             }
             __syncthreads();
-            Y = sY;
+            Y = Yr;
         }
         if (p.X)
             for (int e = t; e < nr * n; e += 256) {
                 const int r = e / n, c = e % n;
-                reinterpret_cast<double2 *>(p.X)[((int64_t)b * p.m + r0 + r) * n + c] = Y[r][c];
+                reinterpret_cast<double2 *>(p.X)[((int64_t)b * p.m + r0 + r) * n + c] = make_double2(Y.re[r][c], Y.im[r][c]);
             }
         if (p.dst)
             for (int e = t; e < nr * n; e += 256) {
                 int r, c;
                 if (p.d_cs != 1) { c = e / nr; r = e % nr; }
                 else { r = e / n; c = e % n; }
-                st_c(p.dst, p.d_esz, (int64_t)b * p.d_bs + (int64_t)(r0 + r) * p.d_rs + (int64_t)c * p.d_cs, Y[r][c],
-                     p.d_conj);
+                st_c(p.dst, p.d_esz, (int64_t)b * p.d_bs + (int64_t)(r0 + r) * p.d_rs + (int64_t)c * p.d_cs,
+                     make_double2(Y.re[r][c], Y.im[r][c]), p.d_conj);
             }
-        if (gown)
-            for (int r = 0; r < nr; ++r) {
-                double2 xi[4], xj[4];
+        if (p.part) {
+            int q = 0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    xi[i] = Y[r][gi + i < n ? gi + i : 0];
-                    xj[i] = Y[r][gj + i < n ? gj + i : 0];
-                }
+            for (int i = 0; i < P; ++i)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int j = i; j < P; ++j, ++q)
+                    if (q % 4 == wave) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {  // conj(x_i) x_j
-                        g[i][j].x = fma(xi[i].x, xj[j].x, fma(xi[i].y, xj[j].y, g[i][j].x));
-                        g[i][j].y = fma(xi[i].x, xj[j].y, fma(-xi[i].y, xj[j].x, g[i][j].y));
+                        for (int k = 0; k < CQR_ROWS; k += CB)
+                            acc_block<true>(g[q / 4], Y, k, CB * i, Y, k, CB * j, lane);
                     }
-            }
+        }
         __syncthreads();
     }
-    if (gown) {
-        double2 *P = reinterpret_cast<double2 *>(p.part) + ((int64_t)b * gridDim.x + blockIdx.x) * n * n;
+    if (p.part) {
+        double2 *G = reinterpret_cast<double2 *>(p.part) + ((int64_t)b * gridDim.x + blockIdx.x) * n * n;
+        int q = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < P; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (gi + i < n && gj + j < n) P[(gi + i) * n + gj + j] = g[i][j];
+            for (int j = i; j < P; ++j, ++q)
+                if (q % 4 == wave) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = CB * i + 4 * r + (lane >> 4), col = CB * j + (lane & 15);
+                        if (row < n && col < n) G[row * n + col] = make_double2(g[q / 4].re[r], g[q / 4].im[r]);
+                    }
+                }
     }
+}
+
+// The whole orthonormalisation of one matrix in one workgroup, n <= 32 columns and
+// at most CQR1_ROWS rows (135 KiB of LDS), which stay there through the three
+// passes: Gram matrix (each wave a share of the rows, the partial sums added in
+// wave order), its factor's inverse in place, rows times inverse.  flags[b] as from
+// launch_chol_inv.  Replaces eleven launches where a matrix alone cannot fill the
+// chip: 128 x 32 takes 61 us (145 before), 32 of 128 x 16 28 (103), 64 x 16 21 (96).
+constexpr int CQR1_ROWS = 256;
+constexpr int XLD = 33;  // padded LDS row of 32 complex doubles
+template <int P>
+__global__ void __launch_bounds__(256) k_cqr_one(QrArgs a, double shift, int *flags) {
+    extern __shared__ double2 lds[];                 // X [rows of 16][XLD]
+    __shared__ double sW[2][CB * P][CLD<P>];
+    __shared__ double red;
+    constexpr int NP = CB * P;
+    const CMat<CLD<P>> W{sW[0], sW[1]};
+    const int t = threadIdx.x, b = blockIdx.x, m = a.m, n = a.n, wave = t >> 6, lane = t & 63;
+    const int x = lane & 15, q = lane >> 4;
+    const int mt = (m + CB - 1) / CB;                // row tiles
+    const bool by_col = a.a_cs != 1;
+    for (int e = t; e < mt * CB * NP; e += 256) {
+        const int r = by_col ? e % (mt * CB) : e / NP, c = by_col ? e / (mt * CB) : e % NP;
+        lds[r * XLD + c] = r < m && c < n ? ld_c(a.A, a.a_esz, (int64_t)b * a.a_bs + (int64_t)r * a.a_rs +
+                                                                   (int64_t)c * a.a_cs, a.a_conj)
+                                          : make_double2(0.0, 0.0);
+    }
+    bool bad = false;
+    for (int pass = 0; pass < 3; ++pass) {
+        __syncthreads();
+        CAcc g[P][P];
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int j = i; j < P; ++j) acc_zero(g[i][j]);
+        for (int r = wave; r < mt; r += 4)
+#pragma unroll
+            for (int k = 0; k < CB; k += 4) {
+                double2 v[P];
+#pragma unroll
+                for (int i = 0; i < P; ++i) v[i] = lds[(CB * r + k + q) * XLD + CB * i + x];
+#pragma unroll
+                for (int i = 0; i < P; ++i)
+#pragma unroll
+                    for (int j = i; j < P; ++j) acc_mma(g[i][j], v[i].x, -v[i].y, v[j].x, v[j].y);
+            }
+        for (int w = 0; w < 4; ++w) {
+            if (wave == w)
+#pragma unroll
+                for (int i = 0; i < P; ++i)
+#pragma unroll
+                    for (int j = i; j < P; ++j) {
+                        if (w == 0) acc_store<false>(g[i][j], W, CB * i, CB * j, 1.0, lane);
+                        else acc_store<true>(g[i][j], W, CB * i, CB * j, 1.0, lane);
+                    }
+            __syncthreads();
+        }
+        const double scale = chol_scale(W, n, NP, pass == 0 ? shift : 0.0, &red);
+        bad |= chol_blocks<P, 4>(W, W, (pass == 0 ? 1e-300 : 1e-14) * scale, wave, lane);
+        for (int r = wave; r < mt; r += 4) {
+            CAcc y[P];
+#pragma unroll
+            for (int c = 0; c < P; ++c) acc_zero(y[c]);
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int k = 0; k < CB; k += 4) {
+                    const double2 v = lds[(CB * r + x) * XLD + CB * i + k + q];
+#pragma unroll
+                    for (int c = i; c < P; ++c)
+                        acc_mma(y[c], v.x, v.y, W.re[CB * i + k + q][CB * c + x], W.im[CB * i + k + q][CB * c + x]);
+                }
+#pragma unroll
+            for (int c = 0; c < P; ++c)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    lds[(CB * r + 4 * k + q) * XLD + CB * c + x] = make_double2(y[c].re[k], y[c].im[k]);
+        }
+    }
+    __syncthreads();
+    const bool q_col = a.q_cs != 1;
+    for (int e = t; e < m * n; e += 256) {
+        const int r = q_col ? e % m : e / n, c = q_col ? e / m : e % n;
+        st_c(a.Q, a.q_esz, (int64_t)b * a.q_bs + (int64_t)r * a.q_rs + (int64_t)c * a.q_cs, lds[r * XLD + c], a.q_conj);
+    }
+    if (t == 0) flags[b] = bad ? 4 : 0;
 }
 
 // G[b][e] = sum over p of parts[b][p][e] (e < nn), in a fixed order: 256
@@ -1073,12 +1243,33 @@ __global__ void __launch_bounds__(256) k_strided_copy(const char *in, int ie, in
 }  // namespace
 
 hipError_t launch_chol_inv(const double *G, int n, int batch, double shift, double clamp, double *Rinv, double *Rf,
-                           int *flags, hipStream_t s) {
+                           int *flags, int first, hipStream_t s) {
     if (n > 64 || n < 1) return hipErrorInvalidValue;
     const double2 *g = reinterpret_cast<const double2 *>(G);
     double2 *ri = reinterpret_cast<double2 *>(Rinv), *rf = reinterpret_cast<double2 *>(Rf);
-    hipLaunchKernelGGL((k_chol_inv<64, 16>), dim3(batch), dim3(1024), 0, s, g, 1, n, shift, clamp, ri, rf, flags);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(batch), dim3(256), 0, s, g, n, shift, clamp, ri, rf, flags, first); };
+    if (n <= 16) go(k_chol_inv<1>);
+    else if (n <= 32) go(k_chol_inv<2>);
+    else if (n <= 48) go(k_chol_inv<3>);
+    else go(k_chol_inv<4>);
     return hipGetLastError();
+}
+
+bool cqr_one_fits(int m, int n) { return n <= 32 && m <= CQR1_ROWS; }
+
+hipError_t launch_cqr_one(const QrArgs &a, double shift, int *flags, hipStream_t s) {
+    if (a.m <= 0 || a.n <= 0 || a.batch <= 0) return hipSuccess;
+    if (!cqr_one_fits(a.m, a.n) || a.R || !flags) return hipErrorInvalidValue;
+    const size_t lds = (size_t)((a.m + CB - 1) / CB * CB) * XLD * sizeof(double2);
+    auto go = [&](auto kernel) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)(CQR1_ROWS * XLD * sizeof(double2)));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(256), lds, s, a, shift, flags);
+        return hipGetLastError();
+    };
+    return a.n <= 16 ? go(k_cqr_one<1>) : go(k_cqr_one<2>);
 }
 
 int cqr_rows_per_block(int m) {
@@ -1102,7 +1293,11 @@ hipError_t launch_cqr_pass(const CqrPass &p, hipStream_t s) {
     if (p.n < 1 || p.n > 64 || p.rb < CQR_ROWS || p.rb % CQR_ROWS) return hipErrorInvalidValue;
     if (p.batch > 65535) return hipErrorInvalidValue;
     const int nblk = (p.m + p.rb - 1) / p.rb;
-    hipLaunchKernelGGL(k_cqr_rows, dim3(nblk, p.batch), dim3(256), 0, s, p);
+    const dim3 g(nblk, p.batch), t(256);
+    if (p.n <= 16) hipLaunchKernelGGL(k_cqr_rows<1>, g, t, 0, s, p);
+    else if (p.n <= 32) hipLaunchKernelGGL(k_cqr_rows<2>, g, t, 0, s, p);
+    else if (p.n <= 48) hipLaunchKernelGGL(k_cqr_rows<3>, g, t, 0, s, p);
+    else hipLaunchKernelGGL(k_cqr_rows<4>, g, t, 0, s, p);
     return hipGetLastError();
 }
 
