@@ -287,7 +287,7 @@ std::string Engine::plan_report(int top) const {
         if (p->calls == 0) continue;
         const double tf = p->ms > 0 ? p->flops * p->calls / (p->ms * 1e-3) / 1e12 : 0.0;
         os << p->ms << '\t' << p->calls << '\t' << tf << '\t' << p->desc << (p->pack ? " packed" : "")
-           << (p->fp32 ? " fp32" : "") << " cfg=" << p->cfg
+           << (p->fp32 == 2 ? " fp32-4M" : p->fp32 ? " fp32" : "") << " cfg=" << p->cfg
            << " split=" << p->base.ksplit << (p->tuned ? " tuned" : "") << '\n';
     }
     os << "calls\tfactorisation\n";
@@ -342,7 +342,7 @@ static bool pack_pays(const Op &A, const Op &B) {
     return op_rows(A, B) > 128 && op_rows(B, A) > 128;
 }
 
-Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0) {
+Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
     const Op A = squeeze(A0), B = squeeze(B0), C = squeeze(C0);
     std::ostringstream ks;
     auto addk = [&](const Op &o) {
@@ -351,7 +351,8 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0) {
         ks << '|';
     };
     addk(A); addk(B); addk(C);
-    const std::string key = std::to_string(prec) + '#' + ks.str();  // plans are per precision
+    const std::string tkey = std::to_string(prec) + '#' + ks.str();  // plans are per precision
+    const std::string key = (keep ? "k" : "") + tkey;
     auto it = plans_.find(key);
     if (it != plans_.end()) return it->second.get();
 
@@ -530,7 +531,7 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0) {
     P->kml = swap ? nl : ml;
     P->knl = swap ? ml : nl;
     P->ldim = dim;
-    P->key = key;
+    P->key = tkey;
     P->flops = 8.0 * (double)M * (double)N * (double)K * (double)Z;
     {
         std::ostringstream d;
@@ -541,19 +542,84 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0) {
     auto tc = tune_cache_.find(P->key);
     if (tc != tune_cache_.end()) {
         P->pack = P->can_pack && tc->second.pack;
-        P->fp32 = (prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6) && tc->second.fp32 && !P->pack;
+        P->fp32 = (prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6) && !P->pack ? tc->second.fp32 : 0;
         set_split(P.get(), tc->second.cfg, tc->second.ks);
         P->tuned = true;
-    } else {
+    } else if (keep) {
         int cfg;
         if (kN <= 16) cfg = tnk::CFG_64x16;
         else if (kM >= 8192 && kN >= 128 && K >= 16) cfg = tnk::CFG_128x64;
         else cfg = tnk::CFG_64x64;
         set_split(P.get(), cfg, 0);
+    } else {
+        choose_tile(P.get());
     }
     Plan *raw = P.get();
     plans_[key] = std::move(P);
     return raw;
+}
+
+// Tile, K slices and (in the split modes) kernel of a contraction, by its extents.
+// All figures: MI355X, random operands, microseconds for M x N x K [x batch].
+//
+// A problem is large when its 64x64 tiles fill the 256 CUs, or would if a K of
+// many hundreds were cut into slices of at least 256; then the tile with the most
+// work per loaded byte wins:
+//   FP64 and FP32: 64x64 on 4 waves (3M).  720896 x 128 x 128: 1546 against 2488 for
+//   128x64 with 4M, which leaves one wave per SIMD.  Outputs of up to 32 columns
+//   take 64x16 (131072 x 32 x 32 x 8: 321 for 415), of up to 32 rows 32x32 (400).
+//   Split-BF16, packed (both sides above 128): 128x128 while its tiles fill the CUs
+//   (8192 x 4096 x 4096 in bf16x6: 6083 against 7344 for 128x64 on 4 waves, 6596 on
+//   8; 16384 x 256 x 512 x 8: 1101 / 1300), else 128x64 on 8 waves (512 x 4096 x
+//   4096: 546 / 578 / 723).
+//   Split-BF16, split while staging: 128x64 on 8 waves (1048576 x 64 x 64: 489 for 805),
+//   64x128 where there are fewer than 128 rows.
+// A small one is bound by the walk along K of its few workgroups: 32x32 tiles (or
+// 64x16, as fast and wider in M, for a short K) and slices of K down to 32 until
+// the CUs are covered, from K = 192 on (a second kernel adds the slices, 5 us).
+// 32 x 512 x 512: 13 against 26 for 64x64 in 4 slices; 64 x 4096 x 64: 9 for 15;
+// 243 x 27 x 729: 13 for 29.
+// In the split modes a short K leaves nothing to amortise the splitting over: the
+// FP32 kernel with four products, up to K = 32 for bf16x6 and 64 for bf16x3, where
+// its error is no larger (against 64 bits, K = 32 and below: at most 1.03e-7
+// relative on normal numbers and 6.1e-8 on positive ones for bf16x6's 1.17e-7 and
+// 7.6e-8; K = 64: 2.0e-7 and 1.2e-7 for bf16x3's 4.4e-6 and 7.1e-7).  262144 x 64 x
+// 16: 138 in bf16x6 and 52 in FP32.
+void Engine::choose_tile(Plan *P) {
+    const int64_t M = P->kM, N = P->kN, K = P->K, Z = P->Z;
+    auto tiles = [&](int cfg) {
+        int bm = 64, bn = 64;
+        tnk::gett_tile(cfg, prec, &bm, &bn);
+        return ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * Z;
+    };
+    const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
+    P->pack = false;
+    P->fp32 = bf16 && K <= (prec == tnk::P_BF16X6 ? 32 : 64) ? 2 : 0;
+    const bool split = bf16 && !P->fp32;  // the split-BF16 kernels
+    const int64_t t64 = tiles(tnk::CFG_64x64);
+    const bool large = t64 >= 256 || t64 * (K / 256) >= 256;
+    int cfg;
+    int64_t ks = 1;
+    if (N <= 16) {
+        cfg = tnk::CFG_64x16;
+    } else if (!large) {
+        cfg = K <= 64 && M >= 64 ? tnk::CFG_64x16 : tnk::CFG_32x32;
+    } else if (!split) {
+        cfg = N <= 32 && M >= 64 ? tnk::CFG_64x16 : M <= 32 ? tnk::CFG_32x32 : tnk::CFG_64x64;
+    } else if (P->can_pack && t64 >= 256) {
+        P->pack = true;
+        cfg = tiles(tnk::CFG_128x128W) >= 256 ? tnk::CFG_128x128W : tnk::CFG_128x64W;
+    } else {
+        cfg = M >= 128 ? tnk::CFG_128x64W : N >= 128 ? tnk::CFG_64x128W : tnk::CFG_64x64;
+    }
+    const int64_t t = tiles(cfg);
+    // FP64 / FP32 keep two workgroups of 64x64 on a CU
+    const int64_t want = cfg == tnk::CFG_64x64 && large ? 512 : 256;
+    if (t < want) {
+        const int64_t least = large ? 256 : 32;  // shortest slice
+        if (large || K >= 192) ks = std::max<int64_t>(1, std::min<int64_t>(want / t, K / least));
+    }
+    set_split(P, cfg, (int)ks);
 }
 
 // ksplit_hint: 0 = heuristic (split K when the output tiles alone cannot fill
@@ -592,7 +658,7 @@ void Engine::set_autotune(bool on, const std::string &cache_path) {
     std::string k;
     int cfg, ks, pk, f32;
     while (f >> k >> cfg >> ks >> pk >> f32)
-        if (cfg >= 0 && cfg < tnk::CFG_COUNT && ks >= 1) tune_cache_[k] = {cfg, ks, pk ? 1 : 0, f32 ? 1 : 0};
+        if (cfg >= 0 && cfg < tnk::CFG_COUNT && ks >= 1) tune_cache_[k] = {cfg, ks, pk ? 1 : 0, f32 == 2 ? 2 : f32 ? 1 : 0};
 }
 
 // Times every candidate (tile configuration x split-K choice) on the call's own
@@ -604,18 +670,21 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
     // In the split-BF16 modes the FP32 kernel (same complex64 storage, at least
     // as accurate) is a candidate too: it can win on shapes whose short K or
     // narrow N leave the split products little to amortise.
-    struct Cand { int cfg, ks; bool pack, fp32; };
+    struct Cand { int cfg, ks; bool pack; int fp32; };
     std::vector<Cand> cands;
     const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
-    const int cfgs[5] = {tnk::CFG_64x16, tnk::CFG_64x64, tnk::CFG_128x64, tnk::CFG_128x64W, tnk::CFG_128x128W};
+    const int cfgs[7] = {tnk::CFG_64x16,   tnk::CFG_64x64,    tnk::CFG_128x64,  tnk::CFG_128x64W,
+                         tnk::CFG_128x128W, tnk::CFG_32x32,    tnk::CFG_64x128W};
     for (int pk = 0; pk < 3; ++pk) {
-        const bool pack = pk == 1, f32 = pk == 2;
+        const bool pack = pk == 1;
+        const int f32 = pk == 2 ? 1 : 0;
         if (pack && !P->can_pack) continue;
         if (f32 && !bf16) continue;
         for (int c : cfgs) {
             if ((c == tnk::CFG_128x64 || c == tnk::CFG_128x64W || c == tnk::CFG_128x128W) && P->kM < 128) continue;
             if (c == tnk::CFG_128x128W && (!pack || P->kN < 128)) continue;  // packed split-BF16 only
             if (c == tnk::CFG_64x16 && P->kN > 64) continue;
+            if (c == tnk::CFG_64x128W && (!bf16 || f32 || P->kN < 128)) continue;  // split-BF16 only
             int bm = 64, bn = 64;
             tnk::gett_tile(c, prec, &bm, &bn);
             const int64_t tiles = ((P->kM + bm - 1) / bm) * ((P->kN + bn - 1) / bn) * P->Z;
@@ -633,7 +702,8 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
     TN_HIP(hipEventCreate(&e0));
     TN_HIP(hipEventCreate(&e1));
     const tnk::GettArgs saved = P->base;
-    const bool saved_pack = P->pack, saved_fp32 = P->fp32;
+    const bool saved_pack = P->pack;
+    const int saved_fp32 = P->fp32;
     const Cand start{P->cfg, std::max(P->base.ksplit, 1), P->pack, P->fp32};
     auto run = [&](const Cand &c, int reps) {
         P->pack = c.pack;
@@ -649,7 +719,7 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             tnk::GettArgs u = t;
             void *pa = nullptr, *pb = nullptr;
             if (c.pack) pack_bf16(u, &pa, &pb);
-            TN_HIP(tnk::launch_gett(u, c.fp32 ? (int)tnk::P_FP32 : prec, c.cfg, s));
+            TN_HIP(tnk::launch_gett(u, kernel_prec(*P), c.cfg, s));
             if (pa) pool_.put(pa);
             if (pb) pool_.put(pb);
         }
@@ -687,10 +757,10 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
     P->fp32 = win.fp32;
     set_split(P, win.cfg, win.ks);
     P->tuned = true;
-    tune_cache_[P->key] = {win.cfg, win.ks, win.pack ? 1 : 0, win.fp32 ? 1 : 0};
+    tune_cache_[P->key] = {win.cfg, win.ks, win.pack ? 1 : 0, win.fp32};
     if (!tune_path_.empty()) {
         std::ofstream f(tune_path_, std::ios::app);
-        f << P->key << ' ' << win.cfg << ' ' << win.ks << ' ' << (win.pack ? 1 : 0) << ' ' << (win.fp32 ? 1 : 0)
+        f << P->key << ' ' << win.cfg << ' ' << win.ks << ' ' << (win.pack ? 1 : 0) << ' ' << win.fp32
           << '\n';
     }
 }
@@ -846,13 +916,17 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         }
         return;
     }
-    Plan *P = plan(A, B, C);
+    Plan *P = plan(A, B, C, keep_sums);
     tnk::GettArgs g = args_of(*P, A, B, C, accumulate);
-    int cfg = P->cfg;
-    if (force_cfg == tnk::CFG_128x128W && !P->pack)
-        throw TnError(ST_UNSUPPORTED, "the 128x128 tile serves packed split-BF16 operands only");
-    if (force_cfg >= 0) {
+    int cfg = P->cfg, kprec = kernel_prec(*P);
+    bool pack = P->pack;
+    if (force_cfg >= 0) {  // the mode's own kernel, packed where packing is offered
+        pack = P->can_pack;
+        kprec = prec;
+        if (force_cfg == tnk::CFG_128x128W && !pack)
+            throw TnError(ST_UNSUPPORTED, "the 128x128 tile serves packed split-BF16 operands only");
         Plan tmp = *P;  // shares the tables, owns nothing
+        tmp.pack = pack;
         set_split(&tmp, force_cfg, force_ksplit);
         tmp.dev = nullptr;
         g.ksplit = tmp.base.ksplit;
@@ -863,6 +937,8 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         g.ksplit = P->base.ksplit;
         g.kchunk = P->base.kchunk;
         cfg = P->cfg;
+        kprec = kernel_prec(*P);
+        pack = P->pack;
     }
     bool masked = false;
     if (mask_) {
@@ -877,6 +953,17 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         else if (!P->kml.empty() && P->kml[0] == mask_letter_) { mode = 2; d = div(P->kml); }
         else if (!P->knl.empty() && P->knl[0] == mask_letter_) { mode = 3; d = div(P->knl); }
         if (mode && d <= INT32_MAX) {
+            if (mode > 1 && force_cfg < 0) {
+                // a tile must not straddle two items: a smaller one where the
+                // plan's does (else the launch computes every item)
+                for (int c : {cfg, (int)tnk::CFG_64x64, (int)tnk::CFG_32x32}) {
+                    int bm = 64, bn = 64;
+                    tnk::gett_tile(c, prec, &bm, &bn);
+                    if (d % (mode == 2 ? bm : bn)) continue;
+                    cfg = c;
+                    break;
+                }
+            }
             g.mask = mask_;
             g.mask_mode = mode;
             g.mask_div = (int)d;
@@ -898,8 +985,8 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         TN_HIP(hipEventRecord(ev->a, s));
     }
     void *pka = nullptr, *pkb = nullptr;
-    if (P->pack) pack_bf16(g, &pka, &pkb);
-    TN_HIP(tnk::launch_gett(g, P->fp32 ? (int)tnk::P_FP32 : prec, cfg, s));
+    if (pack) pack_bf16(g, &pka, &pkb);
+    TN_HIP(tnk::launch_gett(g, kprec, cfg, s));
     if (ev) TN_HIP(hipEventRecord(ev->b, s));
     if (part) pool_.put(part);
     if (pka) pool_.put(pka);
@@ -935,7 +1022,7 @@ void Engine::group_add(Group &gr, const Op &A, const Op &B, const Op &C) {
     Plan *P = nullptr;
     if (op_window(A, B, C) <= (int64_t)tnk::GETT_MAX_WINDOW && op_window(B, A, C) <= (int64_t)tnk::GETT_MAX_WINDOW &&
         op_window(C, A, B) / C.esz <= (int64_t)INT32_MAX)
-        P = plan(A, B, C);
+        P = plan(A, B, C, true);
     if (!P || P->cfg == tnk::CFG_128x64) {  // cut into slices, or the 4M tile: run by itself
         gr.direct.push_back({A, B, C});
         return;

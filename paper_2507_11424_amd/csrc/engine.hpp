@@ -103,7 +103,7 @@ struct Plan {
     int64_t kM = 0, kN = 0, K = 0, Z = 0;
     bool pack = false;    // split-BF16 on packed operand planes (else split while staging)
     bool can_pack = false;  // packing is offered (both matrix sides above 128); the tuner decides
-    bool fp32 = false;      // split-BF16 modes: this shape runs on the FP32 kernel (chosen by the tuner)
+    int fp32 = 0;           // split-BF16 modes: this shape runs on the FP32 kernel, 1: 3M (chosen by the tuner), 2: 4M
     // letters of the batch, kernel-M and kernel-N index spaces, slowest first,
     // and every letter's extent (for masked launches)
     std::string bl, kml, knl;
@@ -147,8 +147,8 @@ class Engine {
     // sampler truncates its amplitude boundaries, whose zero-padded bonds make
     // the fit's matrices rank-deficient (CholeskyQR needs full column rank)
     bool householder_only = false;
-    // Set by the simple update: Householder QR keeps the order of its sums (the
-    // LDS kernels).  Its pair SVD is a one-sided Jacobi, which multiplies columns
+    // Set by the simple update: Householder QR and the contractions keep the order
+    // of their sums (the LDS kernels; the planner's first K slices).  Its pair SVD is a one-sided Jacobi, which multiplies columns
     // by the phases of products that are rounding residue where columns are
     // already orthogonal, so the phases of the singular vectors, and with them
     // the updated site tensors, depend on the last bit of its input: another
@@ -258,7 +258,11 @@ class Engine {
   private:
     Pool pool_;
     std::unordered_map<std::string, std::unique_ptr<Plan>> plans_;
-    Plan *plan(const Op &A, const Op &B, const Op &C);
+    Plan *plan(const Op &A, const Op &B, const Op &C, bool keep);
+    void choose_tile(Plan *P);
+    int kernel_prec(const Plan &P) const {
+        return P.fp32 == 2 ? (int)tnk::P_FP32_4M : P.fp32 ? (int)tnk::P_FP32 : prec;
+    }
     // event pairs recorded around launches in timing mode
     std::deque<EvPair> ev_;
     size_t ev_used_ = 0;

@@ -941,6 +941,8 @@ void gett_tile(int cfg, int prec, int *bm, int *bn) {
         case CFG_64x16: *bm = 64; *bn = 16; break;
         case CFG_128x64W: *bm = 128; *bn = 64; break;
         case CFG_128x128W: *bm = 128; *bn = 128; break;
+        case CFG_32x32: *bm = 32; *bn = 32; break;
+        case CFG_64x128W: *bm = 64; *bn = 128; break;
         default: *bm = 64; *bn = 64; break;
     }
     (void)prec;
@@ -997,6 +999,7 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             case CFG_128x64: return launch_k(gett_mfma<double, 128, 64, 16, 2, 2, false>, a, 128, 64, 256, s);
             case CFG_64x16: return launch_k(gett_mfma<double, 64, 16, 16, 4, 1, GAUSS3M>, a, 64, 16, 256, s);
             case CFG_128x64W: return launch_k(gett_mfma<double, 128, 64, 16, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
+            case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
             default: return hipErrorInvalidValue;
         }
     }
@@ -1006,6 +1009,15 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             case CFG_128x64: return launch_k(gett_mfma<float, 128, 64, 16, 2, 2, false>, a, 128, 64, 256, s);
             case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 4, 1, GAUSS3M>, a, 64, 16, 256, s);
             case CFG_128x64W: return launch_k(gett_mfma<float, 128, 64, 16, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
+            case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (prec == P_FP32_4M) {
+        switch (cfg) {
+            case CFG_64x64: return launch_k(gett_mfma<float, 64, 64, 16, 2, 2, false>, a, 64, 64, 256, s);
+            case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 4, 1, false>, a, 64, 16, 256, s);
+            case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 2, 2, false>, a, 32, 32, 256, s);
             default: return hipErrorInvalidValue;
         }
     }
@@ -1021,6 +1033,10 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
                                             : launch_k(gett_bf16_direct<2, 128, 64, 4, 2>, a, 128, 64, 512, s);
             case CFG_128x128W: return a.kpad ? launch_k(gett_bf16<2, 128, 128, 2, 4, false>, a, 128, 128, 512, s)
                                              : hipErrorInvalidValue;
+            case CFG_32x32: return a.kpad ? launch_k(gett_bf16<2, 32, 32, 2, 2>, a, 32, 32, 256, s)
+                                          : launch_k(gett_bf16_direct<2, 32, 32, 2, 2>, a, 32, 32, 256, s);
+            case CFG_64x128W: return a.kpad ? launch_k(gett_bf16<2, 64, 128, 2, 4>, a, 64, 128, 512, s)
+                                            : launch_k(gett_bf16_direct<2, 64, 128, 2, 4>, a, 64, 128, 512, s);
             default: return hipErrorInvalidValue;
         }
     }
@@ -1035,6 +1051,10 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
                                         : launch_k(gett_bf16_direct<3, 128, 64, 4, 2>, a, 128, 64, 512, s);
         case CFG_128x128W: return a.kpad ? launch_k(gett_bf16<3, 128, 128, 2, 4, false>, a, 128, 128, 512, s)
                                          : hipErrorInvalidValue;
+        case CFG_32x32: return a.kpad ? launch_k(gett_bf16<3, 32, 32, 2, 2>, a, 32, 32, 256, s)
+                                      : launch_k(gett_bf16_direct<3, 32, 32, 2, 2>, a, 32, 32, 256, s);
+        case CFG_64x128W: return a.kpad ? launch_k(gett_bf16<3, 64, 128, 2, 4>, a, 64, 128, 512, s)
+                                        : launch_k(gett_bf16_direct<3, 64, 128, 2, 4>, a, 64, 128, 512, s);
         default: return hipErrorInvalidValue;
     }
 }

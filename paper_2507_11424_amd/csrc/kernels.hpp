@@ -7,7 +7,8 @@
 namespace tnk {
 
 // Compute modes of the contraction engine (mirrors tn_prec).
-enum Prec : int { P_FP64 = 0, P_FP32 = 1, P_BF16X3 = 2, P_BF16X6 = 3 };
+enum Prec : int { P_FP64 = 0, P_FP32 = 1, P_BF16X3 = 2, P_BF16X6 = 3,
+                  P_FP32_4M = 4 };  // FP32 with four real products (a kernel choice of the split modes)
 
 // A batched complex contraction written as a GEMM over gathered indices:
 //   C[b](m, n) (+)= sum_k opA(A[b](m, k)) * opB(B[b](k, n))
@@ -60,8 +61,10 @@ enum GettCfg : int {
     CFG_64x16 = 2,    // skinny N
     CFG_128x64W = 3,  // 8 waves, 32x32 per wave
     CFG_128x128W = 4, // 8 waves, 64x32 per wave (packed split-BF16 only)
-    CFG_COUNT = 5,
-    CFG_K1 = 5        // an output per thread (grouped problems with K = 1 only)
+    CFG_32x32 = 5,    // 4 waves, 16x16 per wave
+    CFG_64x128W = 6,  // 8 waves, 32x32 per wave (split-BF16 only)
+    CFG_COUNT = 7,
+    CFG_K1 = 7        // an output per thread (grouped problems with K = 1 only)
 };
 
 // Grouped launches (FP64): independent problems of any shapes in one kernel.
