@@ -812,10 +812,23 @@ void Engine::pack_bf16(tnk::GettArgs &g, void **pa, void **pb) {
         throw TnError(ST_UNSUPPORTED, "packed split-BF16 operand above 2 GiB per batch item");
     *pa = pool_.get((size_t)ba * g.batch);
     *pb = pool_.get((size_t)bb * g.batch);
+    // a masked launch reads the kept items' rows of the masked operand, and all
+    // of the other one if any item is kept
+    auto pack_mask = [&](int rows_mode) {
+        tnk::PackMask pm{};
+        if (!g.mask) return pm;
+        pm.mask = g.mask;
+        pm.skip = g.mask_skip;
+        pm.mode = g.mask_mode == 1 ? 1 : g.mask_mode == rows_mode ? 2 : 3;
+        pm.div = g.mask_div;
+        const int ext = g.mask_mode == 1 ? g.batch : g.mask_mode == 2 ? g.M : g.N;
+        pm.items = ext / g.mask_div;
+        return pm;
+    };
     TN_HIP(tnk::launch_pack_bf16(np, g.A, g.a_boff, g.a_moff, g.a_koff, g.a_kaff, g.a_ks, g.M, g.K, kpad, g.batch,
-                                 g.conjA, *pa, s));
+                                 g.conjA, *pa, pack_mask(2), s));
     TN_HIP(tnk::launch_pack_bf16(np, g.B, g.b_boff, g.b_noff, g.b_koff, g.b_kaff, g.b_ks, g.N, g.K, kpad, g.batch,
-                                 g.conjB, *pb, s));
+                                 g.conjB, *pb, pack_mask(3), s));
     g.A = *pa;
     g.B = *pb;
     g.kpad = kpad;
@@ -953,22 +966,30 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         else if (!P->kml.empty() && P->kml[0] == mask_letter_) { mode = 2; d = div(P->kml); }
         else if (!P->knl.empty() && P->knl[0] == mask_letter_) { mode = 3; d = div(P->knl); }
         if (mode && d <= INT32_MAX) {
-            if (mode > 1 && force_cfg < 0) {
+            if (mode > 1) {
                 // a tile must not straddle two items: a smaller one where the
-                // plan's does (else the launch computes every item)
+                // plan's does, else every item is computed
+                bool fits = false;
                 for (int c : {cfg, (int)tnk::CFG_64x64, (int)tnk::CFG_32x32}) {
                     int bm = 64, bn = 64;
-                    tnk::gett_tile(c, prec, &bm, &bn);
-                    if (d % (mode == 2 ? bm : bn)) continue;
+                    tnk::gett_tile(c, kprec, &bm, &bn);
+                    if (d % (mode == 2 ? bm : bn)) {
+                        if (force_cfg >= 0) break;
+                        continue;
+                    }
                     cfg = c;
+                    fits = true;
                     break;
                 }
+                if (!fits) mode = 0;
             }
+            masked = true;
+        }
+        if (masked && mode) {
             g.mask = mask_;
             g.mask_mode = mode;
             g.mask_div = (int)d;
             g.mask_skip = mask_skip_;
-            masked = true;
         }
     }
     void *part = nullptr;

@@ -428,28 +428,29 @@ __global__ void __launch_bounds__(256) splitk_reduce_group(const GettArgs *tab, 
 // Split-BF16: FP32 operands split into NP bf16 parts at staging time.
 // MFMA 16x16x32 bf16: lane l holds A[l%16][8*(l/16) .. +8) and
 // B[8*(l/16) .. +8)[l%16]; accumulator layout as the 16x16x4 forms.
-__device__ inline unsigned short bf16_rne(float x) {
-    unsigned int u = __float_as_uint(x);
-    // round to nearest even on the upper 16 bits (inputs are finite here)
-    unsigned int r = u + 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(r >> 16);
-}
-__device__ inline float bf16_to_f(unsigned short h) { return __uint_as_float(((unsigned int)h) << 16); }
-
+// v_cvt_pk_bf16_f32 rounds two floats to nearest even at once: out[q] holds part
+// q of x0 (low half) and of x1 (high half).  Against the rounding by integer
+// arithmetic, with the pairwise stores of the direct kernel and the packing's
+// mask: norm of the D=8 brick lattice at chi=64 in BF16x6 165 -> 157 ms, its
+// samples 805 -> 775 ms.
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 template <int NP>
-__device__ inline void split_bf16(float x, unsigned short *out) {
-    float r = x;
+__device__ inline void split_bf16(float x0, float x1, uint32_t *out) {
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-        unsigned short h = bf16_rne(r);
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){x0, x1}, v2bf));
         out[q] = h;
-        r = r - bf16_to_f(h);
+        x0 -= __uint_as_float(h << 16);
+        x1 -= __uint_as_float(h & 0xFFFF0000u);
     }
 }
 
 // Split-BF16 on unpacked operands: elements gathered through the tables and
 // split into bf16 parts while staging.  Used when one operand is read at most
 // twice (M or N <= 128), where packing would cost more traffic than it saves.
+// Bound by the splitting (vector unit) and its LDS stores, so a thread takes two
+// neighbouring k of a row at a time: one conversion and one 32-bit store for both.
 template <int NP, int BM, int BN, int WGM, int WGN>
 __global__ void __launch_bounds__(64 * WGM * WGN)
 gett_bf16_direct(GettArgs p) {
@@ -460,7 +461,7 @@ gett_bf16_direct(GettArgs p) {
     constexpr int LA = (BM * BK) / NT;
     constexpr int LB = (BK * BN) / NT;
     constexpr int KP = BK + 8;  // padded k extent (bf16 elements), keeps 16-byte alignment
-    static_assert(LA >= 1 && LB >= 1 && NT % BK == 0 && NT >= BM && NT >= BN, "tile");
+    static_assert(LA >= 2 && LB >= 2 && LA % 2 == 0 && LB % 2 == 0 && NT % (BK / 2) == 0 && NT >= BM && NT >= BN, "tile");
     // two LDS stages when they fit in the 160 KiB of a CU, else one
     constexpr int S = (2 * 2 * NP * (BM + BN) * KP * 2 <= 160 * 1024) ? 2 : 1;
     // planes: [stage][re/im][part][row][k]
@@ -484,16 +485,18 @@ gett_bf16_direct(GettArgs p) {
     Stager<LA> sa;
     Stager<LB> sb;
 #pragma unroll
-    for (int i = 0; i < LA; ++i) {
-        if (p.a_kfast) { sa.kk[i] = tid % BK; am[i] = tid / BK + (NT / BK) * i; }
-        else           { am[i] = tid % BM; sa.kk[i] = tid / BM + (NT / BM) * i; }
+    for (int i = 0; i < LA; ++i) {  // elements i, i + 1 (i even): neighbouring k of one row
+        const int u = i / 2;
+        if (p.a_kfast) { sa.kk[i] = 2 * (tid % (BK / 2)) + i % 2; am[i] = tid / (BK / 2) + (2 * NT / BK) * u; }
+        else           { am[i] = tid % BM; sa.kk[i] = 2 * (tid / BM + (NT / BM) * u) + i % 2; }
         const int m = m0 + am[i];
         sa.ro[i] = (m < p.M) ? p.a_moff[m] : -1;
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
-        if (p.b_kfast) { sb.kk[i] = tid % BK; bn[i] = tid / BK + (NT / BK) * i; }
-        else           { bn[i] = tid % BN; sb.kk[i] = tid / BN + (NT / BN) * i; }
+        const int u = i / 2;
+        if (p.b_kfast) { sb.kk[i] = 2 * (tid % (BK / 2)) + i % 2; bn[i] = tid / (BK / 2) + (2 * NT / BK) * u; }
+        else           { bn[i] = tid % BN; sb.kk[i] = 2 * (tid / BN + (NT / BN) * u) + i % 2; }
         const int n = n0 + bn[i];
         sb.ro[i] = (n < p.N) ? p.b_noff[n] : -1;
     }
@@ -535,20 +538,26 @@ gett_bf16_direct(GettArgs p) {
         };
         auto lstore = [&](int st) {
 #pragma unroll
-            for (int i = 0; i < LA; ++i) {
-                unsigned short hr[NP], hi[NP];
-                split_bf16<NP>(ra[i].x, hr);
-                split_bf16<NP>(sgnA * ra[i].y, hi);
+            for (int i = 0; i < LA; i += 2) {
+                uint32_t hr[NP], hi[NP];
+                split_bf16<NP>(ra[i].x, ra[i + 1].x, hr);
+                split_bf16<NP>(sgnA * ra[i].y, sgnA * ra[i + 1].y, hi);
 #pragma unroll
-                for (int q = 0; q < NP; ++q) { sA[st][0][q][am[i]][sa.kk[i]] = hr[q]; sA[st][1][q][am[i]][sa.kk[i]] = hi[q]; }
+                for (int q = 0; q < NP; ++q) {
+                    *reinterpret_cast<uint32_t *>(&sA[st][0][q][am[i]][sa.kk[i]]) = hr[q];
+                    *reinterpret_cast<uint32_t *>(&sA[st][1][q][am[i]][sa.kk[i]]) = hi[q];
+                }
             }
 #pragma unroll
-            for (int i = 0; i < LB; ++i) {
-                unsigned short hr[NP], hi[NP];
-                split_bf16<NP>(rb[i].x, hr);
-                split_bf16<NP>(sgnB * rb[i].y, hi);
+            for (int i = 0; i < LB; i += 2) {
+                uint32_t hr[NP], hi[NP];
+                split_bf16<NP>(rb[i].x, rb[i + 1].x, hr);
+                split_bf16<NP>(sgnB * rb[i].y, sgnB * rb[i + 1].y, hi);
 #pragma unroll
-                for (int q = 0; q < NP; ++q) { sB[st][0][q][bn[i]][sb.kk[i]] = hr[q]; sB[st][1][q][bn[i]][sb.kk[i]] = hi[q]; }
+                for (int q = 0; q < NP; ++q) {
+                    *reinterpret_cast<uint32_t *>(&sB[st][0][q][bn[i]][sb.kk[i]]) = hr[q];
+                    *reinterpret_cast<uint32_t *>(&sB[st][1][q][bn[i]][sb.kk[i]]) = hi[q];
+                }
             }
         };
         // the previous batch item's last step may still read stage 0; the first
@@ -639,11 +648,21 @@ gett_bf16_direct(GettArgs p) {
 // bf16 parts, stored as planes out[b][part][re/im][row][kpad], K contiguous and
 // zero past K.  Done once per contraction, so the GEMM's inner loop reads ready
 // bf16 fragments with 16-byte loads instead of splitting every tile it stages.
+// HBM-bound.  In a masked launch the rows of skipped items are left out, and
+// everything where every item is skipped (pm: see PackMask).
 template <int NP>
 __global__ void __launch_bounds__(256) k_pack_bf16(const float2 *X, const int64_t *boff, const int32_t *roff,
                                                    const int32_t *koff, int kaff, int ks, int rows, int K, int kpad,
-                                                   int conj, unsigned short *out) {
+                                                   int conj, unsigned short *out, PackMask pm) {
     const int b = blockIdx.y;
+    if (pm.mask) {
+        if (pm.mode == 1 && pm.mask[b / pm.div] == pm.skip) return;
+        if (pm.mode == 3) {
+            int on = 0;
+            for (int i = threadIdx.x; i < pm.items; i += 256) on |= pm.mask[i] != pm.skip;
+            if (!__syncthreads_or(on)) return;
+        }
+    }
     const int kc = kpad / 8;
     const int64_t plane = (int64_t)rows * kpad;
     const float2 *Xb = X + boff[b];
@@ -651,23 +670,28 @@ __global__ void __launch_bounds__(256) k_pack_bf16(const float2 *X, const int64_
     const float sg = conj ? -1.f : 1.f;
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < (int64_t)rows * kc; e += (int64_t)gridDim.x * 256) {
         const int row = (int)(e / kc), k8 = (int)(e - (int64_t)row * kc) * 8;
+        if (pm.mask && pm.mode == 2 && pm.mask[row / pm.div] == pm.skip) continue;
         const float2 *xr = Xb + roff[row];
-        v8s pr[NP], pi[NP];
+        v4u pr[NP], pi[NP];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = k8 + j;
-            float2 v = make_float2(0.f, 0.f);
-            if (k < K) v = xr[kaff ? (int64_t)k * ks : (int64_t)koff[k]];
-            unsigned short hr[NP], hi[NP];
-            split_bf16<NP>(v.x, hr);
-            split_bf16<NP>(sg * v.y, hi);
+        for (int j = 0; j < 4; ++j) {
+            float2 v[2];
 #pragma unroll
-            for (int q = 0; q < NP; ++q) { pr[q][j] = (short)hr[q]; pi[q][j] = (short)hi[q]; }
+            for (int i = 0; i < 2; ++i) {
+                const int k = k8 + 2 * j + i;
+                v[i] = make_float2(0.f, 0.f);
+                if (k < K) v[i] = xr[kaff ? (int64_t)k * ks : (int64_t)koff[k]];
+            }
+            uint32_t hr[NP], hi[NP];
+            split_bf16<NP>(v[0].x, v[1].x, hr);
+            split_bf16<NP>(sg * v[0].y, sg * v[1].y, hi);
+#pragma unroll
+            for (int q = 0; q < NP; ++q) { pr[q][j] = hr[q]; pi[q][j] = hi[q]; }
         }
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-            *reinterpret_cast<v8s *>(Ob + (int64_t)(2 * q) * plane + (int64_t)row * kpad + k8) = pr[q];
-            *reinterpret_cast<v8s *>(Ob + (int64_t)(2 * q + 1) * plane + (int64_t)row * kpad + k8) = pi[q];
+            *reinterpret_cast<v4u *>(Ob + (int64_t)(2 * q) * plane + (int64_t)row * kpad + k8) = pr[q];
+            *reinterpret_cast<v4u *>(Ob + (int64_t)(2 * q + 1) * plane + (int64_t)row * kpad + k8) = pi[q];
         }
     }
 }
@@ -916,7 +940,7 @@ hipError_t launch_reduce(const GettArgs &a, hipStream_t s) {
 
 hipError_t launch_pack_bf16(int np, const void *X, const int64_t *boff, const int32_t *roff, const int32_t *koff,
                             int kaff, int ks, int rows, int K, int kpad, int batch, int conj, void *out,
-                            hipStream_t s) {
+                            const PackMask &pm, hipStream_t s) {
     if (rows <= 0 || batch <= 0) return hipSuccess;
     const int64_t work = (int64_t)rows * (kpad / 8);
     int64_t g = (work + 255) / 256;
@@ -927,10 +951,10 @@ hipError_t launch_pack_bf16(int np, const void *X, const int64_t *boff, const in
     auto o = reinterpret_cast<unsigned short *>(out);
     if (np == 2)
         hipLaunchKernelGGL(k_pack_bf16<2>, dim3((unsigned)g, gy), dim3(256), 0, s, x, boff, roff, koff, kaff, ks, rows,
-                           K, kpad, conj, o);
+                           K, kpad, conj, o, pm);
     else
         hipLaunchKernelGGL(k_pack_bf16<3>, dim3((unsigned)g, gy), dim3(256), 0, s, x, boff, roff, koff, kaff, ks, rows,
-                           K, kpad, conj, o);
+                           K, kpad, conj, o, pm);
     return hipGetLastError();
 }
 

@@ -82,9 +82,16 @@ hipError_t launch_gett(const GettArgs &a, int prec, int cfg, hipStream_t s);
 // Split-BF16 operand packing: element (row, k) of batch item b at
 // X + boff[b] + roff[row] + (kaff ? k * ks : koff[k]) (complex64), conjugated if
 // conj, split into np bf16 parts -> out[b][part][re/im][row][kpad] (zero past K).
+// pm (masked launches): what no tile will read may be left out -- batch items b
+// with mask[b / div] == skip (mode 1), rows with mask[row / div] == skip (mode 2), all
+// if every one of the `items` entries is skip (mode 3).
+struct PackMask {
+    const int *mask;
+    int mode, div, skip, items;
+};
 hipError_t launch_pack_bf16(int np, const void *X, const int64_t *boff, const int32_t *roff, const int32_t *koff,
                             int kaff, int ks, int rows, int K, int kpad, int batch, int conj, void *out,
-                            hipStream_t s);
+                            const PackMask &pm, hipStream_t s);
 void gett_tile(int cfg, int prec, int *bm, int *bn);
 
 // ---------------------------------------------------------------- linear algebra

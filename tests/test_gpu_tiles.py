@@ -75,3 +75,25 @@ def test_planned_mask(handle, prec, rows, K):
         assert bool((C[~on.cuda()] == 5.0).all())
     else:
         assert float(err.max()) < TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "bf16x6"])
+@pytest.mark.parametrize("eq", ["zak,zkc,zac", "zak,kc,zac", "ak,zkc,azc", "zqak,zqkc,zqac"])
+@pytest.mark.parametrize("kept", ["some", "none"])
+def test_packed_mask(handle, prec, eq, kept):
+    """What the packing of a masked launch leaves out is never read: kept items
+    are right, skipped ones as they were (packed operands; K leaves a remainder)."""
+    import torch
+    ia, ib, ic = eq.split(",")
+    dim = dict(z=6, q=2, a=320, c=320, k=200)
+    g = torch.Generator(device="cuda").manual_seed(len(eq))
+    A, B = (torch.randn([dim[l] for l in i], generator=g, dtype=torch.complex64, device="cuda") for i in (ia, ib))
+    C = torch.full([dim[l] for l in ic], 5.0, dtype=torch.complex64, device="cuda")
+    on = torch.tensor([1, 0, 1, 1, 0, 0] if kept == "some" else [0] * 6).bool()
+    handle.test_contract(prec, ia, A, ib, B, ic, C, mask=on.to(torch.int32).cuda(), cfg=0)
+    a, b = A.to(torch.complex128).cpu(), B.to(torch.complex128).cpu()
+    err = (C.to(torch.complex128).cpu() - torch.einsum(f"{ia},{ib}->{ic}", a, b)).abs()
+    err = (err / torch.einsum(f"{ia},{ib}->{ic}", a.abs(), b.abs())).movedim(ic.index("z"), 0)
+    got = C.cpu().movedim(ic.index("z"), 0)
+    assert bool((got[~on] == 5.0).all())
+    assert kept == "none" or float(err[on].max()) < TOL[prec]
