@@ -574,11 +574,19 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
 //   4096: 546 / 578 / 723).
 //   Split-BF16, split while staging: 128x64 on 8 waves (1048576 x 64 x 64: 489 for 805),
 //   64x128 where there are fewer than 128 rows.
-// A small one is bound by the walk along K of its few workgroups: 32x32 tiles (or
-// 64x16, as fast and wider in M, for a short K) and slices of K down to 32 until
-// the CUs are covered, from K = 192 on (a second kernel adds the slices, 5 us).
-// 32 x 512 x 512: 13 against 26 for 64x64 in 4 slices; 64 x 4096 x 64: 9 for 15;
-// 243 x 27 x 729: 13 for 29.
+// A small one is bound by the walk along K of its few workgroups.  In FP64 and FP32
+// up to 512 16x16 tiles (two a CU), and any number for a vector (N = 1) or up to 16
+// rows, whose other tiles would be padding, go to the kernel whose waves share K: 256
+// x 256 x 256: 6.8 against 11.8 for 32x32 in 4 slices, 2187 x 9 x 81: 4.3 / 8.2, 32 x
+// 512 x 512: 9.0 / 12.3 in 8; 4 x 128 x 2 x 1000: 21 / 26 for 64x64; 4096 x 1 x 4096:
+// 50 / 199; 512 x 256 x 512 (512 tiles): 17 / 21.  With 1024 tiles it loses (512 x
+// 512 x 32: 7.1 / 6.5, 512 x 512 x 256: 21 / 17, 32768 x 8 x 128: 28 / 17), and with
+// more than 256 of a large problem (32 x 4096 x 4096: 98 / 87).  It cuts K from 768 on,
+// into slices of at least 256 (16 x 256 x 1024: 10.0 in 4 for 14.5; 64 x 64 x 4096:
+// 14 in 16 for 23 with 32x32).
+// Between that and a large one: 32x32 tiles (or 64x16, as fast and wider in M, for a
+// short K) and slices of K down to 32 until the CUs are covered, from K = 192 on (a
+// second kernel adds the slices, 4 us).  64 x 4096 x 64: 8 for 16 with 64x64.
 // In the split modes a short K leaves nothing to amortise the splitting over: the
 // FP32 kernel with four products, up to K = 32 for bf16x6 and 64 for bf16x3, where
 // its error is no larger (against 64 bits, K = 32 and below: at most 1.03e-7
@@ -600,6 +608,12 @@ void Engine::choose_tile(Plan *P) {
     const bool large = t64 >= 256 || t64 * (K / 256) >= 256;
     int cfg;
     int64_t ks = 1;
+    const int64_t t16 = tiles(tnk::CFG_16x16);
+    if (!split && (t16 <= (large ? 256 : 512) || M <= 16 || N == 1)) {
+        if (t16 < 256 && K >= 768) ks = std::min<int64_t>(256 / t16, K / 256);
+        set_split(P, tnk::CFG_16x16, (int)ks);
+        return;
+    }
     if (N <= 16) {
         cfg = tnk::CFG_64x16;
     } else if (!large) {
@@ -673,8 +687,8 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
     struct Cand { int cfg, ks; bool pack; int fp32; };
     std::vector<Cand> cands;
     const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
-    const int cfgs[7] = {tnk::CFG_64x16,   tnk::CFG_64x64,    tnk::CFG_128x64,  tnk::CFG_128x64W,
-                         tnk::CFG_128x128W, tnk::CFG_32x32,    tnk::CFG_64x128W};
+    const int cfgs[8] = {tnk::CFG_64x16,    tnk::CFG_64x64, tnk::CFG_128x64,   tnk::CFG_128x64W,
+                         tnk::CFG_128x128W, tnk::CFG_32x32, tnk::CFG_64x128W, tnk::CFG_16x16};
     for (int pk = 0; pk < 3; ++pk) {
         const bool pack = pk == 1;
         const int f32 = pk == 2 ? 1 : 0;
@@ -684,6 +698,7 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             if ((c == tnk::CFG_128x64 || c == tnk::CFG_128x64W || c == tnk::CFG_128x128W) && P->kM < 128) continue;
             if (c == tnk::CFG_128x128W && (!pack || P->kN < 128)) continue;  // packed split-BF16 only
             if (c == tnk::CFG_64x16 && P->kN > 64) continue;
+            if (c == tnk::CFG_16x16 && bf16 && !f32) continue;  // FP64 / FP32 only
             if (c == tnk::CFG_64x128W && (!bf16 || f32 || P->kN < 128)) continue;  // split-BF16 only
             int bm = 64, bn = 64;
             tnk::gett_tile(c, prec, &bm, &bn);
@@ -938,6 +953,8 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         kprec = prec;
         if (force_cfg == tnk::CFG_128x128W && !pack)
             throw TnError(ST_UNSUPPORTED, "the 128x128 tile serves packed split-BF16 operands only");
+        if (force_cfg == tnk::CFG_16x16 && bf16)
+            throw TnError(ST_UNSUPPORTED, "the 16x16 tile serves FP64 and FP32 only");
         Plan tmp = *P;  // shares the tables, owns nothing
         tmp.pack = pack;
         set_split(&tmp, force_cfg, force_ksplit);
@@ -970,7 +987,9 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
                 // a tile must not straddle two items: a smaller one where the
                 // plan's does, else every item is computed
                 bool fits = false;
-                for (int c : {cfg, (int)tnk::CFG_64x64, (int)tnk::CFG_32x32}) {
+                const bool split = kprec == tnk::P_BF16X3 || kprec == tnk::P_BF16X6;
+                for (int c : {cfg, (int)tnk::CFG_64x64, (int)tnk::CFG_32x32, (int)tnk::CFG_16x16}) {
+                    if (c == tnk::CFG_16x16 && split) break;
                     int bm = 64, bn = 64;
                     tnk::gett_tile(c, kprec, &bm, &bn);
                     if (d % (mode == 2 ? bm : bn)) {

@@ -106,11 +106,37 @@ struct Stager {
         const int ko = kt ? kt[kc - kbeg] : kc * ks;
         return ok ? (uint32_t)(ro[i] + ko) * (uint32_t)esz : OOB;
     }
+    // all L offsets, with one (uniform) branch on the kind of the k offsets
+    __device__ inline void offs(uint32_t *o, int k0, int esz) const {
+        int ko[L];
+        if (kt) {
+#pragma unroll
+            for (int i = 0; i < L; ++i) ko[i] = kt[min(k0 + kk[i], kend - 1) - kbeg];
+        } else {
+#pragma unroll
+            for (int i = 0; i < L; ++i) ko[i] = min(k0 + kk[i], kend - 1) * ks;
+        }
+#pragma unroll
+        for (int i = 0; i < L; ++i)
+            o[i] = ro[i] >= 0 && k0 + kk[i] < kend ? (uint32_t)(ro[i] + ko[i]) * (uint32_t)esz : OOB;
+    }
 };
 
-// Copies the block's K slice of a k table into LDS.
+// Copies the block's K slice of one k table, or of two at once (either may be
+// absent), into LDS.
 __device__ inline void stage_ktab(int *dst, const int32_t *tab, int kbeg, int klen, int tid, int nt) {
     for (int k = tid; k < klen; k += nt) dst[k] = tab[kbeg + k];
+}
+
+__device__ inline void stage_ktabs(int *da, const int32_t *ta, int *db, const int32_t *tb, int kbeg, int klen,
+                                   int tid, int nt) {
+    for (int k = tid; k < klen; k += nt) {
+        int a = 0, b = 0;
+        if (da) a = ta[kbeg + k];
+        if (db) b = tb[kbeg + k];
+        if (da) da[k] = a;
+        if (db) db[k] = b;
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -119,8 +145,11 @@ __device__ inline void stage_ktab(int *dst, const int32_t *tab, int kbeg, int kl
 // sums formed in registers after the LDS reads.  3M saves a quarter of the
 // MFMA work; its imaginary part, P3 - P1 - P2, carries about twice the
 // rounding error of 4M relative to sum |a||b|.
-// Two LDS stages: the tile for step k+1 is loaded from HBM into registers while
-// step k computes, then stored to the other stage; one barrier per step.
+// Two LDS stages, and D steps in flight in registers: while step k computes, the
+// loads of steps k+1 .. k+D are under way, then k+1 is stored to the other stage;
+// one barrier per step.  D = 2 for the 64x16 tile, bound by HBM on its long thin
+// problems (4194304 x 32 x 16 in FP64: 1120 us with D = 1, 993 with 2, 1404 with 4,
+// whose registers leave two waves a SIMD); the wider tiles have none to spare.
 template <typename T, int BM, int BN, int BK> struct GettTiles {
     T a[2][2][BK][BM + 2];  // [stage][re/im][k][m]
     T b[2][2][BK][BN + 2];
@@ -128,7 +157,7 @@ template <typename T, int BM, int BN, int BK> struct GettTiles {
 
 // One BM x BN tile of problem p over its K slice kz, for the batch items b0,
 // b0 + bstep, ...
-template <typename T, int BM, int BN, int BK, int WGM, int WGN, bool G3>
+template <typename T, int BM, int BN, int BK, int D, int WGM, int WGN, bool G3>
 __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, int bstep, int kz,
                                            GettTiles<T, BM, BN, BK> &sm, int *ktab) {
     using C2 = typename Tr<T>::C2;
@@ -150,6 +179,9 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
     const int kbeg = kz * p.kchunk;
     const int kend = min(p.K, kbeg + p.kchunk);
 
+    // everything that the first operand loads wait for is asked for at once
+    if (b0 >= p.batch) return;
+    int64_t oA = p.a_boff[b0], oB = p.b_boff[b0], oC = p.c_boff[b0];
     int am[LA], bn[LB];
     Stager<LA> sa;
     Stager<LB> sb;
@@ -158,22 +190,24 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
         if (p.a_kfast) { sa.kk[i] = tid % BK; am[i] = tid / BK + (NT / BK) * i; }
         else           { am[i] = tid % BM; sa.kk[i] = tid / BM + (NT / BM) * i; }
         const int m = m0 + am[i];
-        sa.ro[i] = (m < p.M) ? p.a_moff[m] : -1;
+        sa.ro[i] = p.a_moff[min(m, p.M - 1)];
+        if (m >= p.M) sa.ro[i] = -1;
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
         if (p.b_kfast) { sb.kk[i] = tid % BK; bn[i] = tid / BK + (NT / BK) * i; }
         else           { bn[i] = tid % BN; sb.kk[i] = tid / BN + (NT / BN) * i; }
         const int n = n0 + bn[i];
-        sb.ro[i] = (n < p.N) ? p.b_noff[n] : -1;
+        sb.ro[i] = p.b_noff[min(n, p.N - 1)];
+        if (n >= p.N) sb.ro[i] = -1;
     }
     sa.ks = p.a_ks; sb.ks = p.b_ks;
     sa.kbeg = sb.kbeg = kbeg;
     sa.kend = sb.kend = kend;
     sa.kt = p.a_kaff ? nullptr : ktab;
     sb.kt = p.b_kaff ? nullptr : ktab + (p.a_kaff ? 0 : p.kchunk);
-    if (!p.a_kaff) stage_ktab(ktab, p.a_koff, kbeg, kend - kbeg, tid, NT);
-    if (!p.b_kaff) stage_ktab(const_cast<int *>(sb.kt), p.b_koff, kbeg, kend - kbeg, tid, NT);
+    stage_ktabs(p.a_kaff ? nullptr : ktab, p.a_koff, p.b_kaff ? nullptr : const_cast<int *>(sb.kt), p.b_koff, kbeg,
+                kend - kbeg, tid, NT);
 
     const int wave = tid >> 6, lane = tid & 63;
     const int wm = wave / WGN, wn = wave % WGN;
@@ -182,9 +216,10 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
 
     for (int b = b0; b < p.batch; b += bstep) {
         if (gett_skip(p, b, m0, n0)) continue;
-        const __amdgpu_buffer_rsrc_t rA = make_rsrc(reinterpret_cast<const C2 *>(p.A) + p.a_boff[b], p.a_bytes);
-        const __amdgpu_buffer_rsrc_t rB = make_rsrc(reinterpret_cast<const C2 *>(p.B) + p.b_boff[b], p.b_bytes);
-        C2 *Cb = reinterpret_cast<C2 *>(p.C) + p.c_boff[b];
+        if (b != b0) { oA = p.a_boff[b]; oB = p.b_boff[b]; oC = p.c_boff[b]; }
+        const __amdgpu_buffer_rsrc_t rA = make_rsrc(reinterpret_cast<const C2 *>(p.A) + oA, p.a_bytes);
+        const __amdgpu_buffer_rsrc_t rB = make_rsrc(reinterpret_cast<const C2 *>(p.B) + oB, p.b_bytes);
+        C2 *Cb = reinterpret_cast<C2 *>(p.C) + oC;
 
         // 4M: accR, accI.  3M (G3): accR = sum aR bR, accI = sum aI bI,
         // acc3 = sum (aR + aI)(bR + bI); Re = accR - accI, Im = acc3 - accR - accI.
@@ -204,40 +239,47 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
                     for (int r = 0; r < 4; ++r) acc3[i][j][r] = T(0);
         }
 
-        C2 ra[LA], rb[LB];
-        auto gload = [&](int k0) {
+        C2 ra[D][LA], rb[D][LB];
+        auto gload = [&](int d, int k0) {  // (past kend: no memory is read, zeros come back)
             uint32_t oa[LA], ob[LB];
+            sa.offs(oa, k0, ESZ);
+            sb.offs(ob, k0, ESZ);
 #pragma unroll
-            for (int i = 0; i < LA; ++i) oa[i] = sa.off(i, k0, ESZ);
+            for (int i = 0; i < LA; ++i) ra[d][i] = bload<C2>(rA, oa[i]);
 #pragma unroll
-            for (int i = 0; i < LB; ++i) ob[i] = sb.off(i, k0, ESZ);
-#pragma unroll
-            for (int i = 0; i < LA; ++i) ra[i] = bload<C2>(rA, oa[i]);
-#pragma unroll
-            for (int i = 0; i < LB; ++i) rb[i] = bload<C2>(rB, ob[i]);
+            for (int i = 0; i < LB; ++i) rb[d][i] = bload<C2>(rB, ob[i]);
         };
-        auto lstore = [&](int st) {
+        auto lstore = [&](int d, int st) {
 #pragma unroll
             for (int i = 0; i < LA; ++i) {
-                sA[st][0][sa.kk[i]][am[i]] = ra[i].x;
-                sA[st][1][sa.kk[i]][am[i]] = sgnA * ra[i].y;
+                sA[st][0][sa.kk[i]][am[i]] = ra[d][i].x;
+                sA[st][1][sa.kk[i]][am[i]] = sgnA * ra[d][i].y;
             }
 #pragma unroll
             for (int i = 0; i < LB; ++i) {
-                sB[st][0][sb.kk[i]][bn[i]] = rb[i].x;
-                sB[st][1][sb.kk[i]][bn[i]] = sgnB * rb[i].y;
+                sB[st][0][sb.kk[i]][bn[i]] = rb[d][i].x;
+                sB[st][1][sb.kk[i]][bn[i]] = sgnB * rb[d][i].y;
             }
         };
         // the previous batch item's last step may still read stage 0; the first
         // pass also publishes the LDS k tables
         __syncthreads();
-        gload(kbeg);
-        lstore(0);
+#pragma unroll
+        for (int d = 0; d < D; ++d) gload(d, kbeg + d * BK);
+        // the offsets of the results arrive meanwhile (one 16x16 tile per wave)
+        int cm[4], cn0 = 0;
+        if constexpr (FM * FN == 1) {
+            if (p.ksplit <= 1) {
+                cn0 = p.c_noff[min(n0 + wn * WTN + (lane & 15), p.N - 1)];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) cm[r] = p.c_moff[min(m0 + wm * WTM + Tr<T>::row(lane, r), p.M - 1)];
+            }
+        }
+        lstore(0, 0);
         __syncthreads();
-        int st = 0;
-        for (int k0 = kbeg; k0 < kend; k0 += BK, st ^= 1) {
+        auto step = [&](int d, int st, int k0) {
             const bool more = k0 + BK < kend;
-            if (more) gload(k0 + BK);
+            if (D > 1 || more) gload(d, k0 + D * BK);
 #pragma unroll
             for (int kq = 0; kq < BK / 4; ++kq) {
                 const int kr = kq * 4 + (lane >> 4);
@@ -288,8 +330,19 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
             if (more) {
                 // the other stage was last read in the previous step, before the
                 // barrier that ended it
-                lstore(st ^ 1);
+                lstore((d + 1) % D, st ^ 1);
                 __syncthreads();
+            }
+        };
+        if constexpr (D == 1) {
+            int st = 0;
+            for (int k0 = kbeg; k0 < kend; k0 += BK, st ^= 1) step(0, st, k0);
+        } else {
+            static_assert(D % 2 == 0, "the register slot and the stage are constants in each copy of the step");
+            for (int k0 = kbeg; k0 < kend; k0 += D * BK) {
+#pragma unroll
+                for (int u = 0; u < D; ++u)
+                    if (k0 + u * BK < kend) step(u, u % 2, k0 + u * BK);
             }
         }
         // epilogue: see Tr<T>::row for the accumulator layout
@@ -300,7 +353,7 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
         for (int j = 0; j < FN; ++j) {
             const int n = n0 + wn * WTN + j * 16 + (lane & 15);
             if (n >= p.N) continue;
-            const int64_t cn = Pb ? 0 : p.c_noff[n];
+            const int64_t cn = Pb ? 0 : FM * FN == 1 ? cn0 : p.c_noff[n];
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -319,7 +372,7 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
                         Pb[(int64_t)m * p.N + n] = v;
                         continue;
                     }
-                    C2 *dst = Cb + p.c_moff[m] + cn;
+                    C2 *dst = Cb + (FM * FN == 1 ? cm[r] : p.c_moff[m]) + cn;
                     if (p.accumulate) { const C2 o = *dst; v.x += o.x; v.y += o.y; }
                     *dst = v;
                 }
@@ -327,8 +380,8 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
     }
 }
 
-template <typename T, int BM, int BN, int BK, int WGM, int WGN, bool G3>
-__global__ void __launch_bounds__(64 * WGM * WGN, 2)
+template <typename T, int BM, int BN, int BK, int D, int WGM, int WGN, bool G3, int OCC = 2>
+__global__ void __launch_bounds__(64 * WGM * WGN, OCC)
 gett_mfma(GettArgs p) {
     __shared__ GettTiles<T, BM, BN, BK> sm;
     extern __shared__ int ktab[];   // non-affine k tables of the block's K slice
@@ -337,7 +390,108 @@ gett_mfma(GettArgs p) {
     // one sample would sit on one or two XCDs and the others would idle
     const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
     const int tile = p.mask ? (int)blockIdx.x : xcd_remap(blockIdx.x, tiles);
-    gett_block<T, BM, BN, BK, WGM, WGN, G3>(p, tile, blockIdx.y, gridDim.y, blockIdx.z, sm, ktab);
+    gett_block<T, BM, BN, BK, D, WGM, WGN, G3>(p, tile, blockIdx.y, gridDim.y, blockIdx.z, sm, ktab);
+}
+
+// A 16x16 tile whose W waves take a share of the K slice each, operands loaded
+// straight into the registers that the matrix instruction reads (a quad of k by 16
+// rows is one 16-byte load per lane), the partial results added through LDS in wave
+// order.  For problems of few tiles, which are bound by latency: a wave's chain is
+// K / (4 W) matrix steps of 200 cycles, where a tile staged through LDS walks all of K
+// at 2100 cycles per 16 (loads, store, barrier and 768 of matrix work in turn).  In
+// FP64, before and after: 8 x 8 x 8 4.0 and 2.5 us; 2187 x 9 x 81 8.2 and 4.3; 32 x 512
+// x 512 12.3 with its second launch and 9.0; 1 x 4096 x 4096 82 and 47 (5.7 TB/s).
+// U = 8 quads in flight per wave; 16 waves a tile leave 128 registers and spill (32 x
+// 512 x 512 12.9 us).
+template <typename T, int W, bool G3>
+__global__ void __launch_bounds__(64 * W)
+gett_wave(GettArgs p) {
+    using C2 = typename Tr<T>::C2;
+    using Acc = typename Tr<T>::Acc;
+    constexpr int U = 8;  // quads of k in flight
+    constexpr uint32_t ESZ = sizeof(C2);
+    __shared__ C2 sums[W][256];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tiles_n = (p.N + 15) / 16;
+    const int m0 = (int)(blockIdx.x / (unsigned)tiles_n) * 16, n0 = (int)(blockIdx.x % (unsigned)tiles_n) * 16;
+    const int kbeg = blockIdx.z * p.kchunk, kend = min(p.K, kbeg + p.kchunk);
+    const int share = ((kend - kbeg + 4 * W - 1) / (4 * W)) * 4;  // whole quads
+    const int kw = kbeg + wave * share, kwe = min(kend, kw + share);
+    const int m = m0 + (lane & 15), n = n0 + (lane & 15);
+    const int mo = m0 + ((tid & 255) >> 4), no = n0 + (tid & 15);  // this thread's result
+    const bool direct = p.ksplit <= 1;
+    int64_t oA = p.a_boff[blockIdx.y], oB = p.b_boff[blockIdx.y], oC = p.c_boff[blockIdx.y];
+    const int am = p.a_moff[min(m, p.M - 1)], bn = p.b_noff[min(n, p.N - 1)];
+    int cm = 0, cn = 0;
+    if (direct) {
+        cm = p.c_moff[min(mo, p.M - 1)];
+        cn = p.c_noff[min(no, p.N - 1)];
+    }
+    const T sgnA = p.conjA ? T(-1) : T(1), sgnB = p.conjB ? T(-1) : T(1);
+    for (int b = blockIdx.y; b < p.batch; b += gridDim.y) {
+        if (b != (int)blockIdx.y) {
+            oA = p.a_boff[b]; oB = p.b_boff[b]; oC = p.c_boff[b];
+            __syncthreads();  // the sums of the last item have been read
+        }
+        if (gett_skip(p, b, m0, n0)) continue;
+        const __amdgpu_buffer_rsrc_t rA = make_rsrc(reinterpret_cast<const C2 *>(p.A) + oA, p.a_bytes);
+        const __amdgpu_buffer_rsrc_t rB = make_rsrc(reinterpret_cast<const C2 *>(p.B) + oB, p.b_bytes);
+        Acc aR = {0, 0, 0, 0}, aI = {0, 0, 0, 0}, a3 = {0, 0, 0, 0}, a4 = {0, 0, 0, 0};
+        for (int k0 = kw; k0 < kwe; k0 += 4 * U) {
+            C2 a[U], bb[U];
+            int ka[U], kb[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = min(k0 + 4 * u + (lane >> 4), kwe - 1);
+                ka[u] = k * p.a_ks;
+                kb[u] = k * p.b_ks;
+                if (!p.a_kaff) ka[u] = p.a_koff[k];
+                if (!p.b_kaff) kb[u] = p.b_koff[k];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (k0 + 4 * u >= kwe) break;
+                const bool ok = k0 + 4 * u + (lane >> 4) < kwe;
+                a[u] = bload<C2>(rA, ok && m < p.M ? (uint32_t)(am + ka[u]) * ESZ : OOB);
+                bb[u] = bload<C2>(rB, ok && n < p.N ? (uint32_t)(bn + kb[u]) * ESZ : OOB);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (k0 + 4 * u >= kwe) break;
+                const T ar = a[u].x, ai = sgnA * a[u].y, br = bb[u].x, bi = sgnB * bb[u].y;
+                aR = Tr<T>::mma(ar, br, aR);
+                aI = Tr<T>::mma(ai, bi, aI);
+                if constexpr (G3) {
+                    a3 = Tr<T>::mma(ar + ai, br + bi, a3);
+                } else {
+                    a3 = Tr<T>::mma(ar, bi, a3);
+                    a4 = Tr<T>::mma(ai, br, a4);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            C2 v;
+            v.x = aR[r] - aI[r];
+            v.y = G3 ? a3[r] - aR[r] - aI[r] : a3[r] + a4[r];
+            sums[wave][Tr<T>::row(lane, r) * 16 + (lane & 15)] = v;
+        }
+        __syncthreads();
+        if (tid >= 256 || mo >= p.M || no >= p.N) continue;
+        C2 v = sums[0][tid];
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+            v.x += sums[w][tid].x;
+            v.y += sums[w][tid].y;
+        }
+        if (!direct) {
+            reinterpret_cast<C2 *>(p.part)[((int64_t)blockIdx.z * p.batch + b) * (int64_t)p.M * p.N + (int64_t)mo * p.N + no] = v;
+            continue;
+        }
+        C2 *dst = reinterpret_cast<C2 *>(p.C) + oC + cm + cn;
+        if (p.accumulate) { const C2 o = *dst; v.x += o.x; v.y += o.y; }
+        *dst = v;
+    }
 }
 
 // Many independent problems in one launch: workgroup i computes the tile,
@@ -347,14 +501,14 @@ gett_mfma(GettArgs p) {
 // 8 us whatever its size, and a BP sweep has about a hundred.  Together they are
 // four to eight launches: tn_bp on the 12 x 12 brick at D = 8 went from 36 to 6.8
 // ms, a Trotter layer of the 129-qubit heavy-hex at D = 16 from 257 to 53 ms.
-template <typename T, int BM, int BN, int BK, int WGM, int WGN>
+template <typename T, int BM, int BN, int BK, int D, int WGM, int WGN>
 __global__ void __launch_bounds__(64 * WGM * WGN, 2)
 gett_group(const GettArgs *tab, const GroupBlock *blk) {
     __shared__ GettTiles<T, BM, BN, BK> sm;
     extern __shared__ int ktab[];
     const GroupBlock g = blk[blockIdx.x];
     const GettArgs p = tab[g.prob];
-    gett_block<T, BM, BN, BK, WGM, WGN, GAUSS3M>(p, g.tile, g.b, p.batch, g.kz, sm, ktab);
+    gett_block<T, BM, BN, BK, D, WGM, WGN, GAUSS3M>(p, g.tile, g.b, p.batch, g.kz, sm, ktab);
 }
 
 template <typename C2>
@@ -926,6 +1080,22 @@ hipError_t launch_k(K kernel, const GettArgs &a, int bm, int bn, int nt, hipStre
     return hipGetLastError();
 }
 
+template <typename T, bool G3>
+hipError_t launch_wave(const GettArgs &a, hipStream_t s) {
+    const int64_t tiles = (int64_t)((a.M + 15) / 16) * ((a.N + 15) / 16);
+    if (tiles > INT32_MAX) return hipErrorInvalidValue;
+    if (a.mask && a.mask_mode > 1 && a.mask_div % 16) return hipErrorInvalidValue;
+    const dim3 g((unsigned)tiles, a.batch < 65535 ? a.batch : 65535, a.ksplit > 1 ? a.ksplit : 1);
+    // 4 waves (less to sum and to place on a CU) for a K of at most one quad each, and
+    // while the tiles are more than the CUs, up to 64: 512 x 256 x 64 5.6 us for 6.4 with
+    // 8 waves, which serve 64 x 16 x 64 in 3.6 us for 4.2
+    const int k = std::min(a.K, a.kchunk);
+    if (k <= 16 || (k <= 64 && tiles * a.batch > 256))
+        hipLaunchKernelGGL((gett_wave<T, 4, G3>), g, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((gett_wave<T, 8, G3>), g, dim3(512), 0, s, a);
+    return hipGetLastError();
+}
+
 template <typename C2>
 hipError_t launch_reduce(const GettArgs &a, hipStream_t s) {
     if (a.ksplit <= 1) return hipSuccess;
@@ -967,6 +1137,7 @@ void gett_tile(int cfg, int prec, int *bm, int *bn) {
         case CFG_128x128W: *bm = 128; *bn = 128; break;
         case CFG_32x32: *bm = 32; *bn = 32; break;
         case CFG_64x128W: *bm = 64; *bn = 128; break;
+        case CFG_16x16: *bm = 16; *bn = 16; break;
         default: *bm = 64; *bn = 64; break;
     }
     (void)prec;
@@ -985,8 +1156,8 @@ hipError_t launch_gett_group(const GettArgs *tab, const GroupBlock *blk, int nbl
         return hipGetLastError();
     };
     switch (cfg) {
-        case CFG_64x64: return go(gett_group<double, 64, 64, 16, 2, 2>);
-        case CFG_64x16: return go(gett_group<double, 64, 16, 16, 4, 1>);
+        case CFG_64x64: return go(gett_group<double, 64, 64, 16, 1, 2, 2>);
+        case CFG_64x16: return go(gett_group<double, 64, 16, 16, 2, 4, 1>);
         case CFG_K1: return go(gett_group_k1);
         default: return hipErrorInvalidValue;
     }
@@ -1019,29 +1190,32 @@ hipError_t launch_gett(const GettArgs &a0, int prec, int cfg, hipStream_t s) {
 static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t s) {
     if (prec == P_FP64) {
         switch (cfg) {
-            case CFG_64x64: return launch_k(gett_mfma<double, 64, 64, 16, 2, 2, GAUSS3M>, a, 64, 64, 256, s);
-            case CFG_128x64: return launch_k(gett_mfma<double, 128, 64, 16, 2, 2, false>, a, 128, 64, 256, s);
-            case CFG_64x16: return launch_k(gett_mfma<double, 64, 16, 16, 4, 1, GAUSS3M>, a, 64, 16, 256, s);
-            case CFG_128x64W: return launch_k(gett_mfma<double, 128, 64, 16, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
-            case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
+            case CFG_64x64: return launch_k(gett_mfma<double, 64, 64, 16, 1, 2, 2, GAUSS3M>, a, 64, 64, 256, s);
+            case CFG_128x64: return launch_k(gett_mfma<double, 128, 64, 16, 1, 2, 2, false>, a, 128, 64, 256, s);
+            case CFG_64x16: return launch_k(gett_mfma<double, 64, 16, 16, 2, 4, 1, GAUSS3M>, a, 64, 16, 256, s);
+            case CFG_128x64W: return launch_k(gett_mfma<double, 128, 64, 16, 1, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
+            case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 1, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
+            case CFG_16x16: return launch_wave<double, GAUSS3M>(a, s);
             default: return hipErrorInvalidValue;
         }
     }
     if (prec == P_FP32) {
         switch (cfg) {
-            case CFG_64x64: return launch_k(gett_mfma<float, 64, 64, 16, 2, 2, GAUSS3M>, a, 64, 64, 256, s);
-            case CFG_128x64: return launch_k(gett_mfma<float, 128, 64, 16, 2, 2, false>, a, 128, 64, 256, s);
-            case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 4, 1, GAUSS3M>, a, 64, 16, 256, s);
-            case CFG_128x64W: return launch_k(gett_mfma<float, 128, 64, 16, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
-            case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
+            case CFG_64x64: return launch_k(gett_mfma<float, 64, 64, 16, 1, 2, 2, GAUSS3M>, a, 64, 64, 256, s);
+            case CFG_128x64: return launch_k(gett_mfma<float, 128, 64, 16, 1, 2, 2, false>, a, 128, 64, 256, s);
+            case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 2, 4, 1, GAUSS3M>, a, 64, 16, 256, s);
+            case CFG_128x64W: return launch_k(gett_mfma<float, 128, 64, 16, 1, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
+            case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 1, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
+            case CFG_16x16: return launch_wave<float, GAUSS3M>(a, s);
             default: return hipErrorInvalidValue;
         }
     }
     if (prec == P_FP32_4M) {
         switch (cfg) {
-            case CFG_64x64: return launch_k(gett_mfma<float, 64, 64, 16, 2, 2, false>, a, 64, 64, 256, s);
-            case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 4, 1, false>, a, 64, 16, 256, s);
-            case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 2, 2, false>, a, 32, 32, 256, s);
+            case CFG_64x64: return launch_k(gett_mfma<float, 64, 64, 16, 1, 2, 2, false>, a, 64, 64, 256, s);
+            case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 2, 4, 1, false>, a, 64, 16, 256, s);
+            case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 1, 2, 2, false>, a, 32, 32, 256, s);
+            case CFG_16x16: return launch_wave<float, false>(a, s);
             default: return hipErrorInvalidValue;
         }
     }

@@ -63,8 +63,9 @@ enum GettCfg : int {
     CFG_128x128W = 4, // 8 waves, 64x32 per wave (packed split-BF16 only)
     CFG_32x32 = 5,    // 4 waves, 16x16 per wave
     CFG_64x128W = 6,  // 8 waves, 32x32 per wave (split-BF16 only)
-    CFG_COUNT = 7,
-    CFG_K1 = 7        // an output per thread (grouped problems with K = 1 only)
+    CFG_16x16 = 7,    // 4 or 8 waves, K shared out over them (FP64 / FP32)
+    CFG_COUNT = 8,
+    CFG_K1 = 8        // an output per thread (grouped problems with K = 1 only)
 };
 
 // Grouped launches (FP64): independent problems of any shapes in one kernel.

@@ -97,3 +97,45 @@ def test_packed_mask(handle, prec, eq, kept):
     got = C.cpu().movedim(ic.index("z"), 0)
     assert bool((got[~on] == 5.0).all())
     assert kept == "none" or float(err[on].max()) < TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("M,N,K,Z", [(1, 1, 1, 1), (15, 17, 3, 2), (16, 16, 16, 3), (33, 16, 17, 300), (16, 40, 65, 1),
+                                     (17, 5, 129, 2), (40, 33, 257, 1), (1, 70, 2100, 1)])
+@pytest.mark.parametrize("ksplit", [1, 3])
+@pytest.mark.parametrize("eq", ["zmk,zkn,zmn", "zkm,znk,znm"])
+def test_wave_tile(handle, prec, M, N, K, Z, ksplit, eq):
+    """The 16x16 tile, whose waves share K: fewer k than waves, remainders of a
+    quad and of a batch of quads, either operand contiguous along k."""
+    import torch
+    td = torch.complex128 if prec == "fp64" else torch.complex64
+    dim = dict(z=Z, m=M, n=N, k=K)
+    ia, ib, ic = eq.split(",")
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    A, B = (torch.randn([dim[l] for l in i], generator=g, dtype=td, device="cuda") for i in (ia, ib))
+    C = torch.randn([dim[l] for l in ic], generator=g, dtype=td, device="cuda")
+    a, b, c = (x.to(torch.complex128).cpu() for x in (A, B, C))
+    handle.test_contract(prec, ia, A, ib, B, ic, C, conjB=True, accumulate=True, cfg=7, ksplit=ksplit)
+    ref = c + torch.einsum(f"{ia},{ib}->{ic}", a, b.conj().resolve_conj())
+    scale = c.abs() + torch.einsum(f"{ia},{ib}->{ic}", a.abs(), b.abs())
+    assert float(((C.to(torch.complex128).cpu() - ref).abs() / scale).max()) < TOL[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("ksplit", [1, 2])
+def test_wave_tile_tables(handle, prec, ksplit):
+    """K offsets that no stride gives, and a masked launch with items of 16 rows."""
+    import torch
+    td = torch.complex128 if prec == "fp64" else torch.complex64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn((12, 7, 16, 13), generator=g, dtype=td, device="cuda")  # z j m l
+    B = torch.randn((13, 21, 7), generator=g, dtype=td, device="cuda")      # l n j
+    C = torch.full((12, 16, 21), 5.0, dtype=td, device="cuda")
+    mask = (torch.arange(12, device="cuda") % 3 != 1).to(torch.int32)
+    handle.test_contract(prec, "zjml", A, "lnj", B, "zmn", C, cfg=7, ksplit=ksplit, mask=mask)
+    a, b = A.to(torch.complex128).cpu(), B.to(torch.complex128).cpu()
+    err = (C.to(torch.complex128).cpu() - torch.einsum("zjml,lnj->zmn", a, b)).abs()
+    err = err / torch.einsum("zjml,lnj->zmn", a.abs(), b.abs())
+    on = mask.cpu().bool()
+    assert float(err[on].max()) < TOL[prec]
+    assert bool((C.cpu()[~on] == 5.0).all())
