@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 namespace tnk {
@@ -800,124 +801,194 @@ __device__ __forceinline__ void acc_store(const CAcc &c, CMat<LD> M, int r0, int
     }
 }
 
-// 1 / d for d > 0 in the normal range: the hardware estimate and two Newton steps.
-__device__ __forceinline__ double recip(double d) {
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(fma(-d, r, 1.0), r, r);
-    return fma(fma(-d, r, 1.0), r, r);
+// 1 / sqrt(d) for d > 0 in the normal range: the hardware estimate r and one step of
+// third order, r (1 + y / 2 + 3 y^2 / 8) with y = 1 - d r^2.
+__device__ __forceinline__ double rsqrt3(double d) {
+    const double r = __builtin_amdgcn_rsq(d);
+    const double y = fma(-d * r, r, 1.0);
+    return fma(r * y, fma(y, 0.375, 0.5), r);
 }
 // Lane K of each row of 16 lanes, to the whole row.
 template <int K> __device__ __forceinline__ double row_lane(double v) {
     const int2 a = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, a.x, 0x150 + K, 0xf, 0xf, false),
-                                                __builtin_amdgcn_update_dpp(0, a.y, 0x150 + K, 0xf, 0xf, false)));
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(a.x, 0x150 + K, 0xf, 0xf, false),
+                                                __builtin_amdgcn_mov_dpp(a.y, 0x150 + K, 0xf, 0xf, false)));
+}
+// out[a] = lane 16 a + x of v, in every lane (x = lane % 16): swaps of half waves,
+// then of rows of 16 lanes.
+__device__ __forceinline__ void rows4(double v, double (&out)[4]) {
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    const uint2 d = __builtin_bit_cast(uint2, v);
+    unsigned int o[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const unsigned int x = h ? d.y : d.x;
+        const v2u p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        const v2u a = __builtin_amdgcn_permlane16_swap(p.x, p.x, false, false);
+        const v2u b = __builtin_amdgcn_permlane16_swap(p.y, p.y, false, false);
+        o[h][0] = a.x; o[h][1] = a.y; o[h][2] = b.x; o[h][3] = b.y;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = __builtin_bit_cast(double, make_uint2(o[0][i], o[1][i]));
 }
 
-// One wave: the 16 x 16 Hermitian diagonal block at `o` of W becomes R (upper,
-// zero below) and that block of E its inverse.  Elimination on the pair [W | I]:
-// at pivot k every later row i takes row_i -= W[i][k] / W[k][k] row_k on both
-// halves, which leaves D^{1/2} R above the diagonal and D^{-1/2} R^{-H} on the
-// other side.  Lane l holds rows 4 r + l / 16 of column l % 16.  A pivot below
-// cl is raised to it (returns true).  Bound by the chain pivot -> reciprocal ->
-// next pivot.
-struct DiagState { double2 w[4], e[4]; double d[4]; };
-template <int K>
-__device__ __forceinline__ void diag_pivot(DiagState &s, double cl, bool &bad, int lane) {
-    constexpr int rk = K >> 2, qk = K & 3;
-    const int x = lane & 15, q = lane >> 4;
-    double d = lane_get(s.w[rk].x, qk * 16 + K);
+// One wave: a 16 x 16 Hermitian block w (in full) becomes R (upper) and e becomes
+// R^{-H} e: elimination on the pair [w | e] in panels of four rows.  Each lane
+// carries the panel's four rows of its column of both halves through the panel's own
+// elimination (the four pivots, one after another, in every lane alike); the rows
+// below take the rank-4 update as one matrix instruction per real product, whose
+// operands are the panel's rows as the accumulator layout holds them.  A pivot
+// below cl is raised to it (returns true).  Bound by the issue of one wave: some
+// 220 instructions and 8 matrix products a panel.
+template <int PN, int A>
+__device__ __forceinline__ void diag_pivot(double (&w)[2][4], double (&e)[2][4], double cl, bool &bad, int x) {
+    double d = row_lane<4 * PN + A>(w[0][A]);
     if (!(d >= cl)) {  // the same in every lane
         bad = true;
         d = cl > 0.0 ? cl : 1e-300;
     }
-    const double inv = recip(d);
-    s.d[rk] = q == qk ? d : s.d[rk];
-    const int src = qk * 16 + x;
-    const double2 pw = make_double2(__shfl(s.w[rk].x, src, 64), __shfl(s.w[rk].y, src, 64));
-    const double2 pe = make_double2(__shfl(s.e[rk].x, src, 64), __shfl(s.e[rk].y, src, 64));
-#pragma unroll
-    for (int r = rk; r < 4; ++r) {
-        const double t = 4 * r + q > K ? inv : 0.0;
-        const double ax = row_lane<K>(s.w[r].x) * t, ay = row_lane<K>(s.w[r].y) * t;
-        s.w[r].x = fma(-ax, pw.x, fma(ay, pw.y, s.w[r].x));
-        s.w[r].y = fma(-ax, pw.y, fma(-ay, pw.x, s.w[r].y));
-        s.e[r].x = fma(-ax, pe.x, fma(ay, pe.y, s.e[r].x));
-        s.e[r].y = fma(-ax, pe.y, fma(-ay, pe.x, s.e[r].y));
-    }
+    const double rs = rsqrt3(d);
+    w[0][A] = x == 4 * PN + A ? d * rs : w[0][A] * rs;
+    w[1][A] *= rs;
+    e[0][A] *= rs;
+    e[1][A] *= rs;
+    auto below = [&](auto bc) {
+        constexpr int B = decltype(bc)::value;
+        if constexpr (B < 4) {
+            const double cr = row_lane<4 * PN + (B & 3)>(w[0][A]), ci = row_lane<4 * PN + (B & 3)>(w[1][A]);
+            w[0][B] = fma(-cr, w[0][A], fma(-ci, w[1][A], w[0][B]));
+            w[1][B] = fma(-cr, w[1][A], fma(ci, w[0][A], w[1][B]));
+            e[0][B] = fma(-cr, e[0][A], fma(-ci, e[1][A], e[0][B]));
+            e[1][B] = fma(-cr, e[1][A], fma(ci, e[0][A], e[1][B]));
+        }
+    };
+    below(std::integral_constant<int, A + 1>());
+    below(std::integral_constant<int, A + 2>());
+    below(std::integral_constant<int, A + 3>());
 }
-template <int K>
-__device__ __forceinline__ void diag_pivots(DiagState &s, double cl, bool &bad, int lane) {
-    diag_pivot<K>(s, cl, bad, lane);
-    if constexpr (K < 15) diag_pivots<K + 1>(s, cl, bad, lane);
-}
-template <int LD>
-__device__ __forceinline__ bool diag_factor(CMat<LD> W, CMat<LD> E, int o, double cl, int lane) {
+template <int PN>
+__device__ __forceinline__ void diag_panel(CAcc &w, CAcc &e, CAcc &R, CAcc &F, double cl, bool &bad, int lane) {
     const int x = lane & 15, q = lane >> 4;
-    DiagState s;
+    double wp[2][4], ep[2][4];
+    rows4(w.re[PN], wp[0]);
+    rows4(w.im[PN], wp[1]);
+    rows4(e.re[PN], ep[0]);
+    rows4(e.im[PN], ep[1]);
+    diag_pivot<PN, 0>(wp, ep, cl, bad, x);
+    diag_pivot<PN, 1>(wp, ep, cl, bad, x);
+    diag_pivot<PN, 2>(wp, ep, cl, bad, x);
+    diag_pivot<PN, 3>(wp, ep, cl, bad, x);
+    auto own = [&](double a, double b, double c, double d) {
+        const double lo = q == 0 ? a : b, hi = q == 2 ? c : d;
+        return q < 2 ? lo : hi;
+    };
+    const double wr = own(wp[0][0], wp[0][1], wp[0][2], wp[0][3]), wi = own(wp[1][0], wp[1][1], wp[1][2], wp[1][3]);
+    const double er = own(ep[0][0], ep[0][1], ep[0][2], ep[0][3]), ei = own(ep[1][0], ep[1][1], ep[1][2], ep[1][3]);
+    R.re[PN] = wr; R.im[PN] = wi;
+    F.re[PN] = er; F.im[PN] = ei;
+    if constexpr (PN < 3) {  // (the rows of finished panels are overwritten with what is not read again)
+        acc_mma(w, -wr, wi, wr, wi);
+        __builtin_amdgcn_sched_barrier(0);  // the next panel waits for these four
+        acc_mma(e, -wr, wi, er, ei);
+        diag_panel<PN + 1>(w, e, R, F, cl, bad, lane);
+    }
+}
+template <int LD> __device__ __forceinline__ void acc_load(CAcc &c, CMat<LD> M, int r0, int c0, int lane) {
+    const int x = lane & 15, q = lane >> 4;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int i = 4 * r + q;
-        s.w[r] = make_double2(W.re[o + i][o + x], W.im[o + i][o + x]);
-        s.e[r] = make_double2(i == x ? 1.0 : 0.0, 0.0);
-        s.d[r] = 1.0;
+        c.re[r] = M.re[r0 + 4 * r + q][c0 + x];
+        c.im[r] = M.im[r0 + 4 * r + q][c0 + x];
     }
-    bool bad = false;
-    diag_pivots<0>(s, cl, bad, lane);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = 4 * r + q;
-        const double rs = 1.0 / sqrt(s.d[r]);
-        W.re[o + i][o + x] = x > i ? s.w[r].x * rs : x == i ? s.d[r] * rs : 0.0;
-        W.im[o + i][o + x] = x > i ? s.w[r].y * rs : 0.0;
-        E.re[o + x][o + i] = x <= i ? s.e[r].x * rs : 0.0;
-        E.im[o + x][o + i] = x <= i ? -s.e[r].y * rs : 0.0;
-    }
-    return bad;
 }
 
 // W (P x P blocks, the diagonal blocks Hermitian in full, the blocks above them
 // filled) = R^H R: R replaces W's upper part and E receives R^{-1} (upper blocks).
-// NW waves; returns whether a pivot was raised (wave 0).  Right-looking over
-// panels of 16: one wave factors the diagonal block, the others' work (the
-// panel's row of R, the trailing update, the inverse's off-diagonal blocks) is
-// matrix products spread over the waves.  E and W may be the same array for P <= 2.
-template <int P, int NW, int LD>
+// NW >= P waves; returns whether a pivot was raised (wave 0).  Right-looking over
+// panels of 16: P waves factor the diagonal block, all alike, each with one of the
+// P blocks that R_pp^{-H} is due on as its right half: the identity (its result is
+// E_pp^H), the rest of the panel's row of W, the column of E above it (transposed).
+// So the panel needs no products of its own; the trailing updates are spread over
+// all waves.  With SAME, E is W (P <= 2): R is not kept.
+template <int P, int NW, bool SAME, int LD>
 __device__ __forceinline__ bool chol_blocks(CMat<LD> W, CMat<LD> E, double cl, int wave, int lane) {
+    static_assert(NW >= P && NW > 1 && (!SAME || P <= 2), "chol_blocks");
+    const int x = lane & 15, q = lane >> 4;
     bool bad = false;
 #pragma unroll 1
     for (int p = 0; p < P; ++p) {
-        if (wave == 0) bad |= diag_factor(W, E, CB * p, cl, lane);
-        __syncthreads();
-        for (int j = p + 1 + wave; j < P; j += NW) {  // R_pj = R_pp^{-H} W_pj
-            CAcc c;
-            acc_zero(c);
-            acc_block<true>(c, E, CB * p, CB * p, W, CB * p, CB * j, lane);
-            acc_store<false>(c, W, CB * p, CB * j, 1.0, lane);
+        const int o = CB * p;
+        const int j = wave <= P - 1 - p ? p + wave : P - 1 - wave;  // right half: block pj of W, or of E for j < p
+        CAcc w, e;
+        if (wave < P) {
+            acc_load(w, W, o, o, lane);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 4 * r + q;
+                if (j > p) {
+                    e.re[r] = W.re[o + i][CB * j + x];
+                    e.im[r] = W.im[o + i][CB * j + x];
+                } else if (j < p) {
+                    e.re[r] = E.re[CB * j + x][o + i];
+                    e.im[r] = -E.im[CB * j + x][o + i];
+                } else {
+                    e.re[r] = i == x ? 1.0 : 0.0;
+                    e.im[r] = 0.0;
+                }
+            }
         }
         __syncthreads();
-        int t = 0;
-        for (int i = p + 1; i < P; ++i)
-            for (int j = i; j < P; ++j, ++t) {
-                if (t % NW != wave) continue;
-                CAcc c;
-                acc_zero(c);
-                acc_block<true>(c, W, CB * p, CB * i, W, CB * p, CB * j, lane);
-                acc_store<true>(c, W, CB * i, CB * j, -1.0, lane);
+        if (wave < P) {
+            CAcc R, F;
+            diag_panel<0>(w, e, R, F, cl, bad, lane);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 4 * r + q;
+                if (j > p) {
+                    W.re[o + i][CB * j + x] = F.re[r];
+                    W.im[o + i][CB * j + x] = F.im[r];
+                } else if (j < p) {
+                    E.re[CB * j + x][o + i] = F.re[r];
+                    E.im[CB * j + x][o + i] = -F.im[r];
+                } else {
+                    if constexpr (!SAME) {
+                        W.re[o + i][o + x] = x >= i ? R.re[r] : 0.0;
+                        W.im[o + i][o + x] = x > i ? R.im[r] : 0.0;
+                    }
+                    E.re[o + x][o + i] = x <= i ? F.re[r] : 0.0;
+                    E.im[o + x][o + i] = x <= i ? -F.im[r] : 0.0;
+                }
             }
+        }
         __syncthreads();
-    }
-#pragma unroll 1
-    for (int d = 1; d < P; ++d) {
-        for (int i = wave; i + d < P; i += NW) {  // E_ij = -E_ii sum_k R_ik E_kj
-            const int j = i + d;
+        if (p == P - 1) break;
+        if constexpr (SAME && P == 2) {  // E_01 takes the place of R_01 once both products have read it
             CAcc c;
             acc_zero(c);
-            for (int k = i + 1; k <= j; ++k) acc_block<false>(c, W, CB * i, CB * k, E, CB * k, CB * j, lane);
-            acc_store<false>(c, E, CB * i, CB * j, 1.0, lane);
-            CAcc f;
-            acc_zero(f);
-            acc_block<false>(f, E, CB * i, CB * i, E, CB * i, CB * j, lane);
-            acc_store<false>(f, E, CB * i, CB * j, -1.0, lane);
+            if (wave == 0) acc_block<true>(c, W, 0, CB, W, 0, CB, lane);
+            if (wave == 1) acc_block<false>(c, E, 0, 0, W, 0, CB, lane);
+            __syncthreads();
+            if (wave == 0) acc_store<true>(c, W, CB, CB, -1.0, lane);
+            if (wave == 1) acc_store<false>(c, E, 0, CB, -1.0, lane);
+        } else {
+            int t = 0;
+            for (int i = p + 1; i < P; ++i) {
+                for (int jj = i; jj < P; ++jj) {  // W_ij -= R_pi^H R_pj
+                    if (t++ % NW != wave) continue;
+                    CAcc c;
+                    acc_zero(c);
+                    acc_block<true>(c, W, o, CB * i, W, o, CB * jj, lane);
+                    acc_store<true>(c, W, CB * i, CB * jj, -1.0, lane);
+                }
+                for (int k = 0; k <= p; ++k) {    // E_ki -= E_kp R_pi (nothing there yet at k = p)
+                    if (t++ % NW != wave) continue;
+                    CAcc c;
+                    acc_zero(c);
+                    acc_block<false>(c, E, CB * k, o, W, o, CB * i, lane);
+                    if (k < p) acc_store<true>(c, E, CB * k, CB * i, -1.0, lane);
+                    else acc_store<false>(c, E, CB * k, CB * i, -1.0, lane);
+                }
+            }
         }
         __syncthreads();
     }
@@ -942,37 +1013,53 @@ __device__ __forceinline__ double chol_scale(CMat<LD> W, int n, int np, double s
 }
 
 // Cholesky factor and inverse, one workgroup per matrix (see launch_chol_inv).
-// A 64 x 64 call takes 33 us, half of it in the four diagonal blocks; an
-// elimination of single rows by 1024 threads, bound by its LDS reads, took 44.
-template <int P>
-__global__ void __launch_bounds__(256) k_chol_inv(const double2 *G, int n, double shift, double clamp, double2 *Rinv,
-                                                 double2 *Rf, int *flags, int first) {
+// A 64 x 64 call takes 24 us, 32 x 32 11.3; with one pivot at a time, its row through
+// shuffles, and the products of the panel apart, 33 and 12.8.  A diagonal block is
+// 7700 cycles, the trailing updates of a 64 x 64 matrix 12700 in all, the load and
+// the store 7300.  Adding up 16 partial Gram matrices here instead of in a launch
+// before it costs more (16.8 for 14 us): one CU reads them.
+template <int P, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) k_chol_inv(const double2 *G, int n, double shift,
+                                                        double clamp, double2 *Rinv, double2 *Rf, int *flags,
+                                                        int first) {
     __shared__ double sm[4][CB * P][CLD<P>];
     __shared__ double red;
     const CMat<CLD<P>> W{sm[0], sm[1]}, E{sm[2], sm[3]};
     const int b = blockIdx.x, t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const double2 *Gb = G + (int64_t)b * n * n;
-    constexpr int NP = CB * P;
+    const int64_t nn = (int64_t)n * n;
+    constexpr int NP = CB * P, NT = 64 * NW, PER = (NP * NP + NT - 1) / NT;
+    double2 g[PER];
 #pragma unroll
-    for (int u = 0; u < NP * NP / 256; ++u) {
-        const int e = t + 256 * u, i = e / NP, j = e % NP;
-        const bool in = i < n && j < n, up = j >= i;
-        double2 g = make_double2(0.0, 0.0);
-        if (in) g = up ? Gb[i * n + j] : Gb[j * n + i];  // only the upper triangle is given
-        W.re[i][j] = g.x;
-        W.im[i][j] = i == j ? 0.0 : up ? g.y : -g.y;
+    for (int u = 0; u < PER; ++u) {
+        // only the upper triangle is given; elsewhere the first element stands in
+        const int e = t + NT * u, i = e / NP, j = e % NP;
+        g[u] = G[b * nn + (j >= i && j < n ? i * n + j : 0)];
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int e = t + NT * u, i = e / NP, j = e % NP;
+        if (j < i || i >= NP) continue;
+        const double2 v = j < n ? g[u] : make_double2(0.0, 0.0);
+        W.re[i][j] = v.x;
+        W.im[i][j] = i == j ? 0.0 : v.y;
+        if (j > i && j / CB == i / CB) {
+            W.re[j][i] = v.x;
+            W.im[j][i] = -v.y;
+        }
     }
     __syncthreads();
     const double scale = chol_scale(W, n, NP, shift, &red);
-    const bool bad = chol_blocks<P, 4>(W, E, clamp * scale, wave, lane);
+    const bool bad = chol_blocks<P, NW, false>(W, E, clamp * scale, wave, lane);
     if (t == 0 && flags) flags[b] = (first ? 0 : flags[b]) | (bad ? 4 : 0);
-    double2 *Ob = Rinv + (int64_t)b * n * n;
-    double2 *Fb = Rf ? Rf + (int64_t)b * n * n : nullptr;
-    for (int e = t; e < n * n; e += 256) {
-        const int i = e / n, j = e % n;
+    double2 *Ob = Rinv + b * nn;
+    double2 *Fb = Rf ? Rf + b * nn : nullptr;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int e = t + NT * u, i = e / NP, j = e % NP;
+        if (i >= n || j >= n) continue;
         const bool up = j >= i;
-        Ob[e] = up ? make_double2(E.re[i][j], E.im[i][j]) : make_double2(0.0, 0.0);
-        if (Fb) Fb[e] = up ? make_double2(W.re[i][j], W.im[i][j]) : make_double2(0.0, 0.0);
+        Ob[i * n + j] = up ? make_double2(E.re[i][j], E.im[i][j]) : make_double2(0.0, 0.0);
+        if (Fb) Fb[i * n + j] = up ? make_double2(W.re[i][j], W.im[i][j]) : make_double2(0.0, 0.0);
     }
 }
 
@@ -987,7 +1074,7 @@ __global__ void __launch_bounds__(256) k_chol_inv(const double2 *G, int n, doubl
 // are dealt to the four waves so that each has the same number of k steps (at P =
 // 4) and keeps its Gram tiles in registers over the staged chunks.  With the
 // products on the vector unit a pass was bound by its LDS reads: 28 us on 4096 x
-// 64, now 14 (the whole orthonormalisation 164 for 285 us; 512 x 32 70 for 146).
+// 64, now 14 (the whole orthonormalisation 146 for 285 us; 512 x 32 66 for 146).
 template <int P>
 __global__ void __launch_bounds__(256) k_cqr_rows(CqrPass p) {
     constexpr int NP = CB * P;
@@ -1108,11 +1195,11 @@ __global__ void __launch_bounds__(256) k_cqr_rows(CqrPass p) {
 // passes: Gram matrix (each wave a share of the rows, the partial sums added in
 // wave order), its factor's inverse in place, rows times inverse.  flags[b] as from
 // launch_chol_inv.  Replaces eleven launches where a matrix alone cannot fill the
-// chip: 128 x 32 takes 61 us (145 before), 32 of 128 x 16 28 (103), 64 x 16 21 (96).
+// chip: 256 x 32 takes 80 us, 32 of 128 x 16 24 (103 before), 64 x 16 19 (96).
 constexpr int CQR1_ROWS = 256;
 constexpr int XLD = 33;  // padded LDS row of 32 complex doubles
 template <int P>
-__global__ void __launch_bounds__(256) k_cqr_one(QrArgs a, double shift, int *flags) {
+__global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int *flags) {
     extern __shared__ double2 lds[];                 // X [rows of 16][XLD]
     __shared__ double sW[2][CB * P][CLD<P>];
     __shared__ double red;
@@ -1159,7 +1246,7 @@ __global__ void __launch_bounds__(256) k_cqr_one(QrArgs a, double shift, int *fl
             __syncthreads();
         }
         const double scale = chol_scale(W, n, NP, pass == 0 ? shift : 0.0, &red);
-        bad |= chol_blocks<P, 4>(W, W, (pass == 0 ? 1e-300 : 1e-14) * scale, wave, lane);
+        bad |= chol_blocks<P, 4, true>(W, W, (pass == 0 ? 1e-300 : 1e-14) * scale, wave, lane);
         for (int r = wave; r < mt; r += 4) {
             CAcc y[P];
 #pragma unroll
@@ -1247,11 +1334,13 @@ hipError_t launch_chol_inv(const double *G, int n, int batch, double shift, doub
     if (n > 64 || n < 1) return hipErrorInvalidValue;
     const double2 *g = reinterpret_cast<const double2 *>(G);
     double2 *ri = reinterpret_cast<double2 *>(Rinv), *rf = reinterpret_cast<double2 *>(Rf);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(batch), dim3(256), 0, s, g, n, shift, clamp, ri, rf, flags, first); };
-    if (n <= 16) go(k_chol_inv<1>);
-    else if (n <= 32) go(k_chol_inv<2>);
-    else if (n <= 48) go(k_chol_inv<3>);
-    else go(k_chol_inv<4>);
+    auto go = [&](auto kernel, int nt) {
+        hipLaunchKernelGGL(kernel, dim3(batch), dim3(nt), 0, s, g, n, shift, clamp, ri, rf, flags, first);
+    };
+    if (n <= 16) go(k_chol_inv<1, 4>, 256);
+    else if (n <= 32) go(k_chol_inv<2, 4>, 256);
+    else if (n <= 48) go(k_chol_inv<3, 8>, 512);
+    else go(k_chol_inv<4, 8>, 512);
     return hipGetLastError();
 }
 
