@@ -579,8 +579,8 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
 // rows, whose other tiles would be padding, go to the kernel whose waves share K: 256
 // x 256 x 256: 6.8 against 11.8 for 32x32 in 4 slices, 2187 x 9 x 81: 4.3 / 8.2, 32 x
 // 512 x 512: 9.0 / 12.3 in 8; 4 x 128 x 2 x 1000: 21 / 26 for 64x64; 4096 x 1 x 4096:
-// 50 / 199; 512 x 256 x 512 (512 tiles): 17 / 21.  With 1024 tiles it loses (512 x
-// 512 x 32: 7.1 / 6.5, 512 x 512 x 256: 21 / 17, 32768 x 8 x 128: 28 / 17), and with
+// 50 / 199; 512 x 256 x 512 (512 tiles): 17 / 21.  With 1024 tiles it wins or loses by
+// K (512 x 512 x 32: 6.0 / 6.5, 512 x 512 x 256: 21 / 17, 32768 x 8 x 128: 28 / 17), and with
 // more than 256 of a large problem (32 x 4096 x 4096: 98 / 87).  It cuts K from 768 on,
 // into slices of at least 256 (16 x 256 x 1024: 10.0 in 4 for 14.5; 64 x 64 x 4096:
 // 14 in 16 for 23 with 32x32).

@@ -401,14 +401,13 @@ gett_mfma(GettArgs p) {
 // at 2100 cycles per 16 (loads, store, barrier and 768 of matrix work in turn).  In
 // FP64, before and after: 8 x 8 x 8 4.0 and 2.5 us; 2187 x 9 x 81 8.2 and 4.3; 32 x 512
 // x 512 12.3 with its second launch and 9.0; 1 x 4096 x 4096 82 and 47 (5.7 TB/s).
-// U = 8 quads in flight per wave; 16 waves a tile leave 128 registers and spill (32 x
+// A wave has U quads in flight; 16 waves a tile leave 128 registers and spill (32 x
 // 512 x 512 12.9 us).
-template <typename T, int W, bool G3>
+template <typename T, int W, int U, bool G3>
 __global__ void __launch_bounds__(64 * W)
 gett_wave(GettArgs p) {
     using C2 = typename Tr<T>::C2;
     using Acc = typename Tr<T>::Acc;
-    constexpr int U = 8;  // quads of k in flight
     constexpr uint32_t ESZ = sizeof(C2);
     __shared__ C2 sums[W][256];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -440,13 +439,20 @@ gett_wave(GettArgs p) {
         for (int k0 = kw; k0 < kwe; k0 += 4 * U) {
             C2 a[U], bb[U];
             int ka[U], kb[U];
+            const int kl = k0 + (lane >> 4);
+            if (p.a_kaff) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int k = min(k0 + 4 * u + (lane >> 4), kwe - 1);
-                ka[u] = k * p.a_ks;
-                kb[u] = k * p.b_ks;
-                if (!p.a_kaff) ka[u] = p.a_koff[k];
-                if (!p.b_kaff) kb[u] = p.b_koff[k];
+                for (int u = 0; u < U; ++u) ka[u] = min(kl + 4 * u, kwe - 1) * p.a_ks;
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) ka[u] = p.a_koff[min(kl + 4 * u, kwe - 1)];
+            }
+            if (p.b_kaff) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) kb[u] = min(kl + 4 * u, kwe - 1) * p.b_ks;
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) kb[u] = p.b_koff[min(kl + 4 * u, kwe - 1)];
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -1089,10 +1095,16 @@ hipError_t launch_wave(const GettArgs &a, hipStream_t s) {
     // 4 waves (less to sum and to place on a CU) for a K of at most one quad each, and
     // while the tiles are more than the CUs, up to 64: 512 x 256 x 64 5.6 us for 6.4 with
     // 8 waves, which serve 64 x 16 x 64 in 3.6 us for 4.2
+    // U: the quads that a wave's share of such a K has, up to 8; fewer registers and
+    // less code than 8 for all (512 x 512 x 32 7.3 us and 6.0, 16 x 4 x 2 x 1000 5.4
+    // and 3.9, 8 x 8 x 8 2.7 and 2.4)
     const int k = std::min(a.K, a.kchunk);
-    if (k <= 16 || (k <= 64 && tiles * a.batch > 256))
-        hipLaunchKernelGGL((gett_wave<T, 4, G3>), g, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((gett_wave<T, 8, G3>), g, dim3(512), 0, s, a);
+    auto go = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, g, dim3(nt), 0, s, a); };
+    if (k <= 16) go(gett_wave<T, 4, 1, G3>, 256);
+    else if (k <= 64 && tiles * a.batch > 256) go(gett_wave<T, 4, 4, G3>, 256);
+    else if (k <= 64) go(gett_wave<T, 8, 2, G3>, 512);
+    else if (k <= 128) go(gett_wave<T, 8, 4, G3>, 512);
+    else go(gett_wave<T, 8, 8, G3>, 512);
     return hipGetLastError();
 }
 
