@@ -119,7 +119,9 @@ PepsDev stage(Engine &E, const tn_peps *p) {
     P.site_index.assign(p->site_index, p->site_index + n);
     P.nq = 0;
     for (int i = 0; i < n; ++i) P.nq += p->phys[i] == 2;
-    const int src_esz = p->dtype == TN_C128 ? 16 : 8;
+    tnk::ConvertSet cs{};
+    cs.src_esz = p->dtype == TN_C128 ? 16 : 8;
+    cs.dst_esz = E.esz;
     for (int r = 0; r < p->rows; ++r)
         for (int c = 0; c < p->cols; ++c) {
             const int i = r * p->cols + c;
@@ -128,8 +130,14 @@ PepsDev stage(Engine &E, const tn_peps *p) {
             const int l = c > 0 ? p->dim_h[r * (p->cols - 1) + c - 1] : 1;
             const int rr = c + 1 < p->cols ? p->dim_h[r * (p->cols - 1) + c] : 1;
             Ten t = E.make({p->phys[i], u, l, d, rr});
-            TN_HIP(tnk::launch_convert(p->site[i], src_esz, t.p, t.esz, t.numel(), E.s));
             P.site.push_back(t);
+            cs.src[cs.count] = p->site[i];
+            cs.dst[cs.count] = t.p;
+            cs.n[cs.count] = t.numel();
+            if (++cs.count == tnk::CS_MAX || i + 1 == n) {  // one launch for the sites, not one each
+                TN_HIP(tnk::launch_convert_set(cs, E.s));
+                cs.count = 0;
+            }
         }
     return P;
 }
@@ -391,11 +399,19 @@ tn_status tn_simple_update(tn_handle *h, const tn_peps *p, void *const *site_out
             so.bp_max_sweeps = bp_max_sweeps;
             so.bp_tol = bp_tol;
             simple_update(E, P, gl, gates, gate_stride, so, eps, messages_in, messages_out);
-            const int dst_esz = p->dtype == TN_C128 ? 16 : 8;
+            tnk::ConvertSet cs{};
+            cs.src_esz = 16;
+            cs.dst_esz = p->dtype == TN_C128 ? 16 : 8;
             for (int i = 0; i < rows * cols; ++i) {
                 const Ten &t = P.site[(size_t)i];
                 if (!site_out[i]) throw TnError(ST_INVALID, "null output site");
-                TN_HIP(tnk::launch_convert(t.p, 16, site_out[i], dst_esz, t.numel(), E.s));
+                cs.src[cs.count] = t.p;
+                cs.dst[cs.count] = site_out[i];
+                cs.n[cs.count] = t.numel();
+                if (++cs.count == tnk::CS_MAX || i + 1 == rows * cols) {
+                    TN_HIP(tnk::launch_convert_set(cs, E.s));
+                    cs.count = 0;
+                }
             }
             E.sync();
         } catch (...) {

@@ -104,7 +104,8 @@ static int64_t prod(const std::vector<int> &d, int a, int b) {
     return p;
 }
 
-// QR of T seen as batch x m x n (batch = first nb dims, n = last dim).
+// QR of T seen as batch x m x n (batch = first nb dims, n = last dim).  R may be T
+// itself (the same memory): the caller drops T only where R->p differs.
 // well_conditioned: R may come from CholeskyQR3 (see Engine::orthonormalise).
 void qr_left(Engine &E, const Ten &T, int nb, Ten &Q, Ten *R, bool well_conditioned) {
     const int rk = (int)T.d.size();
@@ -115,19 +116,20 @@ void qr_left(Engine &E, const Ten &T, int nb, Ten &Q, Ten *R, bool well_conditio
     std::vector<int> qd = T.d;
     qd[rk - 1] = (int)k;
     Q = E.make(qd, T.esz);
-    if (R) {
-        std::vector<int> rd(T.d.begin(), T.d.begin() + nb);
-        rd.push_back((int)k);
-        rd.push_back((int)n);
-        *R = E.make(rd, T.esz);
-    }
+    std::vector<int> rd(T.d.begin(), T.d.begin() + nb);
+    rd.push_back((int)k);
+    rd.push_back((int)n);
     if (m == n) {
         // a square factor spans the whole space: Q = I, R = T is an exact
         // factorisation in another gauge (every output is gauge invariant)
         TN_HIP(tnk::launch_eye(Q.p, Q.esz, (int)n, (int)batch, E.s));
-        if (R) TN_HIP(tnk::launch_convert(T.p, T.esz, R->p, R->esz, T.numel(), E.s));
+        if (R) {
+            *R = T;
+            R->d = rd;
+        }
         return;
     }
+    if (R) *R = E.make(rd, T.esz);
     tnk::QrArgs a{};
     a.m = (int)m; a.n = (int)n; a.batch = (int)batch;
     a.A = T.p; a.a_esz = T.esz; a.a_bs = m * n; a.a_rs = n; a.a_cs = 1; a.a_conj = 0;
@@ -148,17 +150,18 @@ void lq_right(Engine &E, const Ten &T, int nb, Ten &Q, Ten *Lf, bool well_condit
     std::vector<int> qd = T.d;
     qd[nb] = (int)k;
     Q = E.make(qd, T.esz);
-    if (Lf) {
-        std::vector<int> ld(T.d.begin(), T.d.begin() + nb);
-        ld.push_back((int)m);
-        ld.push_back((int)k);
-        *Lf = E.make(ld, T.esz);
-    }
-    if (m == n) {  // square: Q = I, L = T (see qr_left)
+    std::vector<int> ld(T.d.begin(), T.d.begin() + nb);
+    ld.push_back((int)m);
+    ld.push_back((int)k);
+    if (m == n) {  // square: Q = I, L = T itself (see qr_left)
         TN_HIP(tnk::launch_eye(Q.p, Q.esz, (int)n, (int)batch, E.s));
-        if (Lf) TN_HIP(tnk::launch_convert(T.p, T.esz, Lf->p, Lf->esz, T.numel(), E.s));
+        if (Lf) {
+            *Lf = T;
+            Lf->d = ld;
+        }
         return;
     }
+    if (Lf) *Lf = E.make(ld, T.esz);
     // QR of T^H (n x m): T^H(i, j) = conj(T[j][i])
     tnk::QrArgs a{};
     a.m = (int)n; a.n = (int)m; a.batch = (int)batch;
@@ -220,7 +223,7 @@ void canonicalise(Engine &E, std::vector<Ten> &Y, int nb, double *logscale, bool
     for (int c = 0; c + 1 < L; ++c) {
         Ten Q, R;
         qr_left(E, Y[c], nb, Q, &R);
-        E.drop(Y[c]);
+        if (R.p != Y[c].p) E.drop(Y[c]);
         Y[c] = Q;
         Ten N = nb ? E.contract_new(op(R, "zab"), op(Y[c + 1], "zbcd"), "zacd")
                    : E.contract_new(op(R, "ab"), op(Y[c + 1], "bcde"), "acde");
@@ -231,7 +234,7 @@ void canonicalise(Engine &E, std::vector<Ten> &Y, int nb, double *logscale, bool
     for (int c = L - 1; c >= 1; --c) {
         Ten Q, Lm;
         lq_right(E, Y[c], nb, Q, &Lm);
-        E.drop(Y[c]);
+        if (Lm.p != Y[c].p) E.drop(Y[c]);
         Y[c] = Q;
         Ten N = nb ? E.contract_new(op(Y[c - 1], "zabc"), op(Lm, "zcd"), "zabd")
                    : E.contract_new(op(Y[c - 1], "abcd"), op(Lm, "de"), "abce");
@@ -251,7 +254,7 @@ void right_canonicalise(Engine &E, std::vector<Ten> &Y, int nb) {
     for (int c = L - 1; c >= 1; --c) {
         Ten Q, Lm;
         lq_right(E, Y[c], nb, Q, &Lm, true);
-        E.drop(Y[c]);
+        if (Lm.p != Y[c].p) E.drop(Y[c]);
         Y[c] = Q;
         Ten N = nb ? E.contract_new(op(Y[c - 1], "zabc"), op(Lm, "zcd"), "zabd")
                    : E.contract_new(op(Y[c - 1], "abcd"), op(Lm, "de"), "abce");

@@ -302,8 +302,8 @@ void simple_update(Engine &E, PepsDev &P, const std::vector<SuGate> &gates, cons
                 Ten QA, RA, QB, RB;
                 qr_left(E, Ag, 1, QA, &RA);
                 qr_left(E, Bg, 1, QB, &RB);
-                E.drop(Ag);
-                E.drop(Bg);
+                if (RA.p != Ag.p) E.drop(Ag);
+                if (RB.p != Bg.p) E.drop(Bg);
                 live.push_back(QA);
                 live.push_back(QB);
                 const int kA = RA.d[1], kB = RB.d[1];

@@ -1411,10 +1411,8 @@ void Engine::norm2(const void *x, int e, int64_t n, int batch, int64_t bs, doubl
 
 void Engine::normalise(void *x, int e, int64_t n, int batch, int64_t bs, double *logscale, bool acc,
                        int *flags) {
-    void *q = pool_.get((size_t)batch * 8);
-    norm2(x, e, n, batch, bs, reinterpret_cast<double *>(q));
-    TN_HIP(tnk::launch_normalise(x, e, n, batch, bs, reinterpret_cast<double *>(q), logscale, acc ? 1 : 0,
-                                 flags, s));
+    void *q = pool_.get((size_t)tnk::reduce_partial_count(n) * batch * 8);
+    TN_HIP(tnk::launch_normalise(x, e, n, batch, bs, reinterpret_cast<double *>(q), logscale, acc ? 1 : 0, flags, s));
     pool_.put(q);
 }
 

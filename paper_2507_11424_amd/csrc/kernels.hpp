@@ -194,14 +194,24 @@ hipError_t launch_strided_copy(const void *in, int ie, int64_t ibs, int64_t irs,
 int reduce_partial_count(int64_t n);
 hipError_t launch_norm2(const void *x, int esz, int64_t n, int batch, int64_t bs,
                         double *partial, double *out, hipStream_t s);
-// x[b] *= 1/sqrt(norm2[b]); logscale[b] (+)= 0.5 log(norm2[b]); flags[b] |= 1 if
-// norm2 is not finite or not positive.
+// With q = sum |x[b][i]|^2: x[b] *= 1/sqrt(q); logscale[b] (+)= 0.5 log(q); if q is not
+// finite or not positive x[b] and its log stay and flags[b] |= 1.  partial as for
+// launch_norm2.
 hipError_t launch_normalise(void *x, int esz, int64_t n, int batch, int64_t bs,
-                            const double *norm2, double *logscale, int accumulate_log,
+                            double *partial, double *logscale, int accumulate_log,
                             int *flags, hipStream_t s);
 // Element-type conversion / copy (c128 <-> c64), n complex elements.
 hipError_t launch_convert(const void *src, int src_esz, void *dst, int dst_esz, int64_t n,
                           hipStream_t s);
+// The same for up to CS_MAX tensors in one launch.
+constexpr int CS_MAX = 96;
+struct ConvertSet {
+    int count, src_esz, dst_esz;
+    const void *src[CS_MAX];
+    void *dst[CS_MAX];
+    int64_t n[CS_MAX];
+};
+hipError_t launch_convert_set(const ConvertSet &c, hipStream_t s);
 // Philox-uniform complex initial guess: element e of tensor gets counter
 // (e, site, row, sample[b]) and key (seed, tag).
 hipError_t launch_init_tensor(void *out, int esz, int64_t n, int batch, int64_t bs,

@@ -38,49 +38,107 @@ __device__ inline double bsum(double v) {
     return s;
 }
 
+// f(i) for i = first, first + step, ... < n in that order, with the loads l(i) of
+// eight of them in flight (a reduction alone in the chip waits for little else).
+template <typename L, typename F>
+__device__ inline void for_loaded(int64_t first, int64_t step, int64_t n, L l, F f) {
+    int64_t i = first;
+    for (; i + 7 * step < n; i += 8 * step) {
+        decltype(l(i)) v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = l(i + u * step);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f(v[u]);
+    }
+    for (; i < n; i += step) f(l(i));
+}
+
+// Sum of the P <= NT parts of one item in their order, to every thread: the parts
+// come into LDS together (one thread walking through memory took 10 us for 256).
+__device__ inline double parts_sum(const double *part, int P, int stride) {
+    __shared__ double v[NT];
+    __shared__ double sum;
+    if ((int)threadIdx.x < P) v[threadIdx.x] = part[(int64_t)threadIdx.x * stride];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int i = 0; i < P; ++i) s += v[i];
+        sum = s;
+    }
+    __syncthreads();
+    return sum;
+}
+
 __global__ void __launch_bounds__(NT) k_norm2_part(const void *x, int esz, int64_t n, int64_t bs,
                                                   int P, double *partial) {
     const int b = blockIdx.y;
     const char *xb = reinterpret_cast<const char *>(x) + (int64_t)b * bs * esz;
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)P * NT) {
-        const double2 v = ldc(xb, esz, i);
-        s += v.x * v.x + v.y * v.y;
-    }
+    for_loaded((int64_t)blockIdx.x * NT + threadIdx.x, (int64_t)P * NT, n, [&](int64_t i) { return ldc(xb, esz, i); },
+               [&](double2 v) { s += v.x * v.x + v.y * v.y; });
     s = bsum(s);
     if (threadIdx.x == 0) partial[(int64_t)b * P + blockIdx.x] = s;
 }
 
-__global__ void k_sum_parts(const double *partial, int P, int batch, double *out) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= batch) return;
-    double s = 0.0;
-    for (int i = 0; i < P; ++i) s += partial[(int64_t)b * P + i];
-    out[b] = s;
+__global__ void __launch_bounds__(NT) k_sum_parts(const double *partial, int P, double *out) {
+    const int b = blockIdx.x;
+    const double s = parts_sum(partial + (int64_t)b * P, P, 1);
+    if (threadIdx.x == 0) out[b] = s;
 }
 
-__global__ void __launch_bounds__(NT) k_normalise(void *x, int esz, int64_t n, int64_t bs,
-                                                 const double *norm2, double *logscale, int acc,
-                                                 int *flags) {
-    const int b = blockIdx.y;
-    const double q = norm2[b];
+// What normalising does beside the elements: log(norm) and the flag.
+__device__ inline double norm_factor(double q, int b, bool first, double *logscale, int acc, int *flags) {
     const bool bad = !(q > 0.0) || !isfinite(q);
-    const double f = bad ? 1.0 : 1.0 / sqrt(q);
+    if (first && threadIdx.x == 0) {
+        if (logscale) logscale[b] = (acc ? logscale[b] : 0.0) + (bad ? 0.0 : 0.5 * log(q));
+        if (bad && flags) flags[b] |= 1;
+    }
+    return bad ? 1.0 : 1.0 / sqrt(q);
+}
+
+__global__ void __launch_bounds__(NT) k_normalise(void *x, int esz, int64_t n, int64_t bs, const double *partial, int P,
+                                                 double *logscale, int acc, int *flags) {
+    const int b = blockIdx.y;
+    const double f = norm_factor(parts_sum(partial + (int64_t)b * P, P, 1), b, blockIdx.x == 0, logscale, acc, flags);
     char *xb = reinterpret_cast<char *>(x) + (int64_t)b * bs * esz;
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
         double2 v = ldc(xb, esz, i);
         v.x *= f; v.y *= f;
         stc(xb, esz, i, v);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (logscale) logscale[b] = (acc ? logscale[b] : 0.0) + (bad ? 0.0 : 0.5 * log(q));
-        if (bad && flags) flags[b] |= 1;
-    }
+}
+
+// Up to R * NT elements: norm and scaling in one launch, the elements in registers.
+// A launch of this size is all latency, so one for three is a third of the time.
+template <int R>
+__global__ void __launch_bounds__(NT) k_normalise_one(void *x, int esz, int64_t n, int64_t bs, double *logscale,
+                                                     int acc, int *flags) {
+    const int b = blockIdx.x, t = threadIdx.x;
+    char *xb = reinterpret_cast<char *>(x) + (int64_t)b * bs * esz;
+    double2 v[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) v[u] = t + u * NT < n ? ldc(xb, esz, t + u * NT) : make_double2(0.0, 0.0);
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (t + u * NT < n) s += v[u].x * v[u].x + v[u].y * v[u].y;
+    const double f = norm_factor(bsum(s), b, true, logscale, acc, flags);
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (t + u * NT < n) stc(xb, esz, t + u * NT, make_double2(v[u].x * f, v[u].y * f));
 }
 
 __global__ void __launch_bounds__(NT) k_convert(const void *src, int se, void *dst, int de, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT)
         stc(dst, de, i, ldc(src, se, i));
+}
+
+// Many tensors in one launch (a lattice's sites): blockIdx.y names the tensor.
+__global__ void __launch_bounds__(NT) k_convert_set(ConvertSet c) {
+    const int t = blockIdx.y;
+    const int64_t n = c.n[t];
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT)
+        stc(c.dst[t], c.dst_esz, i, ldc(c.src[t], c.src_esz, i));
 }
 
 __global__ void __launch_bounds__(NT) k_fill(void *x, int esz, int64_t n, double re, double im) {
@@ -133,32 +191,33 @@ __global__ void __launch_bounds__(NT) k_dot_part(const void *x, const void *y, i
     if (mask && mask[b] == mask_skip) return;
     const char *xb = reinterpret_cast<const char *>(x) + (int64_t)b * bs * esz;
     const char *yb = reinterpret_cast<const char *>(y) + (int64_t)b * bs * esz;
+    struct Pair { double2 a, c; };
     double sr = 0.0, si = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)P * NT) {
-        const double2 a = ldc(xb, esz, i), c = ldc(yb, esz, i);
-        sr += a.x * c.x - a.y * c.y;
-        si += a.x * c.y + a.y * c.x;
-    }
+    for_loaded((int64_t)blockIdx.x * NT + threadIdx.x, (int64_t)P * NT, n,
+               [&](int64_t i) { return Pair{ldc(xb, esz, i), ldc(yb, esz, i)}; },
+               [&](const Pair &v) {
+                   sr += v.a.x * v.c.x - v.a.y * v.c.y;
+                   si += v.a.x * v.c.y + v.a.y * v.c.x;
+               });
     sr = bsum(sr);
     si = bsum(si);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0) {  // (one part per item is the result itself)
         partial[((int64_t)b * P + blockIdx.x) * 2] = sr;
         partial[((int64_t)b * P + blockIdx.x) * 2 + 1] = si;
     }
 }
 
-__global__ void k_sum_parts2(const double *partial, int P, int batch, double *out, const int *mask,
-                             int mask_skip) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= batch) return;
+__global__ void __launch_bounds__(NT) k_sum_parts2(const double *partial, int P, double *out, const int *mask,
+                                                  int mask_skip) {
+    const int b = blockIdx.x;
     if (mask && mask[b] == mask_skip) return;
-    double sr = 0.0, si = 0.0;
-    for (int i = 0; i < P; ++i) {
-        sr += partial[((int64_t)b * P + i) * 2];
-        si += partial[((int64_t)b * P + i) * 2 + 1];
+    const double sr = parts_sum(partial + (int64_t)b * P * 2, P, 2);
+    __syncthreads();
+    const double si = parts_sum(partial + (int64_t)b * P * 2 + 1, P, 2);
+    if (threadIdx.x == 0) {
+        out[2 * b] = sr;
+        out[2 * b + 1] = si;
     }
-    out[2 * b] = sr;
-    out[2 * b + 1] = si;
 }
 
 __global__ void k_draw(DrawArgs a) {
@@ -479,22 +538,44 @@ int reduce_partial_count(int64_t n) {
 hipError_t launch_norm2(const void *x, int esz, int64_t n, int batch, int64_t bs, double *partial,
                         double *out, hipStream_t s) {
     const int P = reduce_partial_count(n);
-    hipLaunchKernelGGL(k_norm2_part, dim3(P, batch), dim3(NT), 0, s, x, esz, n, bs, P, partial);
-    hipLaunchKernelGGL(k_sum_parts, dim3((batch + 63) / 64), dim3(64), 0, s, partial, P, batch, out);
+    hipLaunchKernelGGL(k_norm2_part, dim3(P, batch), dim3(NT), 0, s, x, esz, n, bs, P, P > 1 ? partial : out);
+    if (P > 1) hipLaunchKernelGGL(k_sum_parts, dim3(batch), dim3(NT), 0, s, partial, P, out);
     return hipGetLastError();
 }
 
-hipError_t launch_normalise(void *x, int esz, int64_t n, int batch, int64_t bs, const double *norm2,
+hipError_t launch_normalise(void *x, int esz, int64_t n, int batch, int64_t bs, double *partial,
                             double *logscale, int acc, int *flags, hipStream_t s) {
+    // what one workgroup holds in registers is normalised by it alone; 32 elements a
+    // thread is the line, where its load and store (3 us) weigh as much as two launches
+    if (n <= 8 * NT) {
+        hipLaunchKernelGGL(k_normalise_one<8>, dim3(batch), dim3(NT), 0, s, x, esz, n, bs, logscale, acc, flags);
+        return hipGetLastError();
+    }
+    if (n <= 32 * NT) {
+        hipLaunchKernelGGL(k_normalise_one<32>, dim3(batch), dim3(NT), 0, s, x, esz, n, bs, logscale, acc, flags);
+        return hipGetLastError();
+    }
+    const int P = reduce_partial_count(n);
+    hipLaunchKernelGGL(k_norm2_part, dim3(P, batch), dim3(NT), 0, s, x, esz, n, bs, P, partial);
     int g = grid_for(n);
     if (g > 512) g = 512;
-    hipLaunchKernelGGL(k_normalise, dim3(g, batch), dim3(NT), 0, s, x, esz, n, bs, norm2, logscale, acc, flags);
+    hipLaunchKernelGGL(k_normalise, dim3(g, batch), dim3(NT), 0, s, x, esz, n, bs, partial, P, logscale, acc, flags);
     return hipGetLastError();
 }
 
 hipError_t launch_convert(const void *src, int se, void *dst, int de, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_convert, dim3(grid_for(n)), dim3(NT), 0, s, src, se, dst, de, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_convert_set(const ConvertSet &c, hipStream_t s) {
+    if (c.count <= 0) return hipSuccess;
+    int64_t mx = 1;
+    for (int i = 0; i < c.count; ++i) mx = c.n[i] > mx ? c.n[i] : mx;
+    int g = grid_for(mx);
+    if (g > 256) g = 256;
+    hipLaunchKernelGGL(k_convert_set, dim3(g, c.count), dim3(NT), 0, s, c);
     return hipGetLastError();
 }
 
@@ -524,10 +605,9 @@ hipError_t launch_init_tensor(void *out, int esz, int64_t n, int batch, int64_t 
 hipError_t launch_dot(const void *x, const void *y, int esz, int64_t n, int batch, int64_t bs,
                       double *partial, double *out, hipStream_t s, const int *mask, int mask_skip) {
     const int P = reduce_partial_count(n);
-    hipLaunchKernelGGL(k_dot_part, dim3(P, batch), dim3(NT), 0, s, x, y, esz, n, bs, P, partial, mask,
+    hipLaunchKernelGGL(k_dot_part, dim3(P, batch), dim3(NT), 0, s, x, y, esz, n, bs, P, P > 1 ? partial : out, mask,
                        mask_skip);
-    hipLaunchKernelGGL(k_sum_parts2, dim3((batch + 63) / 64), dim3(64), 0, s, partial, P, batch, out, mask,
-                       mask_skip);
+    if (P > 1) hipLaunchKernelGGL(k_sum_parts2, dim3(batch), dim3(NT), 0, s, partial, P, out, mask, mask_skip);
     return hipGetLastError();
 }
 
