@@ -341,12 +341,12 @@ __global__ void __launch_bounds__(QR_NT) k_qr_form(FormArgs a) {
 // d = |x_j| + sigma, with its factor f = ph / d in the column's lanes:
 // v = conj(f) p, v_j = 1.  At the top of the tree the reflectors, still in
 // registers, are applied to the identity in the same launch.  Measured against
-// the LDS kernels (five barriers a step), Q and R: 128 x 64 339 for 600 us, 4096 x
-// 64 2.08 for 3.69 ms, 128 x 32 141 for 346, 32 of 128 x 16 48 for 234, 64 x 16 46
-// for 109.  512 threads serve 64 columns as well as 256 (338 and 367 us; 1024: 474);
+// the LDS kernels (five barriers a step), Q and R: 128 x 64 234 for 600 us, 4096 x
+// 64 1.43 for 3.69 ms, 128 x 32 123 for 346, 32 of 128 x 16 30 for 234, 64 x 16 24
+// for 109; with the pivot column through shuffles or twice a step, and divisions and
+// square roots of the library, 339, 2.08, 141, 48 and 46.  512 threads serve 64 columns as well as 256 (338 and 367 us; 1024: 474);
 // up to 32 columns 256 are no slower than 512 and leave room for more blocks.
 constexpr int QR_REG_ROWS = 128;
-constexpr int QR_REG_FEW = 32;  // blocks of at most so many rows hold a quarter of the registers
 
 __device__ inline double lane_get(double v, int lane) {
     const int2 a = __builtin_bit_cast(int2, v);
@@ -361,69 +361,133 @@ template <int NC> __device__ __forceinline__ double2 column(double2 v, int j) {
     return make_double2(__shfl(v.x, src, 64), __shfl(v.y, src, 64));
 }
 
+// Lane K of each row of 16 lanes, to the whole row.
+template <int K> __device__ __forceinline__ double row_lane(double v) {
+    const int2 a = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(a.x, 0x150 + K, 0xf, 0xf, false),
+                                                __builtin_amdgcn_mov_dpp(a.y, 0x150 + K, 0xf, 0xf, false)));
+}
+// 1 / sqrt(d) for d > 0 in the normal range: the hardware estimate r and one step of
+// third order, r (1 + y / 2 + 3 y^2 / 8) with y = 1 - d r^2.
+__device__ __forceinline__ double rsqrt3(double d) {
+    const double r = __builtin_amdgcn_rsq(d);
+    const double y = fma(-d * r, r, 1.0);
+    return fma(r * y, fma(y, 0.375, 0.5), r);
+}
+// 1 / d for d > 0 in the normal range: the hardware estimate and two Newton steps.
+__device__ __forceinline__ double recip(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
+}
+template <int J, int RT> __device__ __forceinline__ void row_lanes(const double2 (&V)[RT], double2 (&p)[RT]) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) p[r] = make_double2(row_lane<J>(V[r].x), row_lane<J>(V[r].y));
+}
+template <int RT> __device__ __forceinline__ void row_lanes(const double2 (&V)[RT], int j, double2 (&p)[RT]) {
+    switch (j) {
+        case 0: row_lanes<0>(V, p); break;
+        case 1: row_lanes<1>(V, p); break;
+        case 2: row_lanes<2>(V, p); break;
+        case 3: row_lanes<3>(V, p); break;
+        case 4: row_lanes<4>(V, p); break;
+        case 5: row_lanes<5>(V, p); break;
+        case 6: row_lanes<6>(V, p); break;
+        case 7: row_lanes<7>(V, p); break;
+        case 8: row_lanes<8>(V, p); break;
+        case 9: row_lanes<9>(V, p); break;
+        case 10: row_lanes<10>(V, p); break;
+        case 11: row_lanes<11>(V, p); break;
+        case 12: row_lanes<12>(V, p); break;
+        case 13: row_lanes<13>(V, p); break;
+        case 14: row_lanes<14>(V, p); break;
+        default: row_lanes<15>(V, p); break;
+    }
+}
+// Rows 0, 0, 2, 2 of 16 lanes of v, or rows 1, 1, 3, 3.
+__device__ __forceinline__ double row_pair(double v, bool odd) {
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    const uint2 d = __builtin_bit_cast(uint2, v);
+    const v2u x = __builtin_amdgcn_permlane16_swap(d.x, d.x, false, false);
+    const v2u y = __builtin_amdgcn_permlane16_swap(d.y, d.y, false, false);
+    return __builtin_bit_cast(double, odd ? make_uint2(x.y, y.y) : make_uint2(x.x, y.x));
+}
+// p = column j of V, every lane its own group's rows (j the same in all lanes): once
+// a step, on the vector unit.  Through shuffles, once for the products and again for
+// the update, this was most of a step.
+template <int NC, int RT> __device__ __forceinline__ void pivot_column(const double2 (&V)[RT], int j, double2 (&p)[RT]) {
+    if constexpr (NC == 64) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) p[r] = make_double2(lane_get(V[r].x, j), lane_get(V[r].y, j));
+    } else if constexpr (NC == 32) {
+        double2 half[RT];
+        const bool odd = j >= 16;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) half[r] = make_double2(row_pair(V[r].x, odd), row_pair(V[r].y, odd));
+        row_lanes(half, j & 15, p);
+    } else {
+        row_lanes(V, j, p);
+    }
+}
+
 template <int NC, int NT> struct QrRegShared {
     double2 part[2][NT / 64][NC];  // [parity of the reduction][wave][column]
     double2 row[2][NC];      // the pivot row
 };
-constexpr int QR_CH = 8;     // registers handled under one test
 
-// Adds the row groups of a wave (its lanes of equal column).
+// Adds the row groups of a wave (its lanes of equal column): halves, then rows of 16.
+__device__ __forceinline__ double half_add(double v) {
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    const uint2 d = __builtin_bit_cast(uint2, v);
+    const v2u x = __builtin_amdgcn_permlane32_swap(d.x, d.x, false, false);
+    const v2u y = __builtin_amdgcn_permlane32_swap(d.y, d.y, false, false);
+    return __builtin_bit_cast(double, make_uint2(x.x, y.x)) + __builtin_bit_cast(double, make_uint2(x.y, y.y));
+}
 template <int NC> __device__ __forceinline__ double2 group_add(double2 v) {
-#pragma unroll
-    for (int o = NC; o < 64; o *= 2) {
-        v.x += __shfl_xor(v.x, o, 64);
-        v.y += __shfl_xor(v.y, o, 64);
-    }
+    if constexpr (NC < 64) v = make_double2(half_add(v.x), half_add(v.y));
+    if constexpr (NC < 32)
+        v = make_double2(row_pair(v.x, false) + row_pair(v.x, true), row_pair(v.y, false) + row_pair(v.y, true));
     return v;
 }
 
-// Visits the registers r of the rows i = g + G r >= lo with f(r, v), v the pivot
-// column's entry of V there; a register none of whose rows is live is skipped
-// eight at a time, and rows above lo get v = 0.
-template <int NC, int NT, int RT, typename F>
-__device__ __forceinline__ void reg_rows(const double2 (&V)[RT], int j, int lo, F f) {
-    constexpr int G = NT / NC, CH = RT < QR_CH ? RT : QR_CH;
+// p = 0 in the rows i = g + G r < lo (lo <= NC, so only the first registers have any).
+template <int NC, int NT, int RT>
+__device__ __forceinline__ void reg_mask(double2 (&p)[RT], int lo) {
+    constexpr int G = NT / NC;
     const int g = threadIdx.x / NC;
 #pragma unroll
-    for (int c = 0; c < RT; c += CH) {
-        if (G * (c + CH) <= lo) continue;  // the same in every thread
-        if (G * c >= lo) {
-#pragma unroll
-            for (int r = c; r < c + CH; ++r) f(r, column<NC>(V[r], j));
-        } else {
-#pragma unroll
-            for (int r = c; r < c + CH; ++r) {
-                const double2 v = column<NC>(V[r], j);
-                const bool live = g + G * r >= lo;
-                f(r, make_double2(live ? v.x : 0.0, live ? v.y : 0.0));
-            }
+    for (int r = 0; r < RT; ++r)
+        if (r * G < NC) {
+            const bool live = g + G * r >= lo;
+            p[r] = make_double2(live ? p[r].x : 0.0, live ? p[r].y : 0.0);
         }
-    }
 }
 
-// sum_i conj(p_i) y_i over the wave's rows i >= lo, p = column j of V.
-template <int NC, int NT, int RT>
-__device__ __forceinline__ double2 reg_dot(const double2 (&V)[RT], const double2 (&Y)[RT], int j, int lo) {
+// sum_i conj(p_i) y_i over the wave's rows.
+template <int NC, int RT>
+__device__ __forceinline__ double2 reg_dot(const double2 (&p)[RT], const double2 (&Y)[RT]) {
     double2 s[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-    reg_rows<NC, NT, RT>(V, j, lo, [&](int r, double2 v) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
         double2 &a = s[r & 1];
-        a.x = fma(v.x, Y[r].x, a.x);
-        a.y = fma(v.x, Y[r].y, a.y);
-        a.x = fma(v.y, Y[r].y, a.x);
-        a.y = fma(-v.y, Y[r].x, a.y);
-    });
+        a.x = fma(p[r].x, Y[r].x, a.x);
+        a.y = fma(p[r].x, Y[r].y, a.y);
+        a.x = fma(p[r].y, Y[r].y, a.x);
+        a.y = fma(-p[r].y, Y[r].x, a.y);
+    }
     return group_add<NC>(make_double2(s[0].x + s[1].x, s[0].y + s[1].y));
 }
 
-// y_i -= p_i u over the rows i >= lo.
-template <int NC, int NT, int RT>
-__device__ __forceinline__ void reg_take(const double2 (&V)[RT], double2 (&Y)[RT], int j, int lo, double2 u) {
-    reg_rows<NC, NT, RT>(V, j, lo, [&](int r, double2 v) {
-        Y[r].x = fma(-v.x, u.x, Y[r].x);
-        Y[r].y = fma(-v.x, u.y, Y[r].y);
-        Y[r].x = fma(v.y, u.y, Y[r].x);
-        Y[r].y = fma(-v.y, u.x, Y[r].y);
-    });
+// y_i -= p_i u.
+template <int RT>
+__device__ __forceinline__ void reg_take(const double2 (&p)[RT], double2 (&Y)[RT], double2 u) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        Y[r].x = fma(-p[r].x, u.x, Y[r].x);
+        Y[r].y = fma(-p[r].x, u.y, Y[r].y);
+        Y[r].x = fma(p[r].y, u.y, Y[r].x);
+        Y[r].y = fma(-p[r].y, u.x, Y[r].y);
+    }
 }
 
 // Householder steps on X; the lanes of column j end with R[j][j] in beta, tau_j
@@ -442,7 +506,10 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
     int pb = 0, ups = 0;
     for (int j = 0; j < kmax;) {
         pb ^= 1;
-        const double2 part = reg_dot<NC, NT, RT>(X, X, j, j + 1);
+        double2 p[RT];
+        pivot_column<NC>(X, j, p);
+        reg_mask<NC, NT>(p, j + 1);
+        const double2 part = reg_dot<NC>(p, X);
         if ((threadIdx.x & 63) < NC) sh.part[pb][w][col] = part;
         const int rj = j / G;  // the pivot row's register
         double2 mine = make_double2(0.0, 0.0);
@@ -452,15 +519,17 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
         if (g == j % G) sh.row[pb][col] = mine;
         __syncthreads();
         double2 dot = make_double2(0.0, 0.0);
+        double s = 0.0;
 #pragma unroll
         for (int q = 0; q < NT / 64; ++q) {
-            const double2 p = sh.part[pb][q][col];
-            dot.x += p.x;
-            dot.y += p.y;
+            const double2 d = sh.part[pb][q][col];
+            dot.x += d.x;
+            dot.y += d.y;
+            s += sh.part[pb][q][j].x;
         }
         const double2 xj = sh.row[pb][col], alpha = sh.row[pb][j];
         const double a2 = alpha.x * alpha.x + alpha.y * alpha.y;
-        const double s = column<NC>(dot, j).x + a2;
+        s += a2;
         // s is the same in every thread, and so is every branch on it
         if (s < HH_SMALL2) {
             if (ups < 3) {
@@ -474,11 +543,13 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
             }
             continue;
         }
-        const double is = rsqrt(s), sigma = s * is;
-        const double ia = a2 > 0.0 ? rsqrt(a2) : 0.0, d = a2 * ia + sigma, id = 1.0 / d;
+        // an alpha below the rounding of sigma counts as zero (its square may be denormal)
+        const bool some = a2 > s * 0x1p-106;
+        const double is = rsqrt3(s), sigma = s * is;
+        const double ia = some ? rsqrt3(a2) : 0.0, d = a2 * ia + sigma, id = recip(d);
         // u = tau conj(f) v^H x_c with v^H x_c = x_jc + f sum_{i > j} conj(x_ij) x_ic:
         // tau |f|^2 = 1 / (sigma d), tau conj(f) = conj(ph) / sigma
-        const double2 ph = make_double2(a2 > 0.0 ? alpha.x * ia : 1.0, alpha.y * ia);
+        const double2 ph = make_double2(some ? alpha.x * ia : 1.0, alpha.y * ia);
         const double isd = is * id;
         const double2 px = cmulc(ph, xj);
         const double2 u = make_double2(col > j ? fma(px.x, is, dot.x * isd) : 0.0,
@@ -489,15 +560,14 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
             tau = d * is;
             fac = make_double2(ph.x * id, ph.y * id);
         }
-        const bool own = col == j && g == j % G;  // the reflector's first entry
 #pragma unroll
         for (int r = 0; r < RT; ++r)
-            if (r * G < NC) {
-                const bool at = own && r == rj;
-                X[r].x = at ? ph.x * d : X[r].x;
-                X[r].y = at ? ph.y * d : X[r].y;
+            if (r * G < NC) {  // the reflector's first entry
+                const bool first = g == j % G && r == rj, at = first && col == j;
+                p[r] = make_double2(first ? ph.x * d : p[r].x, first ? ph.y * d : p[r].y);
+                X[r] = make_double2(at ? ph.x * d : X[r].x, at ? ph.y * d : X[r].y);
             }
-        reg_take<NC, NT, RT>(X, X, j, j, u);
+        reg_take(p, X, u);
         ups = 0;
         ++j;
     }
@@ -514,17 +584,20 @@ __device__ __forceinline__ void reg_apply(double2 (&Y)[RT], const double2 (&V)[R
         const double tj = column<NC>(make_double2(t2, 0.0), j).x;
         if (__builtin_amdgcn_readfirstlane(tj == 0.0)) continue;  // the same in every thread
         pb ^= 1;
-        const double2 part = reg_dot<NC, NT, RT>(V, Y, j, j);
+        double2 p[RT];
+        pivot_column<NC>(V, j, p);
+        reg_mask<NC, NT>(p, j);
+        const double2 part = reg_dot<NC>(p, Y);
         if ((threadIdx.x & 63) < NC) sh.part[pb][w][col] = part;
         __syncthreads();
         double2 ws = make_double2(0.0, 0.0);
 #pragma unroll
         for (int q = 0; q < NT / 64; ++q) {
-            const double2 p = sh.part[pb][q][col];
-            ws.x += p.x;
-            ws.y += p.y;
+            const double2 d = sh.part[pb][q][col];
+            ws.x += d.x;
+            ws.y += d.y;
         }
-        reg_take<NC, NT, RT>(V, Y, j, j, make_double2(tj * ws.x, tj * ws.y));
+        reg_take(p, Y, make_double2(tj * ws.x, tj * ws.y));
     }
 }
 
@@ -627,23 +700,20 @@ __global__ void __launch_bounds__(NT, NT / 256) k_qr_reg_form(FormArgs f) {
     reg_store_q<NC, NT, RT>(f, Y, r0, len, wb);
 }
 
-// One level of the tree: columns rounded up to 16, 32 or 64 lanes, the registers
-// of 128 rows or of at most QR_REG_FEW.
+// One level of the tree: columns rounded up to 16, 32 or 64 lanes, registers for
+// blocks of at most 32, 64 or 128 rows.
+template <int NC, int NT, int ROWS> void launch_reg_rows(const LeafArgs *a, const FormArgs &f, dim3 g, hipStream_t s) {
+    constexpr int R = ROWS * NC / NT;
+    const dim3 b(NT);
+    if (!a) hipLaunchKernelGGL((k_qr_reg_form<NC, NT, R>), g, b, 0, s, f);
+    else if (a->top) hipLaunchKernelGGL((k_qr_reg<NC, NT, R, true>), g, b, 0, s, *a, f);
+    else hipLaunchKernelGGL((k_qr_reg<NC, NT, R, false>), g, b, 0, s, *a, f);
+}
 template <int NC, int NT> void launch_reg_level(const LeafArgs *a, const FormArgs &f, int rows_per_block, dim3 g,
                                                 hipStream_t s) {
-    constexpr int R = QR_REG_ROWS * NC / NT, F = QR_REG_FEW * NC / NT;
-    const dim3 b(NT);
-    const bool few = rows_per_block <= QR_REG_FEW;
-    if (!a) {
-        if (few) hipLaunchKernelGGL((k_qr_reg_form<NC, NT, F>), g, b, 0, s, f);
-        else hipLaunchKernelGGL((k_qr_reg_form<NC, NT, R>), g, b, 0, s, f);
-    } else if (a->top) {
-        if (few) hipLaunchKernelGGL((k_qr_reg<NC, NT, F, true>), g, b, 0, s, *a, f);
-        else hipLaunchKernelGGL((k_qr_reg<NC, NT, R, true>), g, b, 0, s, *a, f);
-    } else {
-        if (few) hipLaunchKernelGGL((k_qr_reg<NC, NT, F, false>), g, b, 0, s, *a, f);
-        else hipLaunchKernelGGL((k_qr_reg<NC, NT, R, false>), g, b, 0, s, *a, f);
-    }
+    if (rows_per_block <= 32) launch_reg_rows<NC, NT, 32>(a, f, g, s);
+    else if (rows_per_block <= 64) launch_reg_rows<NC, NT, 64>(a, f, g, s);
+    else launch_reg_rows<NC, NT, QR_REG_ROWS>(a, f, g, s);
 }
 
 void launch_reg(const LeafArgs *a, const FormArgs &f, int n, int rows_per_block, dim3 g, hipStream_t s) {
@@ -801,19 +871,6 @@ __device__ __forceinline__ void acc_store(const CAcc &c, CMat<LD> M, int r0, int
     }
 }
 
-// 1 / sqrt(d) for d > 0 in the normal range: the hardware estimate r and one step of
-// third order, r (1 + y / 2 + 3 y^2 / 8) with y = 1 - d r^2.
-__device__ __forceinline__ double rsqrt3(double d) {
-    const double r = __builtin_amdgcn_rsq(d);
-    const double y = fma(-d * r, r, 1.0);
-    return fma(r * y, fma(y, 0.375, 0.5), r);
-}
-// Lane K of each row of 16 lanes, to the whole row.
-template <int K> __device__ __forceinline__ double row_lane(double v) {
-    const int2 a = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(a.x, 0x150 + K, 0xf, 0xf, false),
-                                                __builtin_amdgcn_mov_dpp(a.y, 0x150 + K, 0xf, 0xf, false)));
-}
 // out[a] = lane 16 a + x of v, in every lane (x = lane % 16): swaps of half waves,
 // then of rows of 16 lanes.
 __device__ __forceinline__ void rows4(double v, double (&out)[4]) {
