@@ -136,7 +136,7 @@ void qr_left(Engine &E, const Ten &T, int nb, Ten &Q, Ten *R, bool well_conditio
     a.Q = Q.p; a.q_esz = Q.esz; a.q_bs = m * k; a.q_rs = k; a.q_cs = 1; a.q_conj = 0;
     a.R = R ? R->p : nullptr; a.r_esz = T.esz; a.r_bs = k * n; a.r_rs = n; a.r_cs = 1; a.r_conj = 0;
     // the fit needs only an orthonormal basis of the column space
-    if (R && !well_conditioned) E.qr(a);
+    if (R && !well_conditioned) E.factor(a);
     else E.orthonormalise(a);
 }
 
@@ -168,7 +168,7 @@ void lq_right(Engine &E, const Ten &T, int nb, Ten &Q, Ten *Lf, bool well_condit
     a.A = T.p; a.a_esz = T.esz; a.a_bs = m * n; a.a_rs = 1; a.a_cs = n; a.a_conj = 1;
     a.Q = Q.p; a.q_esz = Q.esz; a.q_bs = k * n; a.q_rs = 1; a.q_cs = n; a.q_conj = 1;
     a.R = Lf ? Lf->p : nullptr; a.r_esz = T.esz; a.r_bs = m * k; a.r_rs = 1; a.r_cs = k; a.r_conj = 1;
-    if (Lf && !well_conditioned) E.qr(a);
+    if (Lf && !well_conditioned) E.factor(a);
     else E.orthonormalise(a);
 }
 

@@ -1181,6 +1181,26 @@ static Op view(void *p, const std::string &idx, std::vector<int> dims, std::vect
     return o;
 }
 
+// Tall matrices with R that may have any rank (the rows of the exact product): the
+// register tree walks 128 rows a level, one block after another on a lone path,
+// while the CholeskyQR passes spread over the chip; an item whose Gram matrix says
+// that it is rank-deficient goes through the tree after all.  4096 x 64: 1435 us by
+// the tree, 183 by the passes (24 of it the tree's launches that find no flag); 512 x 32
+// 253 and 82; up to 16 columns or in one block of the tree it is as fast or faster.
+void Engine::factor(const tnk::QrArgs &a) {
+    if (keep_sums || householder_only || !a.R || a.n <= 16 || a.n > 64 || a.m <= 128) {
+        qr(a);
+        return;
+    }
+    qr_shapes_["factor m=" + std::to_string(a.m) + " n=" + std::to_string(a.n) + " batch=" + std::to_string(a.batch)] += 1;
+    try {
+        ortho_impl(a, false, true);
+    } catch (const TnError &e) {
+        if (e.code != ST_OOM) throw;
+        qr(a);  // it needs less scratch
+    }
+}
+
 void Engine::orthonormalise(const tnk::QrArgs &a) {
     const int m = a.m, n = a.n, Z = a.batch;
     {
@@ -1198,7 +1218,7 @@ void Engine::orthonormalise(const tnk::QrArgs &a) {
 // CholeskyQR3 (n <= 64) or the blocked scheme (n > 64) behind orthonormalise;
 // with householder_blocks the blocks of the wide case are factored by
 // Householder TSQR (exact for rank-deficient input) instead of CholeskyQR3.
-void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
+void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_rank) {
     const int m = a.m, n = a.n, Z = a.batch;
     const int saved = prec;
     const bool nested = in_qr_;  // a block of a wider orthonormalisation
@@ -1221,9 +1241,19 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
         // Numerically rank-deficient items (a pivot clamped: the passes cannot
         // complete a basis from dependent columns) are refactored by Householder,
         // which returns orthonormal columns for any rank; the others skip it.
+        // In one launch, slow for a tall matrix, where that is not expected; in the
+        // launches of the register tree where it may well be (any_rank).
         auto fallback = [&](int *flags) {
-            void *ws = raw(tnk::qr_fallback_workspace_bytes(m, n, Z));
-            TN_HIP(tnk::launch_qr_fallback(a, flags, ws, s));
+            void *ws = raw(any_rank ? tnk::qr_workspace_bytes(m, n, Z, 0)
+                                         : tnk::qr_fallback_workspace_bytes(m, n, Z));
+            if (any_rank) {
+                tnk::QrArgs h = a;
+                h.keep_sums = 0;
+                h.only_if = flags;
+                TN_HIP(tnk::launch_qr(h, ws, s));
+            } else {
+                TN_HIP(tnk::launch_qr_fallback(a, flags, ws, s));
+            }
             unraw(ws);
             unraw(flags);
         };
@@ -1238,6 +1268,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
             // factorisation; a last row launch writes Q = X_2 R_3^{-1}.
             const int rb = tnk::cqr_rows_per_block(m);
             const int nblk = (m + rb - 1) / rb;
+            const bool factors = a.R && !any_rank;
             tmp.push_back(make({Z, m, n}, 16));        // X_1 = A R_1^{-1}
             tmp.push_back(make({Z, m, n}, 16));        // X_2 = X_1 R_2^{-1}
             tmp.push_back(make({Z, nblk, n, n}, 16));  // partial Gram matrices
@@ -1246,7 +1277,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
             Ten &X1 = tmp[0], &X2 = tmp[1], &Pg = tmp[2], &Ri = tmp[3], &G = tmp[4];
             // with R requested: the passes factor R_1, R_2, R_3 (A = Q R_3 R_2 R_1)
             const size_t r0 = tmp.size();
-            if (a.R)
+            if (factors)
                 for (int i = 0; i < 3; ++i) tmp.push_back(make({Z, n, n}, 16));
             // a clamped pivot in any pass flags the item for the Householder fallback
             int *flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
@@ -1264,6 +1295,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
                 if (pass == 1) c.X = reinterpret_cast<double *>(X1.p);
                 if (pass == 2) c.X = reinterpret_cast<double *>(X2.p);
                 if (pass == 3) {
+                    if (a.R && any_rank) c.X = reinterpret_cast<double *>(X1.p);  // Q in full precision, for R
                     c.dst = a.Q; c.d_esz = a.q_esz; c.d_bs = a.q_bs; c.d_rs = a.q_rs; c.d_cs = a.q_cs;
                     c.d_conj = a.q_conj;
                 } else {
@@ -1277,12 +1309,25 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks) {
                                              reinterpret_cast<double *>(G.p), s));
                 TN_HIP(tnk::launch_chol_inv(reinterpret_cast<const double *>(G.p), n, Z, shift, clamp,
                                             reinterpret_cast<double *>(Ri.p),
-                                            a.R ? reinterpret_cast<double *>(tmp[r0 + pass].p) : nullptr, flags,
+                                            factors ? reinterpret_cast<double *>(tmp[r0 + pass].p) : nullptr, flags,
                                             pass == 0, s));
             }
-            if (a.R) {
+            if (factors) {
                 contract(op(tmp[r0 + 2], "bij"), op(tmp[r0 + 1], "bjk"), op(G, "bik"));
                 contract(op(G, "bij"), op(tmp[r0], "bjk"), op(Ri, "bik"));
+            } else if (a.R) {
+                // R = Q^H A: what Q misses of A's range is u ||A|| for any condition
+                // number (the product of the passes' factors carries u cond(A) ||A||
+                // of their inverses)
+                Op Aop = view(const_cast<void *>(a.A), "bij", {Z, m, n}, {a.a_bs, a.a_rs, a.a_cs}, a.a_conj != 0);
+                if (a.a_esz != 16) {
+                    TN_HIP(tnk::launch_strided_copy(a.A, a.a_esz, a.a_bs, a.a_rs, a.a_cs, X2.p, 16, (int64_t)m * n, n, 1,
+                                                    m, n, Z, a.a_conj, s));
+                    Aop = op(X2, "bij");
+                }
+                contract(op(X1, "bik", true), Aop, op(Ri, "bkj"));
+            }
+            if (a.R) {
                 TN_HIP(tnk::launch_strided_copy(Ri.p, 16, (int64_t)n * n, n, 1, a.R, a.r_esz, a.r_bs, a.r_rs, a.r_cs, n,
                                                 n, Z, a.r_conj, s));
             }

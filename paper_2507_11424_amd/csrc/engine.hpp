@@ -196,8 +196,11 @@ class Engine {
     void group_run(Group &g);
     void group_free(Group &g);
 
-    // Reduced QR (FP64) of `batch` matrices; see tnk::QrArgs.
+    // Reduced QR (FP64) of `batch` matrices, by Householder; see tnk::QrArgs.
     void qr(const tnk::QrArgs &a);
+    // Q with orthonormal columns and R with A = Q R to rounding, for any rank: by qr,
+    // or by CholeskyQR3 with R = Q^H A (upper triangular up to rounding only).
+    void factor(const tnk::QrArgs &a);
     // Orthonormal Q for m >= n (else Householder): shifted CholeskyQR3 in
     // FP64 -- three passes of Gram matrix (MFMA), Cholesky and R^{-1} (one
     // workgroup), Q <- Q R^{-1} (MFMA); the first pass adds the shift
@@ -210,7 +213,7 @@ class Engine {
     // columns, each orthogonalised against the previous ones by three passes of
     // block Gram-Schmidt before its CholeskyQR3.
     void orthonormalise(const tnk::QrArgs &a);
-    void ortho_impl(const tnk::QrArgs &a, bool householder_blocks);
+    void ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_rank = false);
     // norm2 per batch item into dev[batch]; normalise in place; logscale +=.
     void norm2(const void *x, int e, int64_t n, int batch, int64_t bs, double *out);
     void normalise(void *x, int e, int64_t n, int batch, int64_t bs, double *logscale, bool acc,

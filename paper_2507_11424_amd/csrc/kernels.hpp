@@ -108,6 +108,7 @@ struct QrArgs {
     void *Q; int q_esz; int64_t q_bs, q_rs, q_cs; int q_conj;
     void *R; int r_esz; int64_t r_bs, r_rs, r_cs; int r_conj;
     int keep_sums;
+    const int *only_if;  // optional [batch]: only the items whose flag has bit 4 set (n <= 64, not with keep_sums)
 };
 size_t qr_workspace_bytes(int m, int n, int batch, int keep_sums);
 hipError_t launch_qr(const QrArgs &a, void *workspace, hipStream_t s);

@@ -229,6 +229,7 @@ struct LeafArgs {
     char *ws; int64_t ws_bs;  // workspace base and per-batch stride (bytes)
     size_t v_off, t_off, b_off, rs_off;
     MatOut R; int want_r;    // top only: k x n
+    const int *only_if;      // see QrArgs (register kernels)
 };
 
 __global__ void __launch_bounds__(QR_NT) k_qr_leaf(LeafArgs a) {
@@ -290,6 +291,7 @@ struct FormArgs {
     char *ws; int64_t ws_bs;
     size_t v_off, t_off, b_off, x_off, q_off;  // x_off: parent Q ((nb n) x k), q_off: this level's Q
     MatOut out;                          // level 0 destination
+    const int *only_if;                  // see QrArgs (register kernels)
 };
 
 __global__ void __launch_bounds__(QR_NT) k_qr_form(FormArgs a) {
@@ -623,6 +625,7 @@ __global__ void __launch_bounds__(NT, NT / 256) k_qr_reg(LeafArgs a, FormArgs f)
     __shared__ QrRegShared<NC, NT> sh;
     constexpr int G = NT / NC;
     const int blk = blockIdx.x, bt = blockIdx.y, n = a.n;
+    if (a.only_if && !(a.only_if[bt] & 4)) return;  // uniform over the block
     const int col = threadIdx.x % NC, g = threadIdx.x / NC;
     const int r0 = (int)(((int64_t)blk * a.rows) / a.nb);
     const int r1 = (int)(((int64_t)(blk + 1) * a.rows) / a.nb);
@@ -679,6 +682,7 @@ __global__ void __launch_bounds__(NT, NT / 256) k_qr_reg_form(FormArgs f) {
     __shared__ QrRegShared<NC, NT> sh;
     constexpr int G = NT / NC;
     const int blk = blockIdx.x, n = f.n, k = f.k;
+    if (f.only_if && !(f.only_if[blockIdx.y] & 4)) return;  // uniform over the block
     const int col = threadIdx.x % NC, g = threadIdx.x / NC;
     const int r0 = (int)(((int64_t)blk * f.rows) / f.nb);
     const int r1 = (int)(((int64_t)(blk + 1) * f.rows) / f.nb);
@@ -1511,6 +1515,7 @@ size_t qr_workspace_bytes(int m, int n, int batch, int keep_sums) {
 hipError_t launch_qr(const QrArgs &q, void *workspace, hipStream_t s) {
     const int m = q.m, n = q.n;
     if (m <= 0 || n <= 0 || q.batch <= 0) return hipSuccess;
+    if (q.only_if && !use_reg(n, q.keep_sums)) return hipErrorInvalidValue;
     const int k = m < n ? m : n;
     char *ws = reinterpret_cast<char *>(workspace);
     MatDesc in{q.A, q.a_esz, q.a_bs, q.a_rs, q.a_cs, q.a_conj};
@@ -1546,6 +1551,7 @@ hipError_t launch_qr(const QrArgs &q, void *workspace, hipStream_t s) {
         f.x_off = f.top ? 0 : lv[L + 1].q_off;
         f.q_off = lv[L].q_off;
         f.out = qo;
+        f.only_if = q.only_if;
         return f;
     };
     for (size_t L = 0; L < lv.size(); ++L) {
@@ -1556,6 +1562,7 @@ hipError_t launch_qr(const QrArgs &q, void *workspace, hipStream_t s) {
         a.ws = ws; a.ws_bs = (int64_t)per;
         a.v_off = lv[L].v_off; a.t_off = lv[L].t_off; a.b_off = lv[L].b_off; a.rs_off = lv[L].rs_off;
         a.R = ro; a.want_r = (q.R != nullptr);
+        a.only_if = q.only_if;
         if (use_reg(n, q.keep_sums)) {
             launch_reg(&a, form_of((int)L), n, (lv[L].rows + lv[L].nb - 1) / lv[L].nb, dim3(lv[L].nb, q.batch), s);
         } else {
