@@ -1448,7 +1448,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_
 }
 
 void Engine::norm2(const void *x, int e, int64_t n, int batch, int64_t bs, double *out) {
-    const int P = tnk::reduce_partial_count(n);
+    const int P = tnk::reduce_partial_count(n, e, false);
     void *w = pool_.get((size_t)P * batch * 8);
     TN_HIP(tnk::launch_norm2(x, e, n, batch, bs, reinterpret_cast<double *>(w), out, s));
     pool_.put(w);
@@ -1456,14 +1456,15 @@ void Engine::norm2(const void *x, int e, int64_t n, int batch, int64_t bs, doubl
 
 void Engine::normalise(void *x, int e, int64_t n, int batch, int64_t bs, double *logscale, bool acc,
                        int *flags) {
-    void *q = pool_.get((size_t)tnk::reduce_partial_count(n) * batch * 8);
-    TN_HIP(tnk::launch_normalise(x, e, n, batch, bs, reinterpret_cast<double *>(q), logscale, acc ? 1 : 0, flags, s));
+    void *q = pool_.get((size_t)tnk::reduce_partial_count(n, e, keep_sums) * batch * 8);
+    TN_HIP(tnk::launch_normalise(x, e, n, batch, bs, reinterpret_cast<double *>(q), logscale, acc ? 1 : 0, flags,
+                                 keep_sums, s));
     pool_.put(q);
 }
 
 void Engine::dot(const void *x, const void *y, int e, int64_t n, int batch, int64_t bs, double *out,
                  const int *mask, int mask_skip) {
-    const int P = tnk::reduce_partial_count(n);
+    const int P = tnk::reduce_partial_count(n, e, false);
     void *w = pool_.get((size_t)P * batch * 16);
     TN_HIP(tnk::launch_dot(x, y, e, n, batch, bs, reinterpret_cast<double *>(w), out, s, mask, mask_skip));
     pool_.put(w);

@@ -191,8 +191,9 @@ hipError_t launch_strided_copy(const void *in, int ie, int64_t ibs, int64_t irs,
 // ---------------------------------------------------------------- small kernels
 // out[b] = sum |x[b][i]|^2 over n complex elements (FP64 accumulation), batch
 // stride `bs`.  Deterministic two-level reduction; partial needs
-// reduce_partial_count(n) * batch doubles.
-int reduce_partial_count(int64_t n);
+// reduce_partial_count * batch doubles.  keep: few parts, summed in an order that
+// does not depend on the alignment (see Engine::keep_sums).
+int reduce_partial_count(int64_t n, int esz, bool keep);
 hipError_t launch_norm2(const void *x, int esz, int64_t n, int batch, int64_t bs,
                         double *partial, double *out, hipStream_t s);
 // With q = sum |x[b][i]|^2: x[b] *= 1/sqrt(q); logscale[b] (+)= 0.5 log(q); if q is not
@@ -200,7 +201,7 @@ hipError_t launch_norm2(const void *x, int esz, int64_t n, int batch, int64_t bs
 // launch_norm2.
 hipError_t launch_normalise(void *x, int esz, int64_t n, int batch, int64_t bs,
                             double *partial, double *logscale, int accumulate_log,
-                            int *flags, hipStream_t s);
+                            int *flags, bool keep, hipStream_t s);
 // Element-type conversion / copy (c128 <-> c64), n complex elements.
 hipError_t launch_convert(const void *src, int src_esz, void *dst, int dst_esz, int64_t n,
                           hipStream_t s);

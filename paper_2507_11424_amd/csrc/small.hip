@@ -80,6 +80,40 @@ __global__ void __launch_bounds__(NT) k_norm2_part(const void *x, int esz, int64
     if (threadIdx.x == 0) partial[(int64_t)b * P + blockIdx.x] = s;
 }
 
+// f(v) for the 16-byte words v of the item's n elements (two complex64, or one
+// complex128) that fall to this thread, two loads of L words in flight: what a long
+// reduction needs to reach HBM's rate, together with 16 KiB a workgroup at most until
+// there are 256 of them.  Two vectors of 8 x 131072 complex64: 3.1 us, by single
+// elements in 8 x 8 workgroups 20.8; 8 x 4194304 88 (6.1 TB/s) and 105.
+template <typename L, typename F>
+__device__ inline void for_words(int64_t words, int P, L l, F f) {
+    const int64_t st = (int64_t)P * NT;
+    int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    for (; i + st < words; i += 2 * st) {
+        const auto a = l(i), b = l(i + st);
+        f(a);
+        f(b);
+    }
+    if (i < words) f(l(i));
+}
+template <int ESZ>
+__global__ void __launch_bounds__(NT) k_norm2_words(const void *x, int64_t n, int64_t bs, int P, double *partial) {
+    const int b = blockIdx.y;
+    const float4 *xb = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(x) + (int64_t)b * bs * ESZ);
+    double s = 0.0;
+    for_words(n * ESZ / 16, P, [&](int64_t i) { return xb[i]; }, [&](float4 v) {
+        if constexpr (ESZ == 8) {
+            s += (double)v.x * v.x + (double)v.y * v.y;
+            s += (double)v.z * v.z + (double)v.w * v.w;
+        } else {
+            const double2 d = __builtin_bit_cast(double2, v);
+            s += d.x * d.x + d.y * d.y;
+        }
+    });
+    s = bsum(s);
+    if (threadIdx.x == 0) partial[(int64_t)b * P + blockIdx.x] = s;
+}
+
 __global__ void __launch_bounds__(NT) k_sum_parts(const double *partial, int P, double *out) {
     const int b = blockIdx.x;
     const double s = parts_sum(partial + (int64_t)b * P, P, 1);
@@ -202,6 +236,36 @@ __global__ void __launch_bounds__(NT) k_dot_part(const void *x, const void *y, i
     sr = bsum(sr);
     si = bsum(si);
     if (threadIdx.x == 0) {  // (one part per item is the result itself)
+        partial[((int64_t)b * P + blockIdx.x) * 2] = sr;
+        partial[((int64_t)b * P + blockIdx.x) * 2 + 1] = si;
+    }
+}
+
+template <int ESZ>
+__global__ void __launch_bounds__(NT) k_dot_words(const void *x, const void *y, int64_t n, int64_t bs, int P,
+                                                 double *partial, const int *mask, int mask_skip) {
+    const int b = blockIdx.y;
+    if (mask && mask[b] == mask_skip) return;
+    const float4 *xb = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(x) + (int64_t)b * bs * ESZ);
+    const float4 *yb = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(y) + (int64_t)b * bs * ESZ);
+    struct Pair { float4 a, c; };
+    double sr = 0.0, si = 0.0;
+    auto add = [&](double ax, double ay, double cx, double cy) {
+        sr += ax * cx - ay * cy;
+        si += ax * cy + ay * cx;
+    };
+    for_words(n * ESZ / 16, P, [&](int64_t i) { return Pair{xb[i], yb[i]}; }, [&](const Pair &v) {
+        if constexpr (ESZ == 8) {
+            add(v.a.x, v.a.y, v.c.x, v.c.y);
+            add(v.a.z, v.a.w, v.c.z, v.c.w);
+        } else {
+            const double2 a = __builtin_bit_cast(double2, v.a), c = __builtin_bit_cast(double2, v.c);
+            add(a.x, a.y, c.x, c.y);
+        }
+    });
+    sr = bsum(sr);
+    si = bsum(si);
+    if (threadIdx.x == 0) {
         partial[((int64_t)b * P + blockIdx.x) * 2] = sr;
         partial[((int64_t)b * P + blockIdx.x) * 2 + 1] = si;
     }
@@ -528,23 +592,40 @@ int grid_for(int64_t n) {
 
 }  // namespace
 
-int reduce_partial_count(int64_t n) {
-    int64_t p = (n + 16383) / 16384;
+int reduce_partial_count(int64_t n, int esz, bool keep) {
+    int64_t p;
+    if (keep) p = (n + 16383) / 16384;
+    // one part, one launch; beyond, the second launch (3 us) pays for the spread
+    else p = n <= 8192 ? 1 : (n * esz / 16 + 4 * NT - 1) / (4 * NT);
     if (p < 1) p = 1;
     if (p > 256) p = 256;
     return (int)p;
 }
 
+// Whether 16-byte words tile every item of x.
+static bool whole_words(const void *x, int esz, int64_t n, int64_t bs) {
+    return esz == 16 || (reinterpret_cast<uintptr_t>(x) % 16 == 0 && n % 2 == 0 && bs % 2 == 0);
+}
+
+static void norm2_parts(const void *x, int esz, int64_t n, int batch, int64_t bs, int P, bool keep, double *partial,
+                        hipStream_t s) {
+    const dim3 g(P, batch);
+    if (P == 1 || keep || !whole_words(x, esz, n, bs))
+        hipLaunchKernelGGL(k_norm2_part, g, dim3(NT), 0, s, x, esz, n, bs, P, partial);
+    else if (esz == 8) hipLaunchKernelGGL(k_norm2_words<8>, g, dim3(NT), 0, s, x, n, bs, P, partial);
+    else hipLaunchKernelGGL(k_norm2_words<16>, g, dim3(NT), 0, s, x, n, bs, P, partial);
+}
+
 hipError_t launch_norm2(const void *x, int esz, int64_t n, int batch, int64_t bs, double *partial,
                         double *out, hipStream_t s) {
-    const int P = reduce_partial_count(n);
-    hipLaunchKernelGGL(k_norm2_part, dim3(P, batch), dim3(NT), 0, s, x, esz, n, bs, P, P > 1 ? partial : out);
+    const int P = reduce_partial_count(n, esz, false);
+    norm2_parts(x, esz, n, batch, bs, P, false, P > 1 ? partial : out, s);
     if (P > 1) hipLaunchKernelGGL(k_sum_parts, dim3(batch), dim3(NT), 0, s, partial, P, out);
     return hipGetLastError();
 }
 
 hipError_t launch_normalise(void *x, int esz, int64_t n, int batch, int64_t bs, double *partial,
-                            double *logscale, int acc, int *flags, hipStream_t s) {
+                            double *logscale, int acc, int *flags, bool keep, hipStream_t s) {
     // what one workgroup holds in registers is normalised by it alone; 32 elements a
     // thread is the line, where its load and store (3 us) weigh as much as two launches
     if (n <= 8 * NT) {
@@ -555,8 +636,8 @@ hipError_t launch_normalise(void *x, int esz, int64_t n, int batch, int64_t bs, 
         hipLaunchKernelGGL(k_normalise_one<32>, dim3(batch), dim3(NT), 0, s, x, esz, n, bs, logscale, acc, flags);
         return hipGetLastError();
     }
-    const int P = reduce_partial_count(n);
-    hipLaunchKernelGGL(k_norm2_part, dim3(P, batch), dim3(NT), 0, s, x, esz, n, bs, P, partial);
+    const int P = reduce_partial_count(n, esz, keep);
+    norm2_parts(x, esz, n, batch, bs, P, keep, partial, s);
     int g = grid_for(n);
     if (g > 512) g = 512;
     hipLaunchKernelGGL(k_normalise, dim3(g, batch), dim3(NT), 0, s, x, esz, n, bs, partial, P, logscale, acc, flags);
@@ -604,9 +685,13 @@ hipError_t launch_init_tensor(void *out, int esz, int64_t n, int batch, int64_t 
 
 hipError_t launch_dot(const void *x, const void *y, int esz, int64_t n, int batch, int64_t bs,
                       double *partial, double *out, hipStream_t s, const int *mask, int mask_skip) {
-    const int P = reduce_partial_count(n);
-    hipLaunchKernelGGL(k_dot_part, dim3(P, batch), dim3(NT), 0, s, x, y, esz, n, bs, P, P > 1 ? partial : out, mask,
-                       mask_skip);
+    const int P = reduce_partial_count(n, esz, false);
+    const dim3 g(P, batch);
+    double *to = P > 1 ? partial : out;
+    if (P == 1 || !whole_words(x, esz, n, bs) || !whole_words(y, esz, n, bs))
+        hipLaunchKernelGGL(k_dot_part, g, dim3(NT), 0, s, x, y, esz, n, bs, P, to, mask, mask_skip);
+    else if (esz == 8) hipLaunchKernelGGL(k_dot_words<8>, g, dim3(NT), 0, s, x, y, n, bs, P, to, mask, mask_skip);
+    else hipLaunchKernelGGL(k_dot_words<16>, g, dim3(NT), 0, s, x, y, n, bs, P, to, mask, mask_skip);
     if (P > 1) hipLaunchKernelGGL(k_sum_parts2, dim3(batch), dim3(NT), 0, s, partial, P, out, mask, mask_skip);
     return hipGetLastError();
 }

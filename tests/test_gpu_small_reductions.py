@@ -1,6 +1,7 @@
 """Norms, normalisation and dot products at the sizes where their launches
 change: two sites joined by one bond of dimension D, so that the reduced vectors
-have D^2 entries (2048 and 8192: one workgroup's registers; 16384: one part)."""
+have D^2 entries (2048 and 8192: one workgroup's registers; above, parts of 16-byte words
+where those tile the vector)."""
 import math
 
 import numpy as np
@@ -11,7 +12,7 @@ from peps_inputs import square_lattice
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D", [1, 45, 46, 90, 91, 128, 129])
+@pytest.mark.parametrize("D", [1, 45, 46, 90, 91, 128, 129, 600])
 @pytest.mark.parametrize("dtype,prec,tol", [("c128", "fp64", 1e-11), ("c64", "fp32", 1e-4)])
 def test_two_sites(D, dtype, prec, tol):
     import torch
