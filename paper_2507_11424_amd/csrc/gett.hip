@@ -612,7 +612,7 @@ __device__ inline void split_bf16(float x0, float x1, uint32_t *out) {
 // Bound by the splitting (vector unit) and its LDS stores, so a thread takes two
 // neighbouring k of a row at a time: one conversion and one 32-bit store for both.
 template <int NP, int BM, int BN, int WGM, int WGN>
-__global__ void __launch_bounds__(64 * WGM * WGN)
+__global__ void __launch_bounds__(64 * WGM * WGN, BN > 16 ? 1 : 4)
 gett_bf16_direct(GettArgs p) {
     constexpr int BK = 32;
     constexpr int NT = 64 * WGM * WGN;
@@ -622,8 +622,10 @@ gett_bf16_direct(GettArgs p) {
     constexpr int LB = (BK * BN) / NT;
     constexpr int KP = BK + 8;  // padded k extent (bf16 elements), keeps 16-byte alignment
     static_assert(LA >= 2 && LB >= 2 && LA % 2 == 0 && LB % 2 == 0 && NT % (BK / 2) == 0 && NT >= BM && NT >= BN, "tile");
-    // two LDS stages when they fit in the 160 KiB of a CU, else one
-    constexpr int S = (2 * 2 * NP * (BM + BN) * KP * 2 <= 160 * 1024) ? 2 : 1;
+    // two LDS stages when they fit in the 160 KiB of a CU, else one; one for the narrow
+    // tile, whose problems are long, thin and short in K: four workgroups on a CU cover
+    // for the second stage (2097152 x 16 x 64 in bf16x6 495 -> 350 us)
+    constexpr int S = BN > 16 && (2 * 2 * NP * (BM + BN) * KP * 2 <= 160 * 1024) ? 2 : 1;
     // planes: [stage][re/im][part][row][k]
     __shared__ __attribute__((aligned(16))) unsigned short sA[S][2][NP][BM][KP];
     __shared__ __attribute__((aligned(16))) unsigned short sB[S][2][NP][BN][KP];
