@@ -354,8 +354,9 @@ tn_status tn_plan_report(const tn_handle *h, int top, char *buf, size_t len);
  *   strlen(letters) entries; conjA/conjB conjugate an operand; accumulate adds;
  *   cfg >= 0 forces a tile configuration (0: 64x64, 1: 128x64, 2: 64x16,
  *   3: 128x64 on 8 waves, 4: 128x128 (packed split-BF16), 5: 32x32, 6: 64x128
- *   (split-BF16), 7: 16x16 with K shared by the waves (FP64 / FP32)) and ksplit > 0 a number of K slices, -1 / 0 = the
- *   planner's choice.  Enqueued on the handle's stream.
+ *   (split-BF16), 7: 16x16 with K shared by the waves, 8: 64x32 (both FP64 /
+ *   FP32)) and ksplit > 0 a number of K slices, -1 / 0 = the planner's choice.
+ *   Enqueued on the handle's stream.
  * tn_test_qr: reduced QR (FP64 arithmetic) of `batch` row-major m x n DEVICE
  *   matrices of element size esz (16 or 8 bytes): Q is m x k, R (optional,
  *   NULL = not formed) is k x n, k = min(m, n).  method 0: Householder;

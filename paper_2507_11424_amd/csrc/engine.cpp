@@ -566,8 +566,15 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
 // many hundreds were cut into slices of at least 256; then the tile with the most
 // work per loaded byte wins:
 //   FP64 and FP32: 64x64 on 4 waves (3M).  720896 x 128 x 128: 1546 against 2488 for
-//   128x64 with 4M, which leaves one wave per SIMD.  Outputs of up to 32 columns
-//   take 64x16 (131072 x 32 x 32 x 8: 321 for 415), of up to 32 rows 32x32 (400).
+//   128x64 with 4M, which leaves one wave per SIMD.  Up to K = 64, where loads and
+//   stores weigh as much as the products, and up to 32 columns, 64x32, of which
+//   three fit a CU for two: 4194304 x 32 x 16 834 against 1402 (64x16: 1014), 1048576
+//   x 64 x 64 710 / 824, 65536 x 96 x 32 42 / 55, 524288 x 128 x 128 1110 / 1110 (in
+//   FP32 646 / 741); 4096 x 128 x 256 x 64 1009 / 995.  Below 1024 of them 64x16 keeps
+//   up with its greater number (16384 x 32 x 64: 11.3 for 11.6), as up to 16 columns
+//   (4194304 x 16 x 16: 501); of up to 32 rows 32x32 (32 x 4096 x 512: 20 for 27).
+//   FP32 with four products has four 64x64 on a CU and needs 64x32 only for 32
+//   columns (131072 x 32 x 32 x 8: 164 for 221; 262144 x 64 x 16: 55 / 50).
 //   Split-BF16, packed (both sides above 128): 128x128 while its tiles fill the CUs
 //   (8192 x 4096 x 4096 in bf16x6: 6083 against 7344 for 128x64 on 4 waves, 6596 on
 //   8; 16384 x 256 x 512 x 8: 1101 / 1300), else 128x64 on 8 waves (512 x 4096 x
@@ -619,7 +626,9 @@ void Engine::choose_tile(Plan *P) {
     } else if (!large) {
         cfg = K <= 64 && M >= 64 ? tnk::CFG_64x16 : tnk::CFG_32x32;
     } else if (!split) {
-        cfg = N <= 32 && M >= 64 ? tnk::CFG_64x16 : M <= 32 ? tnk::CFG_32x32 : tnk::CFG_64x64;
+        if (M <= 32) cfg = tnk::CFG_32x32;
+        else if (N <= 32) cfg = tiles(tnk::CFG_64x32) >= 1024 ? tnk::CFG_64x32 : tnk::CFG_64x16;
+        else cfg = K <= 64 && !P->fp32 ? tnk::CFG_64x32 : tnk::CFG_64x64;
     } else if (P->can_pack && t64 >= 256) {
         P->pack = true;
         cfg = tiles(tnk::CFG_128x128W) >= 256 ? tnk::CFG_128x128W : tnk::CFG_128x64W;
@@ -687,8 +696,9 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
     struct Cand { int cfg, ks; bool pack; int fp32; };
     std::vector<Cand> cands;
     const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
-    const int cfgs[8] = {tnk::CFG_64x16,    tnk::CFG_64x64, tnk::CFG_128x64,   tnk::CFG_128x64W,
-                         tnk::CFG_128x128W, tnk::CFG_32x32, tnk::CFG_64x128W, tnk::CFG_16x16};
+    const int cfgs[9] = {tnk::CFG_64x16,    tnk::CFG_64x64, tnk::CFG_128x64,   tnk::CFG_128x64W,
+                         tnk::CFG_128x128W, tnk::CFG_32x32, tnk::CFG_64x128W, tnk::CFG_16x16,
+                         tnk::CFG_64x32};
     for (int pk = 0; pk < 3; ++pk) {
         const bool pack = pk == 1;
         const int f32 = pk == 2 ? 1 : 0;
@@ -698,7 +708,7 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             if ((c == tnk::CFG_128x64 || c == tnk::CFG_128x64W || c == tnk::CFG_128x128W) && P->kM < 128) continue;
             if (c == tnk::CFG_128x128W && (!pack || P->kN < 128)) continue;  // packed split-BF16 only
             if (c == tnk::CFG_64x16 && P->kN > 64) continue;
-            if (c == tnk::CFG_16x16 && bf16 && !f32) continue;  // FP64 / FP32 only
+            if ((c == tnk::CFG_16x16 || c == tnk::CFG_64x32) && bf16 && !f32) continue;  // FP64 / FP32 only
             if (c == tnk::CFG_64x128W && (!bf16 || f32 || P->kN < 128)) continue;  // split-BF16 only
             int bm = 64, bn = 64;
             tnk::gett_tile(c, prec, &bm, &bn);
@@ -953,8 +963,8 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         kprec = prec;
         if (force_cfg == tnk::CFG_128x128W && !pack)
             throw TnError(ST_UNSUPPORTED, "the 128x128 tile serves packed split-BF16 operands only");
-        if (force_cfg == tnk::CFG_16x16 && bf16)
-            throw TnError(ST_UNSUPPORTED, "the 16x16 tile serves FP64 and FP32 only");
+        if ((force_cfg == tnk::CFG_16x16 || force_cfg == tnk::CFG_64x32) && bf16)
+            throw TnError(ST_UNSUPPORTED, "the 16x16 and 64x32 tiles serve FP64 and FP32 only");
         Plan tmp = *P;  // shares the tables, owns nothing
         tmp.pack = pack;
         set_split(&tmp, force_cfg, force_ksplit);

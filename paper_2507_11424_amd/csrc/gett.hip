@@ -1152,6 +1152,7 @@ void gett_tile(int cfg, int prec, int *bm, int *bn) {
         case CFG_32x32: *bm = 32; *bn = 32; break;
         case CFG_64x128W: *bm = 64; *bn = 128; break;
         case CFG_16x16: *bm = 16; *bn = 16; break;
+        case CFG_64x32: *bm = 64; *bn = 32; break;
         default: *bm = 64; *bn = 64; break;
     }
     (void)prec;
@@ -1210,6 +1211,7 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             case CFG_128x64W: return launch_k(gett_mfma<double, 128, 64, 16, 1, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
             case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 1, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<double, GAUSS3M>(a, s);
+            case CFG_64x32: return launch_k(gett_mfma<double, 64, 32, 16, 1, 2, 2, GAUSS3M, 3>, a, 64, 32, 256, s);
             default: return hipErrorInvalidValue;
         }
     }
@@ -1221,6 +1223,7 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             case CFG_128x64W: return launch_k(gett_mfma<float, 128, 64, 16, 1, 4, 2, GAUSS3M>, a, 128, 64, 512, s);
             case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 1, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<float, GAUSS3M>(a, s);
+            case CFG_64x32: return launch_k(gett_mfma<float, 64, 32, 16, 1, 2, 2, GAUSS3M, 4>, a, 64, 32, 256, s);
             default: return hipErrorInvalidValue;
         }
     }
@@ -1232,6 +1235,7 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 2, 4, 1, false>, a, 64, 16, 256, s);
             case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 1, 2, 2, false>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<float, false>(a, s);
+            case CFG_64x32: return launch_k(gett_mfma<float, 64, 32, 8, 1, 2, 2, false, 4>, a, 64, 32, 256, s);
             default: return hipErrorInvalidValue;
         }
     }

@@ -64,8 +64,9 @@ enum GettCfg : int {
     CFG_32x32 = 5,    // 4 waves, 16x16 per wave
     CFG_64x128W = 6,  // 8 waves, 32x32 per wave (split-BF16 only)
     CFG_16x16 = 7,    // 4 or 8 waves, K shared out over them (FP64 / FP32)
-    CFG_COUNT = 8,
-    CFG_K1 = 8        // an output per thread (grouped problems with K = 1 only)
+    CFG_64x32 = 8,    // 4 waves, 32x16 per wave (FP64 / FP32)
+    CFG_COUNT = 9,
+    CFG_K1 = 9        // an output per thread (grouped problems with K = 1 only)
 };
 
 // Grouped launches (FP64): independent problems of any shapes in one kernel.

@@ -35,11 +35,13 @@ def _run(handle, prec, M, N, K, Z, order="mn", **kw):
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3", "bf16x6"])
 @pytest.mark.parametrize("M,N,K,Z", [(1, 1, 5, 1), (33, 65, 70, 2), (130, 200, 97, 1), (31, 129, 4100, 1)])
-@pytest.mark.parametrize("cfg", [5, 6])
+@pytest.mark.parametrize("cfg", [5, 6, 8])
 @pytest.mark.parametrize("ksplit", [1, 3])
 def test_new_tiles(handle, prec, M, N, K, Z, cfg, ksplit):
     if cfg == 6 and not prec.startswith("bf16"):
         pytest.skip("the 64x128 tile exists for split-BF16 only")
+    if cfg == 8 and prec.startswith("bf16"):
+        pytest.skip("the 64x32 tile exists for FP64 and FP32 only")
     _run(handle, prec, M, N, K, Z, cfg=cfg, ksplit=ksplit)
 
 
@@ -48,7 +50,8 @@ def test_new_tiles(handle, prec, M, N, K, Z, cfg, ksplit):
     (64, 16, 300, 1), (64, 17, 191, 1), (64, 17, 192, 1), (700, 40, 64, 1), (63, 40, 64, 1), (700, 40, 65, 1),
     (16384, 32, 33, 1), (16384, 33, 32, 1), (32, 16384, 40, 1), (33, 16384, 40, 1), (64, 2048, 2048, 1),
     (1024, 1024, 64, 1), (1024, 1024, 65, 2), (2000, 130, 300, 1), (130, 9000, 100, 1), (4096, 64, 1024, 1),
-    (100, 4096, 1024, 1), (2048, 2048, 40, 1)])
+    (100, 4096, 1024, 1), (2048, 2048, 40, 1), (70000, 33, 128, 1), (70000, 33, 129, 1), (70000, 32, 129, 1),
+    (33, 70000, 20, 1)])
 @pytest.mark.parametrize("order", ["mn", "nm"])
 def test_planner_choice(handle, prec, M, N, K, Z, order):
     _run(handle, prec, M, N, K, Z, order)
