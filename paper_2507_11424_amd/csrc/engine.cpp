@@ -540,7 +540,8 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
         P->desc = d.str();
     }
     auto tc = tune_cache_.find(P->key);
-    if (tc != tune_cache_.end()) {
+    const bool fp_only = tc != tune_cache_.end() && (tc->second.cfg == tnk::CFG_16x16 || tc->second.cfg == tnk::CFG_64x32);
+    if (tc != tune_cache_.end() && (!fp_only || prec == tnk::P_FP64 || prec == tnk::P_FP32 || tc->second.fp32)) {
         P->pack = P->can_pack && tc->second.pack;
         P->fp32 = (prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6) && !P->pack ? tc->second.fp32 : 0;
         set_split(P.get(), tc->second.cfg, tc->second.ks);
@@ -616,7 +617,8 @@ void Engine::choose_tile(Plan *P) {
     int cfg;
     int64_t ks = 1;
     const int64_t t16 = tiles(tnk::CFG_16x16);
-    if (!split && (t16 <= (large ? 256 : 512) || M <= 16 || N == 1)) {
+    // (the last line: a launch has less than 2^32 threads)
+    if (!split && (t16 <= (large ? 256 : 512) || ((M <= 16 || N == 1) && t16 <= 1 << 22))) {
         if (t16 < 256 && K >= 768) ks = std::min<int64_t>(256 / t16, K / 256);
         set_split(P, tnk::CFG_16x16, (int)ks);
         return;
