@@ -1256,11 +1256,11 @@ __global__ void __launch_bounds__(256) k_cqr_rows(CqrPass p) {
 // passes: Gram matrix (each wave a share of the rows, the partial sums added in
 // wave order), its factor's inverse in place, rows times inverse.  flags[b] as from
 // launch_chol_inv.  Replaces eleven launches where a matrix alone cannot fill the
-// chip: 256 x 32 takes 80 us, 32 of 128 x 16 24 (103 before), 64 x 16 19 (96).
+// chip: 256 x 32 takes 76 us, 32 of 128 x 16 24 (103 before), 64 x 16 19 (96).
 constexpr int CQR1_ROWS = 256;
 constexpr int XLD = 33;  // padded LDS row of 32 complex doubles
-template <int P>
-__global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int *flags) {
+template <int P, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) k_cqr_one(QrArgs a, double shift, int *flags) {
     extern __shared__ double2 lds[];                 // X [rows of 16][XLD]
     __shared__ double sW[2][CB * P][CLD<P>];
     __shared__ double red;
@@ -1270,7 +1270,7 @@ __global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int 
     const int x = lane & 15, q = lane >> 4;
     const int mt = (m + CB - 1) / CB;                // row tiles
     const bool by_col = a.a_cs != 1;
-    for (int e = t; e < mt * CB * NP; e += 256) {
+    for (int e = t; e < mt * CB * NP; e += 64 * NW) {
         const int r = by_col ? e % (mt * CB) : e / NP, c = by_col ? e / (mt * CB) : e % NP;
         lds[r * XLD + c] = r < m && c < n ? ld_c(a.A, a.a_esz, (int64_t)b * a.a_bs + (int64_t)r * a.a_rs +
                                                                    (int64_t)c * a.a_cs, a.a_conj)
@@ -1284,7 +1284,7 @@ __global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int 
         for (int i = 0; i < P; ++i)
 #pragma unroll
             for (int j = i; j < P; ++j) acc_zero(g[i][j]);
-        for (int r = wave; r < mt; r += 4)
+        for (int r = wave; r < mt; r += NW)
 #pragma unroll
             for (int k = 0; k < CB; k += 4) {
                 double2 v[P];
@@ -1295,7 +1295,7 @@ __global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int 
 #pragma unroll
                     for (int j = i; j < P; ++j) acc_mma(g[i][j], v[i].x, -v[i].y, v[j].x, v[j].y);
             }
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < NW; ++w) {
             if (wave == w)
 #pragma unroll
                 for (int i = 0; i < P; ++i)
@@ -1307,8 +1307,8 @@ __global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int 
             __syncthreads();
         }
         const double scale = chol_scale(W, n, NP, pass == 0 ? shift : 0.0, &red);
-        bad |= chol_blocks<P, 4, true>(W, W, (pass == 0 ? 1e-300 : 1e-14) * scale, wave, lane);
-        for (int r = wave; r < mt; r += 4) {
+        bad |= chol_blocks<P, NW, true>(W, W, (pass == 0 ? 1e-300 : 1e-14) * scale, wave, lane);
+        for (int r = wave; r < mt; r += NW) {
             CAcc y[P];
 #pragma unroll
             for (int c = 0; c < P; ++c) acc_zero(y[c]);
@@ -1330,7 +1330,7 @@ __global__ void __launch_bounds__(256, 2) k_cqr_one(QrArgs a, double shift, int 
     }
     __syncthreads();
     const bool q_col = a.q_cs != 1;
-    for (int e = t; e < m * n; e += 256) {
+    for (int e = t; e < m * n; e += 64 * NW) {
         const int r = q_col ? e % m : e / n, c = q_col ? e / m : e % n;
         st_c(a.Q, a.q_esz, (int64_t)b * a.q_bs + (int64_t)r * a.q_rs + (int64_t)c * a.q_cs, lds[r * XLD + c], a.q_conj);
     }
@@ -1411,15 +1411,18 @@ hipError_t launch_cqr_one(const QrArgs &a, double shift, int *flags, hipStream_t
     if (a.m <= 0 || a.n <= 0 || a.batch <= 0) return hipSuccess;
     if (!cqr_one_fits(a.m, a.n) || a.R || !flags) return hipErrorInvalidValue;
     const size_t lds = (size_t)((a.m + CB - 1) / CB * CB) * XLD * sizeof(double2);
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel, int nt) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)(CQR1_ROWS * XLD * sizeof(double2)));
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(256), lds, s, a, shift, flags);
+        hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(nt), lds, s, a, shift, flags);
         return hipGetLastError();
     };
-    return a.n <= 16 ? go(k_cqr_one<1>) : go(k_cqr_one<2>);
+    // two waves a SIMD once each has two row tiles or more: 256 x 32 80 -> 76 us, 64 x 32
+    // 43 -> 45
+    if (a.m <= 128) return a.n <= 16 ? go(k_cqr_one<1, 4>, 256) : go(k_cqr_one<2, 4>, 256);
+    return a.n <= 16 ? go(k_cqr_one<1, 8>, 512) : go(k_cqr_one<2, 8>, 512);
 }
 
 int cqr_rows_per_block(int m) {
