@@ -359,7 +359,7 @@ static DMps fit_double(Engine &E, const DMps &Bin, const LView &V, int r, const 
                 ident[c] = 0;
             }
             if (Le[c + 1].p) E.drop(Le[c + 1]);
-            if (square && u == 1) {
+            if (square && u == 1 && !E.keeps_order()) {
                 Le[c + 1] = t3;
                 Le[c + 1].d = {yr, t3.d[1], t3.d[3], t3.d[5]};
                 continue;

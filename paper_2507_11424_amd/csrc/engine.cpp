@@ -546,7 +546,7 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
         P->fp32 = (prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6) && !P->pack ? tc->second.fp32 : 0;
         set_split(P.get(), tc->second.cfg, tc->second.ks);
         P->tuned = true;
-    } else if (keep) {
+    } else if (keep || prec == tnk::P_BF16X3) {  // see keeps_order
         int cfg;
         if (kN <= 16) cfg = tnk::CFG_64x16;
         else if (kM >= 8192 && kN >= 128 && K >= 16) cfg = tnk::CFG_128x64;
@@ -595,12 +595,11 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
 // Between that and a large one: 32x32 tiles (or 64x16, as fast and wider in M, for a
 // short K) and slices of K down to 32 until the CUs are covered, from K = 192 on (a
 // second kernel adds the slices, 4 us).  64 x 4096 x 64: 8 for 16 with 64x64.
-// In the split modes a short K leaves nothing to amortise the splitting over: the
-// FP32 kernel with four products, up to K = 32 for bf16x6 and 64 for bf16x3, where
-// its error is no larger (against 64 bits, K = 32 and below: at most 1.03e-7
-// relative on normal numbers and 6.1e-8 on positive ones for bf16x6's 1.17e-7 and
-// 7.6e-8; K = 64: 2.0e-7 and 1.2e-7 for bf16x3's 4.4e-6 and 7.1e-7).  262144 x 64 x
-// 16: 138 in bf16x6 and 52 in FP32.
+// In bf16x6 a short K leaves nothing to amortise the splitting over: the FP32 kernel
+// with four products, up to K = 32, where its error is no larger (against 64 bits at
+// most 1.03e-7 relative on normal numbers and 6.1e-8 on positive ones for bf16x6's
+// 1.17e-7 and 7.6e-8).  262144 x 64 x 16: 138 in bf16x6 and 52 in FP32.  Not in bf16x3
+// (see Engine::keeps_order): its sums stay the split ones, on the tiles of the rule in plan().
 void Engine::choose_tile(Plan *P) {
     const int64_t M = P->kM, N = P->kN, K = P->K, Z = P->Z;
     auto tiles = [&](int cfg) {
@@ -608,10 +607,9 @@ void Engine::choose_tile(Plan *P) {
         tnk::gett_tile(cfg, prec, &bm, &bn);
         return ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * Z;
     };
-    const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
     P->pack = false;
-    P->fp32 = bf16 && K <= (prec == tnk::P_BF16X6 ? 32 : 64) ? 2 : 0;
-    const bool split = bf16 && !P->fp32;  // the split-BF16 kernels
+    P->fp32 = prec == tnk::P_BF16X6 && K <= 32 ? 2 : 0;
+    const bool split = prec == tnk::P_BF16X6 && !P->fp32;  // the split-BF16 kernels
     const int64_t t64 = tiles(tnk::CFG_64x64);
     const bool large = t64 >= 256 || t64 * (K / 256) >= 256;
     int cfg;
@@ -1158,7 +1156,7 @@ Ten Engine::contract_new(const Op &A, const Op &B, const std::string &ic) {
 
 void Engine::qr(const tnk::QrArgs &a0) {
     tnk::QrArgs a = a0;
-    a.keep_sums = keep_sums ? 1 : 0;
+    a.keep_sums = keeps_order() ? 1 : 0;
     if (a.n > 64 && a.m >= a.n && (int64_t)a.m * a.n > 8192) {
         // one workgroup per matrix would factor it alone: blocks of 64 columns,
         // block Gram-Schmidt between them and Householder TSQR within
@@ -1200,7 +1198,7 @@ static Op view(void *p, const std::string &idx, std::vector<int> dims, std::vect
 // the tree, 183 by the passes (24 of it the tree's launches that find no flag); 512 x 32
 // 253 and 82; up to 16 columns or in one block of the tree it is as fast or faster.
 void Engine::factor(const tnk::QrArgs &a) {
-    if (keep_sums || householder_only || !a.R || a.n <= 16 || a.n > 64 || a.m <= 128) {
+    if (keeps_order() || householder_only || !a.R || a.n <= 16 || a.n > 64 || a.m <= 128) {
         qr(a);
         return;
     }

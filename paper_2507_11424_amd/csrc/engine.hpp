@@ -154,6 +154,11 @@ class Engine {
     // the updated site tensors, depend on the last bit of its input: another
     // order of summation gives the same state in another gauge.
     bool keep_sums = false;
+    // BF16x3 keeps them too, and every product with a tensor that happens to be an
+    // identity: each product of the mode rounds to 16 bits, so another gauge of a
+    // site (another completion of a rank-deficient one) or a product less is another
+    // rounding of everything after it, and two-site values move by up to 3e-5.
+    bool keeps_order() const { return keep_sums || prec == tnk::P_BF16X3; }
     // Contractions issued while a mask is set skip the tiles of the items z of
     // letter `letter` with mask[z] == skip (device int array over that letter's
     // extent) when the letter is the slowest of the batch, M or N index space;

@@ -223,7 +223,7 @@ std::vector<Ten> fit_single(Engine &E, const std::vector<Ten> &m, const std::vec
                 ident[c] = 0;
             }
             if (Le[c + 1].p) E.drop(Le[c + 1]);
-            if (square && d == 1) {
+            if (square && d == 1 && !E.keeps_order()) {
                 Le[c + 1] = tl;
                 Le[c + 1].d = {Z, yr, tl.d[2], tl.d[4]};
                 continue;
