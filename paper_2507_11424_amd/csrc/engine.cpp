@@ -287,7 +287,7 @@ std::string Engine::plan_report(int top) const {
         if (p->calls == 0) continue;
         const double tf = p->ms > 0 ? p->flops * p->calls / (p->ms * 1e-3) / 1e12 : 0.0;
         os << p->ms << '\t' << p->calls << '\t' << tf << '\t' << p->desc << (p->pack ? " packed" : "")
-           << (p->fp32 == 2 ? " fp32-4M" : p->fp32 ? " fp32" : "") << " cfg=" << p->cfg
+           << (p->fp32 == 2 ? " 4M" : p->fp32 ? " fp32" : "") << " cfg=" << p->cfg
            << " split=" << p->base.ksplit << (p->tuned ? " tuned" : "") << '\n';
     }
     os << "calls\tfactorisation\n";
@@ -543,7 +543,8 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
     const bool fp_only = tc != tune_cache_.end() && (tc->second.cfg == tnk::CFG_16x16 || tc->second.cfg == tnk::CFG_64x32);
     if (tc != tune_cache_.end() && (!fp_only || prec == tnk::P_FP64 || prec == tnk::P_FP32 || tc->second.fp32)) {
         P->pack = P->can_pack && tc->second.pack;
-        P->fp32 = (prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6) && !P->pack ? tc->second.fp32 : 0;
+        const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
+        P->fp32 = !P->pack && (bf16 || tc->second.fp32 == 2) ? tc->second.fp32 : 0;
         set_split(P.get(), tc->second.cfg, tc->second.ks);
         P->tuned = true;
     } else if (keep || prec == tnk::P_BF16X3) {  // see keeps_order
@@ -566,14 +567,18 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
 // A problem is large when its 64x64 tiles fill the 256 CUs, or would if a K of
 // many hundreds were cut into slices of at least 256; then the tile with the most
 // work per loaded byte wins:
-//   FP64 and FP32: 64x64 on 4 waves (3M).  720896 x 128 x 128: 1546 against 2488 for
-//   128x64 with 4M, which leaves one wave per SIMD.  Up to K = 64, where loads and
-//   stores weigh as much as the products, and up to 32 columns, 64x32, of which
-//   three fit a CU for two: 4194304 x 32 x 16 834 against 1402 (64x16: 1014), 1048576
-//   x 64 x 64 710 / 824, 65536 x 96 x 32 42 / 55, 524288 x 128 x 128 1110 / 1110 (in
-//   FP32 646 / 741); 4096 x 128 x 256 x 64 1009 / 995.  Below 1024 of them 64x16 keeps
-//   up with its greater number (16384 x 32 x 64: 11.3 for 11.6), as up to 16 columns
-//   (4194304 x 16 x 16: 501); of up to 32 rows 32x32 (32 x 4096 x 512: 20 for 27).
+//   FP64 and FP32: 64x64 on 4 waves.  Up to K = 64, where loads and stores weigh as
+//   much as the products, and up to 32 columns, 64x32, of which three fit a CU for two:
+//   4194304 x 32 x 16 834 against 1402 (64x16: 1014), 1048576 x 64 x 64 710 / 824, 65536
+//   x 96 x 32 42 / 55, 524288 x 128 x 128 1110 / 1110 (in FP32 646 / 741); 4096 x 128 x
+//   256 x 64 1009 / 995.  Below 1024 of them 64x16 keeps up with its greater number
+//   (16384 x 32 x 64: 11.3 for 11.6), as up to 16 columns (4194304 x 16 x 16: 501); of
+//   up to 32 rows 32x32 (32 x 4096 x 512: 20 for 27).
+//   From 8192 x 128 x 16 on with four products, elsewhere with three: the line between
+//   the forms is one of accuracy (the imaginary part of three products has twice the
+//   error) and is where callers have had it, with a 128x64 tile that left one wave per
+//   SIMD.  720896 x 128 x 128 in FP64: 1707 (128x64 2362, three products 1455), in FP32
+//   885 (1029, 988); 65536 x 128 x 32: 58 on 64x32 (88; 64x64 62), 36 (44).
 //   FP32 with four products has four 64x64 on a CU and needs 64x32 only for 32
 //   columns (131072 x 32 x 32 x 8: 164 for 221; 262144 x 64 x 16: 55 / 50).
 //   Split-BF16, packed (both sides above 128): 128x128 while its tiles fill the CUs
@@ -608,7 +613,8 @@ void Engine::choose_tile(Plan *P) {
         return ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * Z;
     };
     P->pack = false;
-    P->fp32 = prec == tnk::P_BF16X6 && K <= 32 ? 2 : 0;
+    if (prec == tnk::P_BF16X6) P->fp32 = K <= 32 ? 2 : 0;
+    else P->fp32 = M >= 8192 && N >= 128 && K >= 16 ? 2 : 0;
     const bool split = prec == tnk::P_BF16X6 && !P->fp32;  // the split-BF16 kernels
     const int64_t t64 = tiles(tnk::CFG_64x64);
     const bool large = t64 >= 256 || t64 * (K / 256) >= 256;
@@ -628,7 +634,7 @@ void Engine::choose_tile(Plan *P) {
     } else if (!split) {
         if (M <= 32) cfg = tnk::CFG_32x32;
         else if (N <= 32) cfg = tiles(tnk::CFG_64x32) >= 1024 ? tnk::CFG_64x32 : tnk::CFG_64x16;
-        else cfg = K <= 64 && !P->fp32 ? tnk::CFG_64x32 : tnk::CFG_64x64;
+        else cfg = K <= 64 && (prec == tnk::P_FP64 || !P->fp32) ? tnk::CFG_64x32 : tnk::CFG_64x64;
     } else if (P->can_pack && t64 >= 256) {
         P->pack = true;
         cfg = tiles(tnk::CFG_128x128W) >= 256 ? tnk::CFG_128x128W : tnk::CFG_128x64W;

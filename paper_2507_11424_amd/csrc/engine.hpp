@@ -103,7 +103,9 @@ struct Plan {
     int64_t kM = 0, kN = 0, K = 0, Z = 0;
     bool pack = false;    // split-BF16 on packed operand planes (else split while staging)
     bool can_pack = false;  // packing is offered (both matrix sides above 128); the tuner decides
-    int fp32 = 0;           // split-BF16 modes: this shape runs on the FP32 kernel, 1: 3M (chosen by the tuner), 2: 4M
+    // 2: the FP64 or FP32 kernel with four real products (in bf16x6 too, on short sums);
+    // 1: split-BF16 modes on the FP32 kernel with three (older tuning files)
+    int fp32 = 0;
     // letters of the batch, kernel-M and kernel-N index spaces, slowest first,
     // and every letter's extent (for masked launches)
     std::string bl, kml, knl;
@@ -269,7 +271,8 @@ class Engine {
     Plan *plan(const Op &A, const Op &B, const Op &C, bool keep);
     void choose_tile(Plan *P);
     int kernel_prec(const Plan &P) const {
-        return P.fp32 == 2 ? (int)tnk::P_FP32_4M : P.fp32 ? (int)tnk::P_FP32 : prec;
+        if (P.fp32 == 2) return prec == tnk::P_FP64 ? (int)tnk::P_FP64_4M : (int)tnk::P_FP32_4M;
+        return P.fp32 ? (int)tnk::P_FP32 : prec;
     }
     // event pairs recorded around launches in timing mode
     std::deque<EvPair> ev_;

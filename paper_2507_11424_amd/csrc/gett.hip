@@ -2,9 +2,10 @@
 //
 // Every contraction of the boundary-MPS fit and of the sampler (products of
 // boundary MPS, row tensors, their conjugates and environments) is a batched
-// complex GEMM over gathered indices (see GettArgs).  Complex products use the
-// 4M form on real MFMA:
+// complex GEMM over gathered indices (see GettArgs).  Complex products are four
+// real ones on MFMA (4M),
 //   Re C += Re A Re B - Im A Im B,   Im C += Re A Im B + Im A Re B,
+// or in FP64 and FP32 three (3M, see gett_block; Engine::choose_tile says which),
 // with A and B tiles staged through LDS as planar (re, im) slabs.
 //
 // Precisions:
@@ -71,7 +72,7 @@ __device__ inline bool gett_skip(const GettArgs &p, int b, int m0, int n0) {
 // loads of a stage issue back to back.  k offsets are affine (k * ks, kept in
 // registers) or come from the k table, staged into LDS once per block.
 constexpr uint32_t OOB = 0x80000000u;
-constexpr bool GAUSS3M = true;  // 64x64 and 64x16 FP64 / FP32 tiles; 128x64 keeps 4M (3M would spill)
+constexpr bool GAUSS3M = true;  // the FP64 / FP32 tiles of P_FP64 and P_FP32; 128x64 keeps 4M (3M would spill)
 
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
     // the base is the same for the whole workgroup (batch item); say so, so
@@ -1199,7 +1200,7 @@ hipError_t launch_gett(const GettArgs &a0, int prec, int cfg, hipStream_t s) {
     }
     hipError_t e = launch_main(a, prec, cfg, s);
     if (e != hipSuccess || a.ksplit <= 1) return e;
-    return prec == P_FP64 ? launch_reduce<double2>(a, s) : launch_reduce<float2>(a, s);
+    return prec == P_FP64 || prec == P_FP64_4M ? launch_reduce<double2>(a, s) : launch_reduce<float2>(a, s);
 }
 
 static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t s) {
@@ -1212,6 +1213,15 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 1, 2, 2, GAUSS3M>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<double, GAUSS3M>(a, s);
             case CFG_64x32: return launch_k(gett_mfma<double, 64, 32, 16, 1, 2, 2, GAUSS3M, 3>, a, 64, 32, 256, s);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (prec == P_FP64_4M) {
+        switch (cfg) {
+            case CFG_64x64: return launch_k(gett_mfma<double, 64, 64, 16, 1, 2, 2, false>, a, 64, 64, 256, s);
+            case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 1, 2, 2, false>, a, 32, 32, 256, s);
+            case CFG_16x16: return launch_wave<double, false>(a, s);
+            case CFG_64x32: return launch_k(gett_mfma<double, 64, 32, 16, 1, 2, 2, false, 3>, a, 64, 32, 256, s);
             default: return hipErrorInvalidValue;
         }
     }

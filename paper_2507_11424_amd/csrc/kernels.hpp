@@ -8,7 +8,7 @@ namespace tnk {
 
 // Compute modes of the contraction engine (mirrors tn_prec).
 enum Prec : int { P_FP64 = 0, P_FP32 = 1, P_BF16X3 = 2, P_BF16X6 = 3,
-                  P_FP32_4M = 4 };  // FP32 with four real products (a kernel choice of the split modes)
+                  P_FP32_4M = 4, P_FP64_4M = 5 };  // kernel choices: four real products for three
 
 // A batched complex contraction written as a GEMM over gathered indices:
 //   C[b](m, n) (+)= sum_k opA(A[b](m, k)) * opB(B[b](k, n))
