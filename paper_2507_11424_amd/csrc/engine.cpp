@@ -532,6 +532,7 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
     P->knl = swap ? ml : nl;
     P->ldim = dim;
     P->key = tkey;
+    P->keep = keep;
     P->flops = 8.0 * (double)M * (double)N * (double)K * (double)Z;
     {
         std::ostringstream d;
@@ -539,7 +540,8 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
           << (swap ? " swapped" : "");
         P->desc = d.str();
     }
-    auto tc = tune_cache_.find(P->key);
+    // a tuned tile or number of slices would sum in another order
+    auto tc = keep ? tune_cache_.end() : tune_cache_.find(P->key);
     const bool fp_only = tc != tune_cache_.end() && (tc->second.cfg == tnk::CFG_16x16 || tc->second.cfg == tnk::CFG_64x32);
     if (tc != tune_cache_.end() && (!fp_only || prec == tnk::P_FP64 || prec == tnk::P_FP32 || tc->second.fp32)) {
         P->pack = P->can_pack && tc->second.pack;
@@ -978,7 +980,7 @@ void Engine::contract(const Op &A, const Op &B, const Op &C, bool accumulate) {
         g.ksplit = tmp.base.ksplit;
         g.kchunk = tmp.base.kchunk;
         cfg = force_cfg;
-    } else if (autotune_ && !P->tuned && !accumulate) {
+    } else if (autotune_ && !P->tuned && !P->keep && !accumulate) {
         tune(P, g);
         g.ksplit = P->base.ksplit;
         g.kchunk = P->base.kchunk;

@@ -102,6 +102,7 @@ struct Plan {
     bool tuned = false;   // tile configuration chosen by measurement
     int64_t kM = 0, kN = 0, K = 0, Z = 0;
     bool pack = false;    // split-BF16 on packed operand planes (else split while staging)
+    bool keep = false;    // made for keep_sums: never tuned
     bool can_pack = false;  // packing is offered (both matrix sides above 128); the tuner decides
     // 2: the FP64 or FP32 kernel with four real products (in bf16x6 too, on short sums);
     // 1: split-BF16 modes on the FP32 kernel with three (older tuning files)
@@ -150,8 +151,9 @@ class Engine {
     // the fit's matrices rank-deficient (CholeskyQR needs full column rank)
     bool householder_only = false;
     // Set by the simple update: Householder QR and the contractions keep the order
-    // of their sums (the LDS kernels; the planner's first K slices).  Its pair SVD is a one-sided Jacobi, which multiplies columns
-    // by the phases of products that are rounding residue where columns are
+    // of their sums (the LDS kernels; the tiles and K slices of the rule in plan(),
+    // which the tuner leaves alone).  Its pair SVD is a one-sided Jacobi, which
+    // multiplies columns by the phases of products that are rounding residue where columns are
     // already orthogonal, so the phases of the singular vectors, and with them
     // the updated site tensors, depend on the last bit of its input: another
     // order of summation gives the same state in another gauge.
