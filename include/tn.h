@@ -406,6 +406,11 @@ tn_status tn_test_eig(tn_handle *h, int n, int batch, const void *A, void *lam, 
  *   TN_ERR_INVALID for a NULL handle, negative wave / rows_limit or graphs
  *   other than 0 and 1. */
 tn_status tn_test_sample_config(tn_handle *h, int wave, int rows_limit, double *log_cond, int graphs);
+/* tn_test_workspace: later calls on this handle hold at most `cap` bytes of device
+ *   workspace (0 = no cap): an allocation beyond it fails as one that the device
+ *   refuses (TN_ERR_OOM where no other way is left).  *in_use (optional): bytes of
+ *   the handle's workspace in use now, that is neither free nor cached. */
+tn_status tn_test_workspace(tn_handle *h, size_t cap, size_t *in_use);
 
 #ifdef __cplusplus
 }

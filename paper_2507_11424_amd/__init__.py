@@ -32,7 +32,8 @@ STATUS = {0: "TN_OK", 1: "TN_ERR_INVALID", 2: "TN_ERR_SHAPE", 3: "TN_ERR_OOM", 4
 EXPORTS = ["tn_default_opts", "tn_create", "tn_destroy", "tn_boundary_contract", "tn_environments",
            "tn_sample", "tn_amplitude", "tn_sample_stats", "tn_last_error", "tn_get_counters", "tn_set_timing",
            "tn_set_autotune", "tn_plan_report", "tn_test_contract", "tn_test_qr", "tn_test_svd", "tn_test_set_mask",
-           "tn_test_sample_config", "tn_sample_stats_noalloc", "tn_bp", "tn_test_eig", "tn_simple_update"]
+           "tn_test_sample_config", "tn_sample_stats_noalloc", "tn_bp", "tn_test_eig", "tn_simple_update",
+           "tn_test_workspace"]
 
 
 class TnError(RuntimeError):
@@ -94,6 +95,7 @@ def lib(path: Optional[str] = None):
     L.tn_test_svd.argtypes = [vp, ctypes.c_int, ctypes.c_int, vp, ctypes.c_double, ctypes.c_int, vp, vp,
                               ctypes.c_int, vp]
     L.tn_test_set_mask.argtypes = [vp, vp, ctypes.c_char]
+    L.tn_test_workspace.argtypes = [vp, ctypes.c_size_t, ctypes.POINTER(ctypes.c_size_t)]
     L.tn_test_sample_config.argtypes = [vp, ctypes.c_int, ctypes.c_int, vp, ctypes.c_int]
     ip = ctypes.POINTER(ctypes.c_int)
     L.tn_bp.argtypes = [vp, ctypes.POINTER(c_peps), ctypes.c_int, ctypes.c_double, dp, dp, ip, dp, dp, dp,
@@ -104,7 +106,8 @@ def lib(path: Optional[str] = None):
     for f in ("tn_create", "tn_destroy", "tn_boundary_contract", "tn_environments", "tn_sample",
               "tn_get_counters", "tn_set_timing", "tn_set_autotune", "tn_test_contract",
               "tn_test_qr", "tn_test_svd", "tn_test_set_mask", "tn_amplitude", "tn_sample_stats",
-              "tn_test_sample_config", "tn_sample_stats_noalloc", "tn_bp", "tn_test_eig", "tn_simple_update"):
+              "tn_test_sample_config", "tn_sample_stats_noalloc", "tn_bp", "tn_test_eig", "tn_simple_update",
+              "tn_test_workspace"):
         getattr(L, f).restype = ctypes.c_int
     if path is None:
         _lib = L
@@ -449,6 +452,13 @@ class Handle:
         must stay alive while the setting is in force."""
         ptr = ctypes.c_void_p(log_cond.data_ptr()) if log_cond is not None else None
         self._check(lib().tn_test_sample_config(self.h, int(wave), int(rows_limit), ptr, 1 if graphs else 0))
+
+    def test_workspace(self, cap: int = 0) -> int:
+        """Caps the device workspace of later calls (bytes, 0 = no cap); returns the
+        bytes in use now (see tn_test_workspace)."""
+        n = ctypes.c_size_t()
+        self._check(lib().tn_test_workspace(self.h, int(cap), ctypes.byref(n)))
+        return n.value
 
     def test_contract(self, prec: str, ia: str, A, ib: str, B, ic: str, C, conjA=False, conjB=False,
                       accumulate=False, cfg: int = -1, ksplit: int = 0, mask=None, mask_letter: str = "z"):

@@ -702,6 +702,13 @@ tn_status tn_test_sample_config(tn_handle *h, int wave, int rows_limit, double *
     return TN_OK;
 }
 
+tn_status tn_test_workspace(tn_handle *h, size_t cap, size_t *in_use) {
+    if (!h || !h->E) return TN_ERR_INVALID;
+    h->E->set_workspace_cap(cap);
+    if (in_use) *in_use = h->E->held() - h->E->idle();
+    return TN_OK;
+}
+
 tn_status tn_test_eig(tn_handle *h, int n, int batch, const void *A, void *lam, double *eps, int32_t *info) {
     try {
         if (!h || !h->E) throw TnError(ST_INVALID, "null handle");

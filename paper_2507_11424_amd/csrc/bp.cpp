@@ -298,14 +298,6 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
             tab.push_back({t.p, static_cast<char *>(c.A.p) + (size_t)i * per * 16, 1, per, 0});
         }
     }
-    // a sweep's intermediates: at most eight of the state's size, held together
-    // unless they would take more than a quarter of the memory (asked from 1 GiB on)
-    bool grouped = true;
-    if (8 * class_bytes > (double)((size_t)1 << 30)) {
-        size_t freeb = 0, total = 0;
-        TN_HIP(hipMemGetInfo(&freeb, &total));
-        grouped = 8 * class_bytes <= 0.25 * ((double)freeb + (double)E.held());
-    }
     // neighbour table and initial messages: identity / sqrt(D) on bonds, e0 e0^T elsewhere
     std::vector<int> hn((size_t)N * NLEG, -1);
     std::vector<double> hm((size_t)N * NLEG * n2 * 2, 0.0);
@@ -350,7 +342,34 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
         E.unraw(dscal);
         if (dtab) E.unraw(dtab);
     };
+    // A stage's intermediates, held together: at most eight of the state's size in a
+    // sweep, two for each of the up to six leg pairs of the loops (K slices and
+    // tables come on top, small beside them).  One after another where those would
+    // take more than a quarter of the free memory (asked from 1 GiB on), and
+    // from the first stage on that does not get its memory after all.
+    bool grouped = true;
+    auto stage = [&](auto add) {  // runs what add(Stages &) adds
+        if (grouped) {
+            try {
+                Stages S(E, true);
+                add(S);
+                S.run();
+                return;
+            } catch (const TnError &e) {
+                if (e.code != ST_OOM) throw;
+                grouped = false;
+            }
+        }
+        Stages S(E, false);
+        add(S);
+    };
     try {
+        const double most = (o.loops ? 12 : 8) * class_bytes;
+        if (most > (double)((size_t)1 << 30)) {
+            size_t freeb = 0, total = 0;
+            TN_HIP(hipMemGetInfo(&freeb, &total));
+            grouped = most <= 0.25 * ((double)freeb + (double)E.idle());
+        }
         if (o.init_messages) {  // grid layout [NG][4][Dm][Dm]: the active sites' blocks
             for (int i = 0; i < N; ++i)
                 tab.push_back({static_cast<const char *>(o.init_messages) + (size_t)act[i] * site_msgs * 16,
@@ -374,11 +393,25 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
         };
         double delta = INFINITY;
         int sweep = 0;
-        Stages round(E, grouped);
+        auto outgoing = [&](Stages &S) {
+            for (const auto &c : cls) all_outgoing(S, c, msg, Dm, out_op);
+        };
+        std::unique_ptr<Stages> round;  // added once, run by every sweep
         while (sweep < o.max_sweeps) {
-            if (sweep == 0 || !grouped)
-                for (const auto &c : cls) all_outgoing(round, c, msg, Dm, out_op);
-            round.run();
+            if (grouped) {
+                try {
+                    if (!round) {
+                        round.reset(new Stages(E, true));
+                        outgoing(*round);
+                    }
+                    round->run();
+                } catch (const TnError &e) {
+                    if (e.code != ST_OOM) throw;
+                    grouped = false;
+                    round.reset();
+                }
+            }
+            if (!grouped) stage(outgoing);
             ++sweep;
             const bool check = sweep % 4 == 0 || sweep == o.max_sweeps;
             TN_HIP(tnk::launch_bp_update(out.p, msg.p, nbr, N, Dm, dmax, check ? dscal : nullptr, E.s));
@@ -389,13 +422,14 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
                 if (delta < o.tol) break;
             }
         }
+        round.reset();  // its intermediates go before the next stages' come
         res.sweeps = sweep;
         res.delta = delta;
         // Z_BP from the final messages
         if (o.free_energy) {
-            Stages fin(E, grouped);
-            for (const auto &c : cls) pair_closed(fin, c, msg, {3}, out_op(3, c), Dm);
-            fin.run();
+            stage([&](Stages &S) {
+                for (const auto &c : cls) pair_closed(S, c, msg, {3}, out_op(3, c), Dm);
+            });
             double *zv = static_cast<double *>(E.raw((size_t)N * 16));
             double *ze = static_cast<double *>(E.raw((size_t)N * 32));
             TN_HIP(tnk::launch_bp_free_energy(static_cast<char *>(out.p) + (size_t)3 * N * n2 * 16, msg.p, nbr, N, Dm,
@@ -446,19 +480,19 @@ void bp_contract(Engine &E, const PepsDev &P, const BpOpts &o, BpResult &res) {
                 Ten pt = E.make({(int)pairs.size(), N, Dm, Dm, Dm, Dm});
                 TN_HIP(tnk::launch_fill(pt.p, pt.esz, pt.numel(), 0.0, 0.0, E.s));
                 const size_t pstride = (size_t)N * n2 * n2;
-                Stages prs(E, grouped);
-                for (size_t k = 0; k < pairs.size(); ++k)
-                    for (const auto &c : cls) {
-                        const int a = pairs[k].first, b = pairs[k].second;
-                        Op q;
-                        q.p = static_cast<char *>(pt.p) + (k * pstride + (size_t)c.start * n2 * n2) * 16;
-                        q.esz = 16;
-                        q.idx = std::string("z") + KET[a] + BRA[a] + KET[b] + BRA[b];
-                        q.dims = {c.count, c.dims[a + 1], c.dims[a + 1], c.dims[b + 1], c.dims[b + 1]};
-                        q.str = {(int64_t)n2 * n2, (int64_t)Dm * n2, n2, Dm, 1};
-                        pair_closed(prs, c, msg, {a, b}, q, Dm);
-                    }
-                prs.run();
+                stage([&](Stages &S) {
+                    for (size_t k = 0; k < pairs.size(); ++k)
+                        for (const auto &c : cls) {
+                            const int a = pairs[k].first, b = pairs[k].second;
+                            Op q;
+                            q.p = static_cast<char *>(pt.p) + (k * pstride + (size_t)c.start * n2 * n2) * 16;
+                            q.esz = 16;
+                            q.idx = std::string("z") + KET[a] + BRA[a] + KET[b] + BRA[b];
+                            q.dims = {c.count, c.dims[a + 1], c.dims[a + 1], c.dims[b + 1], c.dims[b + 1]};
+                            q.str = {(int64_t)n2 * n2, (int64_t)Dm * n2, n2, Dm, 1};
+                            pair_closed(S, c, msg, {a, b}, q, Dm);
+                        }
+                });
                 // loops grouped by length: gather [loop][k] matrices, multiply along the walk
                 std::map<int, std::vector<int>> bylen;
                 for (int i = 0; i < (int)loops.size(); ++i) bylen[(int)loops[i].size()].push_back(i);

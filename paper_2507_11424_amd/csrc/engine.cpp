@@ -118,6 +118,12 @@ void Pool::release(const std::vector<void *> &blocks) {
     }
 }
 
+size_t Pool::idle() const {
+    size_t n = 0;
+    for (const auto &kv : free_) n += kv.first;
+    return n;
+}
+
 void Pool::trim() {
     if (free_.empty()) return;
     (void)hipDeviceSynchronize();
@@ -474,7 +480,10 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
         // the pool's cached blocks may hold the memory: return them and retry
         (void)hipGetLastError();
         if (!capturing()) pool_.trim();
-        TN_HIP(hipMalloc(&P->dev, bytes));
+        if (hipMalloc(&P->dev, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            throw TnError(ST_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+        }
     }
     TN_HIP(hipMemcpy(P->dev, host.data(), bytes, hipMemcpyHostToDevice));
     char *d = reinterpret_cast<char *>(P->dev);

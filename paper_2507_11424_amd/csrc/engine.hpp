@@ -68,6 +68,9 @@ class Pool {
     void *get(size_t bytes);
     void put(void *p);
     size_t held() const { return held_; }
+    // Bytes of the blocks that nothing uses.
+    size_t idle() const;
+    void set_cap(size_t cap) { cap_ = cap; }
     void trim();
     // Arena mode (stream capture): between begin_arena and end_arena every block
     // handed out -- taken from the free list or newly allocated -- is recorded,
@@ -234,6 +237,8 @@ class Engine {
     void *raw(size_t bytes) { return pool_.get(bytes); }
     void unraw(void *p) { pool_.put(p); }
     size_t held() const { return pool_.held(); }
+    size_t idle() const { return pool_.idle(); }  // of those, bytes that nothing uses
+    void set_workspace_cap(size_t cap) { pool_.set_cap(cap); }  // 0: none
 
     void sync() { TN_HIP(hipStreamSynchronize(s)); }
 
