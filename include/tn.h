@@ -364,7 +364,9 @@ tn_status tn_plan_report(const tn_handle *h, int top, char *buf, size_t len);
  *   otherwise), R = R_3 R_2 R_1.  method 2: CholeskyQR3 of the LQ moves, Q
  *   only (R must be NULL, m >= n): A and Q hold the conjugate transposes
  *   (n x m, row-major), so the rows of Q are an orthonormal basis of the rows
- *   of A.  Enqueued on the handle's stream.
+ *   of A.  method 3: the factorisation of exact rows, Householder or, for many
+ *   rows, CholeskyQR3 with R = Q^H A (upper triangular up to rounding).
+ *   Enqueued on the handle's stream.
  * tn_test_svd: the sampler's SVD truncation step on `batch` row-major n x n
  *   complex128 DEVICE matrices R (n <= 256): U (n x n) and SV (n x n), element
  *   size esz (16 or 8), with R ~ U SV; columns of U and rows of SV past the

@@ -499,7 +499,8 @@ class Handle:
         """method "householder" or "cholesky" (default: Householder when R is
         given, CholeskyQR3 otherwise); "cholesky_lq": A and Q are n x m (wide),
         the rows of Q an orthonormal basis of the rows of A, read and written
-        through conjugate-transposed strides as in the fit's LQ moves."""
+        through conjugate-transposed strides as in the fit's LQ moves; "factor": Q
+        and R of an exact row's site."""
         m, n = A.shape[-2], A.shape[-1]
         if method == "cholesky_lq":
             m, n = n, m
@@ -510,4 +511,4 @@ class Handle:
         self._check(lib().tn_test_qr(self.h, m, n, batch, esz, ctypes.c_void_p(A.data_ptr()),
                                      ctypes.c_void_p(Q.data_ptr()),
                                      ctypes.c_void_p(R.data_ptr()) if R is not None else None,
-                                     {"householder": 0, "cholesky": 1, "cholesky_lq": 2}[method]))
+                                     {"householder": 0, "cholesky": 1, "cholesky_lq": 2, "factor": 3}[method]))

@@ -682,6 +682,7 @@ tn_status tn_test_qr(tn_handle *h, int m, int n, int batch, int esz, const void 
             a.R = nullptr;
         }
         if (method == 0) h->E->qr(a);
+        else if (method == 3) h->E->factor(a);
         else h->E->orthonormalise(a);
         return TN_OK;
     } catch (const TnError &e) {

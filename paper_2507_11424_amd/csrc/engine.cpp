@@ -1254,9 +1254,13 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_
     EvPair *ev = (timing && !nested) ? next_pair(1) : nullptr;
     std::vector<Ten> tmp;
     tmp.reserve(8);  // references into tmp are taken below: no reallocation
+    int *flags = nullptr;  // the items for the fallback
+    void *ws = nullptr;    // its workspace
     auto cleanup = [&]() {
         for (auto &t : tmp)
             if (t.p) drop(t);
+        if (flags) unraw(flags);
+        if (ws) unraw(ws);
         in_qr_ = nested;
         set_prec(saved);
     };
@@ -1270,9 +1274,8 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_
         // which returns orthonormal columns for any rank; the others skip it.
         // In one launch, slow for a tall matrix, where that is not expected; in the
         // launches of the register tree where it may well be (any_rank).
-        auto fallback = [&](int *flags) {
-            void *ws = raw(any_rank ? tnk::qr_workspace_bytes(m, n, Z, 0)
-                                         : tnk::qr_fallback_workspace_bytes(m, n, Z));
+        auto fallback = [&]() {
+            ws = raw(any_rank ? tnk::qr_workspace_bytes(m, n, Z, 0) : tnk::qr_fallback_workspace_bytes(m, n, Z));
             if (any_rank) {
                 tnk::QrArgs h = a;
                 h.keep_sums = 0;
@@ -1281,13 +1284,11 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_
             } else {
                 TN_HIP(tnk::launch_qr_fallback(a, flags, ws, s));
             }
-            unraw(ws);
-            unraw(flags);
         };
         if (!a.R && tnk::cqr_one_fits(m, n)) {
-            int *flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
+            flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
             TN_HIP(tnk::launch_cqr_one(a, shift0, flags, s));
-            fallback(flags);
+            fallback();
         } else if (n <= 64) {
             // Three CholeskyQR passes (the first shifted), each one launch over
             // row blocks (rows times the previous inverse factor, their partial
@@ -1307,7 +1308,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_
             if (factors)
                 for (int i = 0; i < 3; ++i) tmp.push_back(make({Z, n, n}, 16));
             // a clamped pivot in any pass flags the item for the Householder fallback
-            int *flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
+            flags = static_cast<int *>(raw((size_t)Z * sizeof(int)));
             for (int pass = 0; pass <= 3; ++pass) {
                 tnk::CqrPass c{};
                 c.m = m; c.n = n; c.batch = Z; c.rb = rb;
@@ -1358,7 +1359,7 @@ void Engine::ortho_impl(const tnk::QrArgs &a, bool householder_blocks, bool any_
                 TN_HIP(tnk::launch_strided_copy(Ri.p, 16, (int64_t)n * n, n, 1, a.R, a.r_esz, a.r_bs, a.r_rs, a.r_cs, n,
                                                 n, Z, a.r_conj, s));
             }
-            fallback(flags);
+            fallback();
         } else {
             // Wider than one Cholesky block: columns in blocks of 64; each block is
             // made orthogonal to the finished ones by three passes of block
