@@ -349,6 +349,17 @@ __global__ void __launch_bounds__(QR_NT) k_qr_form(FormArgs a) {
 // square roots of the library, 339, 2.08, 141, 48 and 46.  512 threads serve 64 columns as well as 256 (338 and 367 us; 1024: 474);
 // up to 32 columns 256 are no slower than 512 and leave room for more blocks.
 constexpr int QR_REG_ROWS = 128;
+// A column whose sum of squares s is outside [REG_SMALL2, REG_LARGE2] is scaled to s
+// near 1 for its step: the pivot's square (kept down to 2^-106 s), the column's
+// products with columns of any other size and their quotients by its norm stay
+// normal numbers.  (A pivot of subnormal square gave a phase off by 1e-12, and Q with
+// it; columns of 1e-290 after ones of 1e-150 lost their R.)
+constexpr double REG_SMALL2 = 1e-40, REG_LARGE2 = 1e20;
+__device__ __forceinline__ bool out_of_range(double s) {  // s >= 0 or NaN: one comparison of the upper words
+    constexpr unsigned lo = (unsigned)(__builtin_bit_cast(unsigned long long, REG_SMALL2) >> 32);
+    constexpr unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, REG_LARGE2) >> 32);
+    return (unsigned)(__builtin_bit_cast(unsigned long long, s) >> 32) - lo > hi - lo;
+}
 
 __device__ inline double lane_get(double v, int lane) {
     const int2 a = __builtin_bit_cast(int2, v);
@@ -493,9 +504,9 @@ __device__ __forceinline__ void reg_take(const double2 (&p)[RT], double2 (&Y)[RT
 }
 
 // Householder steps on X; the lanes of column j end with R[j][j] in beta, tau_j
-// and f_j.  A column whose squares fall below HH_SMALL2 is scaled up by 2^400 (its
-// reflector does not change with scale) and its step taken again, at most three
-// times: then it is zero, with tau = 0.
+// and f_j.  A column out of range is scaled by a power of two (its reflector does not
+// change with scale) and its step taken again; one that is still too small for its
+// squares after three times 2^400 is zero, with tau = 0.
 template <int NC, int NT, int RT>
 __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, double2 &beta, double &tau, double2 &fac,
                                            QrRegShared<NC, NT> &sh) {
@@ -505,7 +516,7 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
     fac = make_double2(0.0, 0.0);
     tau = 0.0;
     const int kmax = rows < n ? rows : n;
-    int pb = 0, ups = 0;
+    int pb = 0, ups = 0, ex = 0;  // scalings of this column, and their exponent
     for (int j = 0; j < kmax;) {
         pb ^= 1;
         double2 p[RT];
@@ -533,19 +544,22 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
         const double a2 = alpha.x * alpha.x + alpha.y * alpha.y;
         s += a2;
         // s is the same in every thread, and so is every branch on it
-        if (s < HH_SMALL2) {
-            if (ups < 3) {
-                ++ups;
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-                    if (col == j && g + G * r >= j) { X[r].x *= 0x1p400; X[r].y *= 0x1p400; }
-            } else {
-                ups = 0;
+        if (out_of_range(s) && ups < 4 && s < INFINITY) {
+            if (s < HH_SMALL2 && ups == 3) {
+                ups = ex = 0;
                 ++j;
+                continue;
             }
+            const int e = s < HH_SMALL2 ? 400 : -(ilogb(s) / 2);
+            ++ups;
+            ex += e;
+            const double up = ldexp(1.0, e);
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+                if (col == j && g + G * r >= j) { X[r].x *= up; X[r].y *= up; }
             continue;
         }
-        // an alpha below the rounding of sigma counts as zero (its square may be denormal)
+        // an alpha below the rounding of sigma counts as zero (its square may underflow)
         const bool some = a2 > s * 0x1p-106;
         const double is = rsqrt3(s), sigma = s * is;
         const double ia = some ? rsqrt3(a2) : 0.0, d = a2 * ia + sigma, id = recip(d);
@@ -557,8 +571,7 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
         const double2 u = make_double2(col > j ? fma(px.x, is, dot.x * isd) : 0.0,
                                        col > j ? fma(px.y, is, dot.y * isd) : 0.0);
         if (col == j) {
-            beta = make_double2(-ph.x * sigma, -ph.y * sigma);
-            for (int i = 0; i < ups; ++i) { beta.x *= 0x1p-400; beta.y *= 0x1p-400; }
+            beta = make_double2(ldexp(-ph.x * sigma, -ex), ldexp(-ph.y * sigma, -ex));
             tau = d * is;
             fac = make_double2(ph.x * id, ph.y * id);
         }
@@ -570,7 +583,7 @@ __device__ __forceinline__ void reg_factor(double2 (&X)[RT], int rows, int n, do
                 X[r] = make_double2(at ? ph.x * d : X[r].x, at ? ph.y * d : X[r].y);
             }
         reg_take(p, X, u);
-        ups = 0;
+        ups = ex = 0;
         ++j;
     }
 }
