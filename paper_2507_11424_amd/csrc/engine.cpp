@@ -690,6 +690,12 @@ void Engine::set_split(Plan *P, int cfg, int ksplit_hint) {
     }
 }
 
+// Tiles that the FP64 and FP32 kernels with four products have.
+static bool four_products(int cfg) {
+    return cfg == tnk::CFG_64x64 || cfg == tnk::CFG_64x16 || cfg == tnk::CFG_32x32 || cfg == tnk::CFG_16x16 ||
+           cfg == tnk::CFG_64x32 || cfg == tnk::CFG_128x64;
+}
+
 void Engine::set_autotune(bool on, const std::string &cache_path) {
     autotune_ = on;
     tune_path_ = cache_path;
@@ -698,7 +704,8 @@ void Engine::set_autotune(bool on, const std::string &cache_path) {
     std::string k;
     int cfg, ks, pk, f32;
     while (f >> k >> cfg >> ks >> pk >> f32)
-        if (cfg >= 0 && cfg < tnk::CFG_COUNT && ks >= 1) tune_cache_[k] = {cfg, ks, pk ? 1 : 0, f32 == 2 ? 2 : f32 ? 1 : 0};
+        if (cfg >= 0 && cfg < tnk::CFG_COUNT && ks >= 1 && (f32 != 2 || four_products(cfg)))
+            tune_cache_[k] = {cfg, ks, pk ? 1 : 0, f32 == 2 ? 2 : f32 ? 1 : 0};
 }
 
 // Times every candidate (tile configuration x split-K choice) on the call's own
@@ -707,9 +714,10 @@ void Engine::set_autotune(bool on, const std::string &cache_path) {
 void Engine::tune(Plan *P, tnk::GettArgs g) {
     // candidates: tile configuration x K slices, and for split-BF16 shapes that
     // may pack, packed or split while staging (the packing is timed with it)
-    // In the split-BF16 modes the FP32 kernel (same complex64 storage, at least
-    // as accurate) is a candidate too: it can win on shapes whose short K or
-    // narrow N leave the split products little to amortise.
+    // In the split-BF16 modes the FP32 kernel with four products (same complex64
+    // storage) is a candidate too: it can win on shapes whose short K or narrow N
+    // leave the split products little to amortise.  Not the one with three, whose
+    // error is larger than bf16x6's from K = 8 on (9.1e-8 against 8.3e-8 relative).
     struct Cand { int cfg, ks; bool pack; int fp32; };
     std::vector<Cand> cands;
     const bool bf16 = prec == tnk::P_BF16X3 || prec == tnk::P_BF16X6;
@@ -718,7 +726,7 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
                          tnk::CFG_64x32};
     for (int pk = 0; pk < 3; ++pk) {
         const bool pack = pk == 1;
-        const int f32 = pk == 2 ? 1 : 0;
+        const int f32 = pk == 2 ? 2 : 0;
         if (pack && !P->can_pack) continue;
         if (f32 && !bf16) continue;
         for (int c : cfgs) {
@@ -726,7 +734,8 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             if (c == tnk::CFG_128x128W && (!pack || P->kN < 128)) continue;  // packed split-BF16 only
             if (c == tnk::CFG_64x16 && P->kN > 64) continue;
             if ((c == tnk::CFG_16x16 || c == tnk::CFG_64x32) && bf16 && !f32) continue;  // FP64 / FP32 only
-            if (c == tnk::CFG_64x128W && (!bf16 || f32 || P->kN < 128)) continue;  // split-BF16 only
+            if (c == tnk::CFG_64x128W && (!bf16 || P->kN < 128)) continue;  // split-BF16 only
+            if (f32 && !four_products(c)) continue;
             int bm = 64, bn = 64;
             tnk::gett_tile(c, prec, &bm, &bn);
             const int64_t tiles = ((P->kM + bm - 1) / bm) * ((P->kN + bn - 1) / bn) * P->Z;

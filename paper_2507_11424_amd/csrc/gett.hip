@@ -1219,6 +1219,8 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
     if (prec == P_FP64_4M) {
         switch (cfg) {
             case CFG_64x64: return launch_k(gett_mfma<double, 64, 64, 16, 1, 2, 2, false>, a, 64, 64, 256, s);
+            case CFG_128x64: return launch_k(gett_mfma<double, 128, 64, 16, 1, 2, 2, false>, a, 128, 64, 256, s);
+            case CFG_64x16: return launch_k(gett_mfma<double, 64, 16, 16, 2, 4, 1, false>, a, 64, 16, 256, s);
             case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 1, 2, 2, false>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<double, false>(a, s);
             case CFG_64x32: return launch_k(gett_mfma<double, 64, 32, 16, 1, 2, 2, false, 3>, a, 64, 32, 256, s);
@@ -1242,6 +1244,7 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
             // 8 k a step: 128 registers and 17 KiB, four workgroups a CU (262144 x 64 x 8
             // 56 -> 42 us, 256 x 131072 x 32 x 8 1246 -> 1187)
             case CFG_64x64: return launch_k(gett_mfma<float, 64, 64, 8, 1, 2, 2, false, 4>, a, 64, 64, 256, s);
+            case CFG_128x64: return launch_k(gett_mfma<float, 128, 64, 16, 1, 2, 2, false>, a, 128, 64, 256, s);
             case CFG_64x16: return launch_k(gett_mfma<float, 64, 16, 16, 2, 4, 1, false>, a, 64, 16, 256, s);
             case CFG_32x32: return launch_k(gett_mfma<float, 32, 32, 32, 1, 2, 2, false>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<float, false>(a, s);
