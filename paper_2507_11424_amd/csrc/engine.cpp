@@ -348,6 +348,12 @@ static bool pack_pays(const Op &A, const Op &B) {
     return op_rows(A, B) > 128 && op_rows(B, A) > 128;
 }
 
+// Whether a tile has a kernel with four products in this mode.
+static bool four_products(int prec, int cfg) {
+    if (cfg == tnk::CFG_64x64 || cfg == tnk::CFG_32x32 || cfg == tnk::CFG_16x16 || cfg == tnk::CFG_64x32) return true;
+    return prec != tnk::P_FP64 && (cfg == tnk::CFG_64x16 || cfg == tnk::CFG_128x64);
+}
+
 Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
     const Op A = squeeze(A0), B = squeeze(B0), C = squeeze(C0);
     std::ostringstream ks;
@@ -551,6 +557,7 @@ Plan *Engine::plan(const Op &A0, const Op &B0, const Op &C0, bool keep) {
     }
     // a tuned tile or number of slices would sum in another order
     auto tc = keep ? tune_cache_.end() : tune_cache_.find(P->key);
+    if (tc != tune_cache_.end() && tc->second.fp32 == 2 && !four_products(prec, tc->second.cfg)) tc = tune_cache_.end();
     const bool fp_only = tc != tune_cache_.end() && (tc->second.cfg == tnk::CFG_16x16 || tc->second.cfg == tnk::CFG_64x32);
     if (tc != tune_cache_.end() && (!fp_only || prec == tnk::P_FP64 || prec == tnk::P_FP32 || tc->second.fp32)) {
         P->pack = P->can_pack && tc->second.pack;
@@ -690,12 +697,6 @@ void Engine::set_split(Plan *P, int cfg, int ksplit_hint) {
     }
 }
 
-// Tiles that the FP64 and FP32 kernels with four products have.
-static bool four_products(int cfg) {
-    return cfg == tnk::CFG_64x64 || cfg == tnk::CFG_64x16 || cfg == tnk::CFG_32x32 || cfg == tnk::CFG_16x16 ||
-           cfg == tnk::CFG_64x32 || cfg == tnk::CFG_128x64;
-}
-
 void Engine::set_autotune(bool on, const std::string &cache_path) {
     autotune_ = on;
     tune_path_ = cache_path;
@@ -704,7 +705,7 @@ void Engine::set_autotune(bool on, const std::string &cache_path) {
     std::string k;
     int cfg, ks, pk, f32;
     while (f >> k >> cfg >> ks >> pk >> f32)
-        if (cfg >= 0 && cfg < tnk::CFG_COUNT && ks >= 1 && (f32 != 2 || four_products(cfg)))
+        if (cfg >= 0 && cfg < tnk::CFG_COUNT && ks >= 1)
             tune_cache_[k] = {cfg, ks, pk ? 1 : 0, f32 == 2 ? 2 : f32 ? 1 : 0};
 }
 
@@ -735,7 +736,7 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             if (c == tnk::CFG_64x16 && P->kN > 64) continue;
             if ((c == tnk::CFG_16x16 || c == tnk::CFG_64x32) && bf16 && !f32) continue;  // FP64 / FP32 only
             if (c == tnk::CFG_64x128W && (!bf16 || P->kN < 128)) continue;  // split-BF16 only
-            if (f32 && !four_products(c)) continue;
+            if (f32 && !four_products(prec, c)) continue;
             int bm = 64, bn = 64;
             tnk::gett_tile(c, prec, &bm, &bn);
             const int64_t tiles = ((P->kM + bm - 1) / bm) * ((P->kN + bn - 1) / bn) * P->Z;

@@ -381,6 +381,9 @@ __device__ __forceinline__ void gett_block(const GettArgs &p, int tile, int b0, 
     }
 }
 
+// OCC: workgroups of four waves on a CU that the registers leave room for.  Three of
+// the FP64 64x32 tile are 168 registers: with three products two are spilled (12
+// bytes a lane), with four none; the figures of choose_tile are with that spill.
 template <typename T, int BM, int BN, int BK, int D, int WGM, int WGN, bool G3, int OCC = 2>
 __global__ void __launch_bounds__(64 * WGM * WGN, OCC)
 gett_mfma(GettArgs p) {
@@ -625,7 +628,8 @@ gett_bf16_direct(GettArgs p) {
     static_assert(LA >= 2 && LB >= 2 && LA % 2 == 0 && LB % 2 == 0 && NT % (BK / 2) == 0 && NT >= BM && NT >= BN, "tile");
     // two LDS stages when they fit in the 160 KiB of a CU, else one; one for the narrow
     // tile, whose problems are long, thin and short in K: four workgroups on a CU cover
-    // for the second stage (2097152 x 16 x 64 in bf16x6 495 -> 350 us)
+    // for the second stage (2097152 x 16 x 64 in bf16x6 495 -> 350 us, with the 4 and
+    // 8 registers that bf16x3 and bf16x6 spill in 128)
     constexpr int S = BN > 16 && (2 * 2 * NP * (BM + BN) * KP * 2 <= 160 * 1024) ? 2 : 1;
     // planes: [stage][re/im][part][row][k]
     __shared__ __attribute__((aligned(16))) unsigned short sA[S][2][NP][BM][KP];
@@ -862,7 +866,9 @@ __global__ void __launch_bounds__(256) k_pack_bf16(const float2 *X, const int64_
 // Split-BF16 GEMM on packed operands (see k_pack_bf16): p.A / p.B are the
 // packed planes (rows M / N, p.kpad columns), p.a_bytes / p.b_bytes one batch
 // item's planes.  Each stage copies 16-byte chunks (8 k values of one plane
-// row) through LDS; rows past M / N read as zero (buffer range check).
+// row) through LDS; rows past M / N read as zero (buffer range check).  The tiles
+// on eight waves have 256 registers a lane, of which bf16x6 spills 6 at 128x64 and
+// 64x128 and 32 at 128x128 (28 and 132 bytes a lane; bf16x3 none).
 template <int NP, int BM, int BN, int WGM, int WGN, bool PF2 = true>
 __global__ void __launch_bounds__(64 * WGM * WGN)
 gett_bf16(GettArgs p) {
@@ -1219,8 +1225,6 @@ static hipError_t launch_main(const GettArgs &a, int prec, int cfg, hipStream_t 
     if (prec == P_FP64_4M) {
         switch (cfg) {
             case CFG_64x64: return launch_k(gett_mfma<double, 64, 64, 16, 1, 2, 2, false>, a, 64, 64, 256, s);
-            case CFG_128x64: return launch_k(gett_mfma<double, 128, 64, 16, 1, 2, 2, false>, a, 128, 64, 256, s);
-            case CFG_64x16: return launch_k(gett_mfma<double, 64, 16, 16, 2, 4, 1, false>, a, 64, 16, 256, s);
             case CFG_32x32: return launch_k(gett_mfma<double, 32, 32, 32, 1, 2, 2, false>, a, 32, 32, 256, s);
             case CFG_16x16: return launch_wave<double, false>(a, s);
             case CFG_64x32: return launch_k(gett_mfma<double, 64, 32, 16, 1, 2, 2, false, 3>, a, 64, 32, 256, s);
