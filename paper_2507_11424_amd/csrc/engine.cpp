@@ -740,6 +740,12 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             int bm = 64, bn = 64;
             tnk::gett_tile(c, prec, &bm, &bn);
             const int64_t tiles = ((P->kM + bm - 1) / bm) * ((P->kN + bn - 1) / bn) * P->Z;
+            // the small tiles only around their lines (see choose_tile): timed on every
+            // large shape as well, they made a tuned first call a fifth longer
+            if (c == tnk::CFG_16x16 && tiles > 1024 && P->kM > 16 && P->kN > 1) continue;
+            if (c == tnk::CFG_16x16 && tiles > 1 << 22) continue;  // (a launch's threads)
+            if (c == tnk::CFG_32x32 && tiles > 2048 && P->kM > 32) continue;
+            if (c == tnk::CFG_64x32 && P->kN > 64 && P->K > 128) continue;
             cands.push_back({c, 1, pack, f32});
             // K slices only pay when the output tiles leave CUs idle
             if (tiles >= 1024) continue;
