@@ -1101,9 +1101,16 @@ tnk::GettArgs Engine::args_of(const Plan &P, const Op &A, const Op &B, const Op 
     return g;
 }
 
+// The kinds of blocks in a group: tiles with three products, which all add K in the
+// same order, and sums of one term.
+static constexpr int GROUP_CFG[] = {tnk::CFG_64x64, tnk::CFG_64x16, tnk::CFG_64x32, tnk::CFG_32x32, tnk::CFG_K1};
+
 // A grouped contraction keeps the K slices that the planner gives the same
-// contraction on its own, so it is the same sum in the same order; the tile is
-// the narrow one for at most 16 columns (the planner's line).
+// contraction on its own, so it is the same sum in the same order, whatever the
+// tile: the narrow one for at most 16 columns, 32x32 for up to 32 rows (a message of a
+// bond of 20 fills 10 % of 64x64 and 39 % of it), 64x32 up to 32 columns or 64 terms.
+// A layer with 60 sweeps a colour group of the 105-qubit rotated square at D = 20:
+// 1.64 s on 64x64 and 64x16 alone, 0.91 with these (1.39 one by one on tuned tiles).
 void Engine::group_add(Group &gr, const Op &A, const Op &B, const Op &C) {
     if (prec != tnk::P_FP64 || A.esz != 16 || B.esz != 16 || C.esz != 16)
         throw TnError(ST_INVALID, "grouped contractions are FP64");
@@ -1116,57 +1123,58 @@ void Engine::group_add(Group &gr, const Op &A, const Op &B, const Op &C) {
         return;
     }
     tnk::GettArgs g = args_of(*P, A, B, C, false);
-    const int c = P->K == 1 ? 2 : P->kN <= 16 ? 1 : 0;
-    const int bm = 64, bn = c == 1 ? 16 : 64;
+    const int c = P->K == 1 ? 4 : P->kN <= 16 ? 1 : P->kM <= 32 ? 3 : P->kN <= 32 || P->K <= 64 ? 2 : 0;
+    int bm = 0, bn = 0;
+    tnk::gett_tile(GROUP_CFG[c], prec, &bm, &bn);
     if (g.ksplit > 1) {
         g.part = pool_.get((size_t)g.ksplit * g.batch * (size_t)g.M * g.N * 16);
         gr.mem.push_back(g.part);
     }
     const int id = (int)gr.args.size();
-    const int tiles = c == 2 ? (int)(((int64_t)g.M * g.N + 255) / 256) : ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+    const int tiles = c == 4 ? (int)(((int64_t)g.M * g.N + 255) / 256) : ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
     for (int z = 0; z < g.ksplit; ++z)
         for (int b = 0; b < g.batch; ++b)
             for (int t = 0; t < tiles; ++t) gr.blk[c].push_back({id, t, b, z});
     if (g.ksplit > 1)
         for (int64_t e = 0; e < (int64_t)g.M * g.N * g.batch; e += 256) gr.red.push_back({id, (int)(e / 256), 0, 0});
-    if (c < 2) gr.ktab[c] = std::max(gr.ktab[c], (g.a_kaff ? 0 : g.kchunk) + (g.b_kaff ? 0 : g.kchunk));
+    if (c < 4) gr.ktab[c] = std::max(gr.ktab[c], (g.a_kaff ? 0 : g.kchunk) + (g.b_kaff ? 0 : g.kchunk));
     gr.flops += P->flops;
     gr.bytes += 16.0 * P->Z * ((double)P->kM * P->K + (double)P->K * P->kN + (double)P->kM * P->kN);
     gr.args.push_back(g);
 }
 
 void Engine::group_run(Group &gr) {
-    static const int cfg[3] = {tnk::CFG_64x64, tnk::CFG_64x16, tnk::CFG_K1};
+    constexpr int NK = Group::NK;
     if (!gr.tab && !gr.args.empty()) {
-        size_t off[5], end = 0;
+        size_t off[NK + 2], end = 0;
         auto place = [&](int i, const void *src, size_t bytes) {
             off[i] = end;
             end += (bytes + 15) & ~size_t(15);
             gr.host.resize(end);
             if (bytes) std::memcpy(gr.host.data() + off[i], src, bytes);
         };
-        for (int i = 0; i < 4; ++i) {
-            const std::vector<tnk::GroupBlock> &b = i < 3 ? gr.blk[i] : gr.red;
+        for (int i = 0; i <= NK; ++i) {
+            const std::vector<tnk::GroupBlock> &b = i < NK ? gr.blk[i] : gr.red;
             place(i, b.data(), b.size() * sizeof(tnk::GroupBlock));
         }
-        place(4, gr.args.data(), gr.args.size() * sizeof(tnk::GettArgs));
+        place(NK + 1, gr.args.data(), gr.args.size() * sizeof(tnk::GettArgs));
         char *d = static_cast<char *>(pool_.get(end));
         gr.mem.push_back(d);
         // gr.host lives until group_free, which synchronises
         TN_HIP(hipMemcpyAsync(d, gr.host.data(), end, hipMemcpyHostToDevice, s));
-        for (int i = 0; i < 4; ++i) gr.dblk[i] = reinterpret_cast<const tnk::GroupBlock *>(d + off[i]);
-        gr.tab = reinterpret_cast<const tnk::GettArgs *>(d + off[4]);
+        for (int i = 0; i <= NK; ++i) gr.dblk[i] = reinterpret_cast<const tnk::GroupBlock *>(d + off[i]);
+        gr.tab = reinterpret_cast<const tnk::GettArgs *>(d + off[NK + 1]);
     }
     for (const auto &d : gr.direct) contract(d.A, d.B, d.C);
     if (gr.args.empty()) return;
     EvPair *ev = timing ? next_pair(0) : nullptr;
     if (ev) TN_HIP(hipEventRecord(ev->a, s));
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < NK; ++i) {
         if (gr.blk[i].empty()) continue;
-        TN_HIP(tnk::launch_gett_group(gr.tab, gr.dblk[i], (int)gr.blk[i].size(), cfg[i], gr.ktab[i], s));
+        TN_HIP(tnk::launch_gett_group(gr.tab, gr.dblk[i], (int)gr.blk[i].size(), GROUP_CFG[i], gr.ktab[i], s));
         ctr.gemm_launches += 1;
     }
-    if (!gr.red.empty()) TN_HIP(tnk::launch_reduce_group(gr.tab, gr.dblk[3], (int)gr.red.size(), s));
+    if (!gr.red.empty()) TN_HIP(tnk::launch_reduce_group(gr.tab, gr.dblk[NK], (int)gr.red.size(), s));
     if (ev) TN_HIP(hipEventRecord(ev->b, s));
     ctr.gemm_flops += gr.flops;
     ctr.gemm_bytes += gr.bytes;

@@ -194,14 +194,15 @@ class Engine {
     // fixed when they are added), then free it.
     struct Group {
         std::vector<tnk::GettArgs> args;
-        std::vector<tnk::GroupBlock> blk[3], red;   // 64x64 tiles, 64x16 tiles, K = 1; split-K sums
-        int ktab[3] = {0, 0, 0};                    // k table entries a workgroup stages
+        static constexpr int NK = 5;                // kinds of blocks (see group_run)
+        std::vector<tnk::GroupBlock> blk[NK], red;  // by kind; split-K sums
+        int ktab[NK] = {0, 0, 0, 0, 0};             // k table entries a workgroup stages
         struct Direct { Op A, B, C; };
         std::vector<Direct> direct;                 // operands above the kernel's windows: run one by one
         std::vector<void *> mem;                    // device tables, split-K partials
         std::vector<char> host;                     // the tables as uploaded
         const tnk::GettArgs *tab = nullptr;
-        const tnk::GroupBlock *dblk[4] = {nullptr, nullptr, nullptr, nullptr};
+        const tnk::GroupBlock *dblk[NK + 1] = {};
         double flops = 0, bytes = 0;
     };
     void group_add(Group &g, const Op &A, const Op &B, const Op &C);

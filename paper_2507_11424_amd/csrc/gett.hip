@@ -511,8 +511,8 @@ gett_wave(GettArgs p) {
 // 8 us whatever its size, and a BP sweep has about a hundred.  Together they are
 // four to eight launches: tn_bp on the 12 x 12 brick at D = 8 went from 36 to 6.8
 // ms, a Trotter layer of the 129-qubit heavy-hex at D = 16 from 257 to 53 ms.
-template <typename T, int BM, int BN, int BK, int D, int WGM, int WGN>
-__global__ void __launch_bounds__(64 * WGM * WGN, 2)
+template <typename T, int BM, int BN, int BK, int D, int WGM, int WGN, int OCC = 2>
+__global__ void __launch_bounds__(64 * WGM * WGN, OCC)
 gett_group(const GettArgs *tab, const GroupBlock *blk) {
     __shared__ GettTiles<T, BM, BN, BK> sm;
     extern __shared__ int ktab[];
@@ -1180,6 +1180,8 @@ hipError_t launch_gett_group(const GettArgs *tab, const GroupBlock *blk, int nbl
     switch (cfg) {
         case CFG_64x64: return go(gett_group<double, 64, 64, 16, 1, 2, 2>);
         case CFG_64x16: return go(gett_group<double, 64, 16, 16, 2, 4, 1>);
+        case CFG_64x32: return go(gett_group<double, 64, 32, 16, 1, 2, 2, 3>);
+        case CFG_32x32: return go(gett_group<double, 32, 32, 32, 1, 2, 2>);
         case CFG_K1: return go(gett_group_k1);
         default: return hipErrorInvalidValue;
     }
