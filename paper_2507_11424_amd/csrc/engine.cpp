@@ -745,7 +745,8 @@ void Engine::tune(Plan *P, tnk::GettArgs g) {
             if (c == tnk::CFG_16x16 && tiles > 1024 && P->kM > 16 && P->kN > 1) continue;
             if (c == tnk::CFG_16x16 && tiles > 1 << 22) continue;  // (a launch's threads)
             if (c == tnk::CFG_32x32 && tiles > 2048 && P->kM > 32) continue;
-            if (c == tnk::CFG_64x32 && P->kN > 64 && P->K > 128) continue;
+            if (c == tnk::CFG_64x32 && P->kN > 64 && P->K > 64) continue;
+            if (c == tnk::CFG_64x128W && P->kM >= 256) continue;
             cands.push_back({c, 1, pack, f32});
             // K slices only pay when the output tiles leave CUs idle
             if (tiles >= 1024) continue;
