@@ -1241,7 +1241,7 @@ static Op view(void *p, const std::string &idx, std::vector<int> dims, std::vect
 // Tall matrices with R that may have any rank (the rows of the exact product): the
 // register tree walks 128 rows a level, one block after another on a lone path,
 // while the CholeskyQR passes spread over the chip; an item whose Gram matrix says
-// that it is rank-deficient goes through the tree after all.  4096 x 64: 1435 us by
+// that it is rank-deficient goes through the tree after all.  4096 x 64: 1457 us by
 // the tree, 183 by the passes (24 of it the tree's launches that find no flag); 512 x 32
 // 253 and 82; up to 16 columns or in one block of the tree it is as fast or faster.
 void Engine::factor(const tnk::QrArgs &a) {

@@ -156,10 +156,10 @@ class Engine {
     // Set by the simple update: Householder QR and the contractions keep the order
     // of their sums (the LDS kernels; the tiles and K slices of the rule in plan(),
     // which the tuner leaves alone).  Its pair SVD is a one-sided Jacobi, which
-    // multiplies columns by the phases of products that are rounding residue where columns are
-    // already orthogonal, so the phases of the singular vectors, and with them
-    // the updated site tensors, depend on the last bit of its input: another
-    // order of summation gives the same state in another gauge.
+    // multiplies columns by the phases of products that are rounding residue where
+    // columns are already orthogonal, so the phases of the singular vectors, and
+    // with them the updated site tensors, depend on the last bit of its input:
+    // another order of summation gives the same state in another gauge.
     bool keep_sums = false;
     // BF16x3 keeps them too, and every product with a tensor that happens to be an
     // identity: each product of the mode rounds to 16 bits, so another gauge of a

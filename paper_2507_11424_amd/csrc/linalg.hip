@@ -343,8 +343,8 @@ __global__ void __launch_bounds__(QR_NT) k_qr_form(FormArgs a) {
 // d = |x_j| + sigma, with its factor f = ph / d in the column's lanes:
 // v = conj(f) p, v_j = 1.  At the top of the tree the reflectors, still in
 // registers, are applied to the identity in the same launch.  Measured against
-// the LDS kernels (five barriers a step), Q and R: 128 x 64 234 for 600 us, 4096 x
-// 64 1.43 for 3.69 ms, 128 x 32 123 for 346, 32 of 128 x 16 30 for 234, 64 x 16 24
+// the LDS kernels (five barriers a step), Q and R: 128 x 64 237 for 600 us, 4096 x
+// 64 1.46 for 3.69 ms, 128 x 32 122 for 346, 32 of 128 x 16 29 for 234, 64 x 16 24
 // for 109; with the pivot column through shuffles or twice a step, and divisions and
 // square roots of the library, 339, 2.08, 141, 48 and 46.  512 threads serve 64 columns as well as 256 (338 and 367 us; 1024: 474);
 // up to 32 columns 256 are no slower than 512 and leave room for more blocks.
